@@ -8,7 +8,7 @@ HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 OUT = os.path.join(HERE, "libsara.so")
-SOURCES = ["model_kernels.hip", "controller_kernels.hip", "sara_api.hip"]
+SOURCES = ["model_kernels.hip", "prefill_kernels.hip", "controller_kernels.hip", "sara_api.hip"]
 FLAGS = ["-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",
          # packed fp32 arithmetic is left to no code path (all HIP sources)
          "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",

@@ -17,18 +17,12 @@
 
 #include "sara_internal.h"
 
-#include <hip/hip_ext.h>
-
 #include <math.h>
 #include <string.h>
 
 #include <algorithm>
 
 namespace sara {
-
-typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 
 // ---------------------------------------------------------------------------
 // block reductions (fixed tree order -> deterministic)
@@ -1029,186 +1023,6 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
   }
 }
 
-// bf16 paged GQA attention on the MFMA.  Block (row i, KV head g, split c)
-// covers KV pages [c*kAttnChunks, (c+1)*kAttnChunks) of the row's sequence
-// (prompt pages, then private pages; each page holds up to 16 positions);
-// its 4 waves take every 4th page.  Per page and wave:
-//   S^T = K q^T  (16 tokens x 16 padded heads, v_mfma_f32_16x16x32_bf16; the
-//                 lane supplying token l%16 of K and head l%16 of q reads the
-//                 same HD/4 dimensions, so the k order inside the MFMA is moot)
-//   online softmax per head (the 4 lanes holding one head's 16 scores)
-//   O += P V     (v_mfma_f32_16x16x16bf16_1k; the score registers are already
-//                 the A operand's layout, V^T pages give the B operand; P is
-//                 split into bf16 hi + lo parts, two MFMAs)
-// The 4 waves' (max, sum, O) are merged in LDS into one partial per split.
-//
-template <int HD>
-__global__ __launch_bounds__(256) void k_attn_mfma(const int32_t* __restrict__ M_ptr,
-    const RowDesc* __restrict__ rows, const uint16_t* __restrict__ qbuf,
-    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
-    const int32_t* __restrict__ btab, int MAXB, int PB, int layer, int64_t n_blocks, int hq,
-    int hkv, int n_splits, float scale, float* __restrict__ part) {
-  typedef short short4_ __attribute__((ext_vector_type(4)));
-  constexpr int DPL = HD / 4;     // dims per lane in the QK^T operands
-  constexpr int NCC = HD / 32;    // 16x16x32 MFMAs per page for QK^T
-  constexpr int NT = HD / 16;     // output tiles of 16 dims
-  __shared__ float m_w[4][16], l_w[4][16];
-  __shared__ float o_w[4][16][HD + 1];
-  // persistent over work items (split c, row i, KV head g), split-major, so
-  // that no block waits only to find its row absent
-  const int M = *M_ptr;
-  const int total = M * hkv * n_splits;
-  for (int item = blockIdx.x; item < total; item += gridDim.x) {
-  const int c = item / (M * hkv);
-  const int i = (item - c * M * hkv) / hkv, g = item % hkv;
-  const RowDesc r = rows[i];
-  const int ctx = r.pos + 1;
-  const int pl = min(ctx, r.plen);                      // prompt positions attended
-  const int pc = (pl + 15) >> 4;                         // prompt pages
-  const int vcnt = ctx - pl;                             // private positions
-  const int nch = pc + ((vcnt + 15) >> 4);
-  const int ch0 = c * kAttnChunks;
-  if (ch0 >= nch) continue;
-  const int ch1 = min(nch, ch0 + kAttnChunks);
-  const int G = hq / hkv;
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int row = lane & 15, grp = lane >> 4;
-  // per-wave softmax state and output accumulators; q operand (set below)
-  float m_run = -INFINITY, l_run = 0.f;
-  f32x4 o[NT];
-#pragma unroll
-  for (int t = 0; t < NT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  uint4 qv[NCC];
-  const int32_t* bt = btab + (size_t)r.tab * MAXB;
-  // Block-table entries of this split's pages, one per lane 0..15, shared by
-  // shuffles (no table load on the page path).
-  int my_blk = 0;
-  if (lane < kAttnChunks && ch0 + lane < ch1) {
-    const int cl = ch0 + lane;
-    my_blk = bt[(cl < pc) ? cl : PB + (cl - pc)];
-  }
-  // Two page slots per wave: the next page's K, V (and its valid count) are
-  // loaded while the current one is processed.  Loads past the wave's last
-  // page re-read its first page (always valid) and are never used.
-  typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-  struct Pg { u32x4 k[NCC]; u32x2 v[NT]; int n; };
-  auto load_page = [&](Pg& P, int ch) {
-    const int cv = (ch < ch1) ? ch : (ch0 + wave);
-    int n;
-    if (cv < pc) n = min(16, pl - 16 * cv);
-    else n = min(16, vcnt - 16 * (cv - pc));
-    P.n = (ch < ch1) ? n : 0;
-    const int blk = __shfl(my_blk, cv - ch0, 64);
-    const size_t pg = ((size_t)layer * n_blocks + blk) * hkv + g;
-    const u32x4* kp = (const u32x4*)(kc + (pg * kBlockTok + row) * HD + DPL * grp);
-#pragma unroll
-    for (int cc = 0; cc < NCC; ++cc) P.k[cc] = kp[cc];
-    const uint16_t* vp = vc + pg * (size_t)HD * kBlockTok + 4 * grp;
-#pragma unroll
-    for (int t = 0; t < NT; ++t) P.v[t] = *(const u32x2*)(vp + (size_t)(16 * t + row) * kBlockTok);
-  };
-  auto process_page = [&](const Pg& P) {
-    const int n = P.n;
-    // S^T[token][head]
-    f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int cc = 0; cc < NCC; ++cc)
-      sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, P.k[cc]),
-                                                   __builtin_bit_cast(bf16x8, qv[cc]), sc, 0, 0, 0);
-    // lane holds tokens 4*grp + q (q < 4) of head `row`
-    float sv[4];
-    float mt = -INFINITY;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      sv[q] = (4 * grp + q < n) ? sc[q] * scale : -INFINITY;
-      mt = fmaxf(mt, sv[q]);
-    }
-    mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-    mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-    const float mn = fmaxf(m_run, mt);
-    const float alpha = expf(m_run - mn);
-    // P enters the MFMA as a bf16 pair hi + lo (|p - hi - lo| <= 2^-16 p), so
-    // the PV product keeps fp32 accuracy without a bf16 rounding point
-    float ps = 0.f;
-    uint16_t pb[4], plo[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float pv = expf(sv[q] - mn);
-      uint16_t bb = f32_to_bf16(pv);
-      pb[q] = bb;
-      plo[q] = f32_to_bf16(pv - bf16_to_f32(bb));
-      ps += pv;
-    }
-    ps += __shfl_xor(ps, 16, 64);
-    ps += __shfl_xor(ps, 32, 64);
-    l_run = l_run * alpha + ps;
-    m_run = mn;
-    // rows of O are heads 4*grp + q: fetch their rescale factors
-    float al[4];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) al[q] = __shfl(alpha, 4 * grp + q, 64);
-    short4_ pa, pa_lo;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) { pa[q] = (short)pb[q]; pa_lo[q] = (short)plo[q]; }
-#pragma unroll
-    for (int t = 0; t < NT; ++t) {
-      // positions beyond the page's n valid tokens may hold stale bits: zero them
-      short4_ vb;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        uint32_t w = (q < 2) ? P.v[t].x : P.v[t].y;
-        uint16_t h = (uint16_t)((q & 1) ? (w >> 16) : (w & 0xFFFF));
-        vb[q] = (short)((4 * grp + q < n) ? h : (uint16_t)0);
-      }
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o[t][q] *= al[q];
-      o[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vb, o[t], 0, 0, 0);
-      o[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa_lo, vb, o[t], 0, 0, 0);
-    }
-  };
-  Pg pa_, pb_;
-  load_page(pa_, ch0 + wave);
-  // q operand: head `row` of this KV group (zero beyond G), dims [DPL*grp, DPL*grp + DPL)
-  if (row < G) {
-    const uint4* qp = (const uint4*)(qbuf + ((size_t)i * hq + g * G + row) * HD + DPL * grp);
-#pragma unroll
-    for (int cc = 0; cc < NCC; ++cc) qv[cc] = qp[cc];
-  } else {
-#pragma unroll
-    for (int cc = 0; cc < NCC; ++cc) qv[cc] = make_uint4(0, 0, 0, 0);
-  }
-  for (int ch = ch0 + wave; ch < ch1; ch += 8) {
-    load_page(pb_, ch + 4);
-    process_page(pa_);
-    if (ch + 4 >= ch1) break;
-    load_page(pa_, ch + 8);
-    process_page(pb_);
-  }
-  // merge the 4 waves: lane `row` (grp 0) holds head row's (m, l); O rows are heads 4*grp + q
-  if (grp == 0) { m_w[wave][row] = m_run; l_w[wave][row] = l_run; }
-#pragma unroll
-  for (int t = 0; t < NT; ++t)
-#pragma unroll
-    for (int q = 0; q < 4; ++q) o_w[wave][4 * grp + q][16 * t + row] = o[t][q];
-  __syncthreads();
-  for (int e = threadIdx.x; e < G * HD; e += 256) {
-    int h = e / HD, dd = e - h * HD;
-    float mx = fmaxf(fmaxf(m_w[0][h], m_w[1][h]), fmaxf(m_w[2][h], m_w[3][h]));
-    float num = 0.f, den = 0.f;
-#pragma unroll
-    for (int w = 0; w < 4; ++w) {
-      float wt = (m_w[w][h] == -INFINITY) ? 0.f : expf(m_w[w][h] - mx);
-      num += wt * o_w[w][h][dd];
-      den += wt * l_w[w][h];
-    }
-    float* dst = part + ((((size_t)i * hkv + g) * n_splits + c) * kMaxGroup + h) * (HD + 2);
-    dst[dd] = num;
-    if (dd == 0) { dst[HD] = mx; dst[HD + 1] = den; }
-  }
-  __syncthreads();   // LDS is reused by the next item
-  }
-}
-
 // Fused q|k|v projection of the decode rows with the rotary / KV-append
 // epilogue (bf16 weights in rotation-pair order, see qkv_pair_col).  Block =
 // one 16-row weight tile; its 4 waves take a quarter of K each and stream
@@ -2031,21 +1845,6 @@ __global__ void k_copy_logits(const Ctl* __restrict__ ctl, const RowDesc* __rest
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-// Kernel launch on a context's stream.  While a per-kernel profile record is
-// open (prof_begin), the launch goes through hipExtLaunchKernelGGL with the
-// record's event pair, so the dispatch itself stamps the kernel's start and
-// end: the elapsed time is the kernel's own duration, as in a kernel trace.
-template <typename F, typename... Args>
-static void launch_k(sara_ctx* c, hipStream_t st, F kernel, dim3 grid, dim3 block, uint32_t shm, Args... args) {
-  const int p = c->prof_pending;
-  if (p >= 0) {
-    c->prof_pending = -1;
-    c->prof_last = p;
-    hipExtLaunchKernelGGL(kernel, grid, block, shm, st, c->prof_events[p], c->prof_events[p + 1], 0u, args...);
-  } else {
-    hipLaunchKernelGGL(kernel, grid, block, shm, st, args...);
-  }
-}
 static int gemm(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap,
                 int N, int K, int& splits_out, int max_splits = 1 << 30, bool oproj = false) {
   int64_t stride = (int64_t)M_cap * N;
@@ -2156,12 +1955,6 @@ static int qkv_spread(sara_ctx* c, F kernel) {
   return c->qkv_spread;
 }
 
-// persistent attention grid: enough blocks for two per CU, never more than items
-static int attn_grid(sara_ctx* c, int M_cap) {
-  int items = M_cap * c->hkv * c->attn_splits_max;
-  return std::max(1, std::min(items, 1024));
-}
-
 // h += split-K sum of ws; x = RMSNorm(h) * w
 template <typename T>
 static void residual_norm(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w, int x_tiled = 0) {
@@ -2191,7 +1984,7 @@ static void residual_norm(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, 
 }
 
 template <typename T, int HD>
-static void layers_T(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_norm_out) {
+static void layers_T(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_norm_out, int chunk) {
   hipStream_t st = c->stream;
   const int d = c->d;
   const int64_t stride_qkv = (int64_t)M_cap * c->nqkv;
@@ -2251,21 +2044,20 @@ static void layers_T(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_no
                        c->PB, (T*)c->qbuf, (T*)c->kc, (T*)c->vc, mfma_attn ? 1 : 0);
     PROF_E(c, kPQkv, c->nqkv, 0);
     PROF_B(c);
-    if (mfma_attn)
-      launch_k(c, st, (k_attn_mfma<HD>), dim3(attn_grid(c, M_cap)), dim3(256), 0,
-                         M_ptr, c->rows, (const uint16_t*)c->qbuf, (const uint16_t*)c->kc,
-                         (const uint16_t*)c->vc, c->btab, c->MAXB, c->PB, l, c->n_blocks, c->hq, c->hkv,
-                         c->attn_splits_max, 1.0f / sqrtf((float)HD), c->attn_part);
-    else
+    if (mfma_attn) {
+      launch_attn_prefill(c, chunk, l);
+      PROF_E(c, kPAttn, 0, 0);
+    } else {
       launch_k(c, st, (k_attention<T, HD>), dim3(M_cap, c->hkv, c->attn_splits_max), dim3(256), 0,
                          M_ptr, c->rows, (const T*)c->qbuf, (const T*)c->kc, (const T*)c->vc, c->btab,
                          c->MAXB, c->PB, l, c->n_blocks, c->hq, c->hkv, c->attn_splits_max,
                          1.0f / sqrtf((float)HD), c->attn_part);
-    PROF_E(c, kPAttn, 0, 0);
-    PROF_B(c);
-    launch_k(c, st, (k_attn_combine<T, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows,
-                       c->attn_part, c->hq, c->hkv, c->attn_splits_max, mfma_attn ? kAttnChunks : 0, 0, x);
-    PROF_E(c, kPCombine, 0, 0);
+      PROF_E(c, kPAttn, 0, 0);
+      PROF_B(c);
+      launch_k(c, st, (k_attn_combine<T, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows,
+                         c->attn_part, c->hq, c->hkv, c->attn_splits_max, 0, 0, x);
+      PROF_E(c, kPCombine, 0, 0);
+    }
     }
     PROF_B(c);
     gemm(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, sp, 1 << 30, true);
@@ -2306,9 +2098,9 @@ static void layers_T(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_no
 }
 
 template <typename T>
-static void layers(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_norm_out) {
-  if (c->hd == 128) layers_T<T, 128>(c, M_ptr, M_cap, final_norm_out);
-  else layers_T<T, 64>(c, M_ptr, M_cap, final_norm_out);
+static void layers(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_norm_out, int chunk = 0) {
+  if (c->hd == 128) layers_T<T, 128>(c, M_ptr, M_cap, final_norm_out, chunk);
+  else layers_T<T, 64>(c, M_ptr, M_cap, final_norm_out, chunk);
 }
 
 int launch_prefill(sara_ctx* c) {
@@ -2318,7 +2110,8 @@ int launch_prefill(sara_ctx* c) {
   std::vector<int64_t> pre(c->U + 1, 0);
   for (int u = 0; u < c->U; ++u) pre[u + 1] = pre[u] + (c->h_off[u + 1] - c->h_off[u] - 1);
   int64_t rows_total = pre[c->U];
-  for (int64_t r0 = 0; r0 < rows_total; r0 += c->prefill_rows) {
+  int chunk = 0;
+  for (int64_t r0 = 0; r0 < rows_total; r0 += c->prefill_rows, ++chunk) {
     int n = (int)((rows_total - r0 < c->prefill_rows) ? rows_total - r0 : c->prefill_rows);
     launch_k(c, st, k_prefill_rows, dim3((n + 255) / 256), dim3(256), 0, c->pre, c->U, (int)r0,
                        n, c->tok, c->off, c->S, c->rows, c->rows_M, c->PB);
@@ -2326,7 +2119,7 @@ int launch_prefill(sara_ctx* c) {
       launch_k(c, st, k_embed_norm<uint16_t>, dim3(n), dim3(256), 0, c->rows_M, c->rows,
                          (const uint16_t*)c->embed, c->norms, c->d, c->md.rms_eps, c->h,
                          (uint16_t*)c->x);
-      layers<uint16_t>(c, c->rows_M, n, false);
+      layers<uint16_t>(c, c->rows_M, n, false, chunk);
     } else {
       launch_k(c, st, k_embed_norm<float>, dim3(n), dim3(256), 0, c->rows_M, c->rows,
                          (const float*)c->embed, c->norms, c->d, c->md.rms_eps, c->h, (float*)c->x);

@@ -225,8 +225,7 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   c->elt = (md->dtype == SARA_BF16) ? 2 : 4;
   c->prefill_rows = 4096;
   c->row_cap = std::max(c->S, c->prefill_rows);
-  c->attn_splits_max = std::max((c->max_pos + kAttnSplit - 1) / kAttnSplit,
-                                (c->MAXB + kAttnChunks - 1) / kAttnChunks);
+  c->attn_splits_max = (c->max_pos + kAttnSplit - 1) / kAttnSplit;
   c->dec_splits_max = (c->MAXB + kDecPages - 1) / kDecPages;
   {
     // split-K partials of the VALU / MFMA GEMMs that write fp32 (the GEMM
@@ -282,6 +281,7 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->off, sizeof(int32_t) * (c->U + 1));
   ALLOC(c->pre, sizeof(int32_t) * (c->U + 1));
   ALLOC(c->p, sizeof(double) * c->U);
+  if (md->dtype == SARA_BF16) ALLOC(c->pf_tiles, sizeof(int4) * (size_t)max_prefill_tiles(c));
   ALLOC(c->flen, sizeof(int32_t) * (size_t)c->U * c->k);
   // controller
   ALLOC(c->ctl, sizeof(Ctl));
@@ -317,9 +317,10 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->qbuf, (size_t)c->row_cap * c->qdim * E);
   ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
   ALLOC(c->ws, sizeof(float) * (size_t)c->ws_floats);
+  // context-split partials: fp32 attention (every row), bf16 decode rows
   ALLOC(c->attn_part, sizeof(float) *
-                          (size_t)std::max((int64_t)c->row_cap * c->attn_splits_max,
-                                           (int64_t)c->S * c->dec_splits_max) *
+                          (size_t)(md->dtype == SARA_BF16 ? (int64_t)c->S * c->dec_splits_max
+                                                          : (int64_t)c->row_cap * c->attn_splits_max) *
                           c->hkv * kMaxGroup * (c->hd + 2));
   // per (row, vocabulary chunk) winners: kSampleChunks chunks (fp32 models),
   // one per 128-id block of the fused LM-head sampler (bf16 models)
@@ -446,6 +447,12 @@ extern "C" int sara_begin_step(sara_ctx* c, const int32_t* d_tokens, const int32
           "copy offsets");
   HIP_TRY(hipMemcpyAsync(c->pre, pre.data(), sizeof(int32_t) * (U + 1), hipMemcpyHostToDevice, st),
           "copy prefix");
+  if (c->md.dtype == SARA_BF16) {
+    build_prefill_tiles(c, pre.data());
+    if (!c->h_pf_tiles.empty())
+      HIP_TRY(hipMemcpyAsync(c->pf_tiles, c->h_pf_tiles.data(), sizeof(int4) * c->h_pf_tiles.size(),
+                             hipMemcpyHostToDevice, st), "copy prefill tiles");
+  }
   HIP_TRY(hipMemcpyAsync(c->p, d_p, sizeof(double) * U, hipMemcpyDeviceToDevice, st), "copy p");
   c->has_flen = d_forced_len ? 1 : 0;
   if (d_forced_len)

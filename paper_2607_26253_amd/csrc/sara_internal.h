@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <hip/hip_ext.h>
 #include <stdint.h>
 
 #include <string>
@@ -16,7 +17,6 @@ namespace sara {
 // ---------------------------------------------------------------------------
 constexpr int kBlockTok = 16;        // KV page size in tokens
 constexpr int kAttnSplit = 256;      // tokens per context split (fp32 VALU attention)
-constexpr int kAttnChunks = 16;      // KV pages per context split (bf16 MFMA prefill attention)
 constexpr int kDecPpw = 2;           // KV pages per wave in the decode attention
 constexpr int kDecPages = 4 * kDecPpw;  // KV pages per context split in the decode attention
 constexpr int kMaxSplitsDec = 12;    // split-K partials of a decode GEMM (summed in one batch; a multiple of 4)
@@ -130,6 +130,12 @@ struct sara_ctx {
   int has_flen = 0;
   int64_t tok_cap = 0;
   std::vector<int32_t> h_off;
+  // query tiles of the prefill attention (bf16 models): (first row in the
+  // chunk, tokens, first page, first position); chunk i owns
+  // [h_pf_tile_off[i], h_pf_tile_off[i + 1])
+  int4* pf_tiles = nullptr;
+  std::vector<int4> h_pf_tiles;
+  std::vector<int> h_pf_tile_off;
 
   // controller state
   sara::Ctl* ctl = nullptr;
@@ -217,6 +223,26 @@ int prof_collect(sara_ctx* c);
 void set_error(const std::string& msg);
 int hip_fail(hipError_t e, const char* what);
 
+// Kernel launch on a context's stream.  While a per-kernel profile record is
+// open (prof_begin), the launch goes through hipExtLaunchKernelGGL with the
+// record's event pair, so the dispatch itself stamps the kernel's start and
+// end: the elapsed time is the kernel's own duration, as in a kernel trace.
+template <typename F, typename... Args>
+static void launch_k(sara_ctx* c, hipStream_t st, F kernel, dim3 grid, dim3 block, uint32_t shm, Args... args) {
+  const int p = c->prof_pending;
+  if (p >= 0) {
+    c->prof_pending = -1;
+    c->prof_last = p;
+    hipExtLaunchKernelGGL(kernel, grid, block, shm, st, c->prof_events[p], c->prof_events[p + 1], 0u, args...);
+  } else {
+    hipLaunchKernelGGL(kernel, grid, block, shm, st, args...);
+  }
+}
+
+// launchers (prefill of bf16 models)
+void build_prefill_tiles(sara_ctx* c, const int32_t* pre);
+int64_t max_prefill_tiles(const sara_ctx* c);
+void launch_attn_prefill(sara_ctx* c, int chunk, int layer);
 // launchers (model)
 int launch_prefill(sara_ctx* c);
 int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_free);
@@ -247,6 +273,15 @@ int launch_tile_weights_pairs(sara_ctx* c, const void* src, void* dst, int n_row
 // ---------------------------------------------------------------------------
 // device helpers
 // ---------------------------------------------------------------------------
+typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// two fp32 values rounded (to nearest even) to a bf16 pair, a in the low half
+__device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
+  const bf16x2 v = {(__bf16)a, (__bf16)b};
+  return __builtin_bit_cast(uint32_t, v);
+}
 __device__ __forceinline__ float bf16_to_f32(uint16_t b) {
   return __uint_as_float(((uint32_t)b) << 16);
 }

@@ -1,0 +1,51 @@
+"""Prefill of bf16 models: every query-head group size and head width, prompt
+lengths at the edges of the attention's key blocks and query tiles."""
+import numpy as np
+import pytest
+
+import workloads as W
+from oracle import run as ORUN
+from tests.gpu_harness import compare_logs, device_setup, forced_table, run_gpu_step, slot_rows
+
+pytestmark = pytest.mark.gpu
+
+
+def generic_cfg(d, hq, hkv, hd, ffn, lengths, layers=2, vocab=512, **alloc):
+    """A small bf16 decoder and one probe for each prompt of the given lengths."""
+    cfg = W.get_config("qwen1p5b_shape")
+    cfg["model"].update(n_layers=layers, d_model=d, n_heads=hq, n_kv_heads=hkv, head_dim=hd, d_ffn=ffn, vocab=vocab,
+                        eos_id=vocab - 1)
+    U = len(lengths)
+    cfg["alloc"].update(B=U, k=2, n0=1, commit_min=2, budget_N=2 * U, pool_U=U, n_slots=U, max_prompt=max(lengths),
+                        max_new=2)
+    cfg["alloc"].update(alloc)
+    return cfg
+
+
+def check_against_oracle(cfg, lengths):
+    """One teacher-forced step: logs bit-exact, every row's logits within the
+    2-layer bound of the bf16 slices (3e-2 of the oracle row's rms)."""
+    w, pool, seed = W.make_weights(cfg), W.pool_with_lengths(cfg, lengths), W.sampling_seed(cfg)
+    ora = ORUN.run_step(cfg, w, pool, seed, keep_logits=lambda u, j, i: True)
+    ctx, _ = device_setup(cfg, w)
+    gpu = run_gpu_step(ctx, cfg, pool, forced=forced_table(cfg, ora["rollouts_detail"]), capture_logits=True)
+    ctx.close()
+    compare_logs(gpu["logs"], ora)
+    worst = {}
+    for (t, s), key in slot_rows(gpu).items():
+        o = ora["logits"][key].astype(np.float64)
+        rel = float(np.max(np.abs(gpu["logits"][t][s] - o)) / np.sqrt(np.mean(o * o)))
+        worst[key[0]] = max(rel, worst.get(key[0], 0.0))
+    assert set(worst) == set(range(len(lengths)))
+    bad = {lengths[u]: r for u, r in worst.items() if r > 3e-2}
+    assert not bad, bad
+    return max(worst.values())
+
+
+@pytest.mark.parametrize("hq,hkv,hd", [(2, 2, 64), (4, 2, 64), (6, 2, 64), (8, 2, 64), (8, 1, 64), (5, 1, 64), (7, 1, 128),
+                                       (6, 1, 128), (10, 2, 128), (4, 4, 128), (8, 1, 128)])
+def test_prefill_attention_group_sizes(hq, hkv, hd):
+    # P - 1 positions are prefilled: none, one, tile and key-block edges (16, 32, 64, 128, 256) and a few blocks
+    lengths = [1, 2, 16, 17, 18, 33, 34, 65, 66, 129, 130, 257, 258, 300]
+    cfg = generic_cfg(512, hq, hkv, hd, 512, lengths)
+    print(f"[prefill] {hq}/{hkv} x {hd}: max |dlogit| / rms {check_against_oracle(cfg, lengths):.4f}", flush=True)
