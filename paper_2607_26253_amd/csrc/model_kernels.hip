@@ -37,6 +37,13 @@ __device__ __forceinline__ float wave_max(float v) {
   for (int o = 32; o > 0; o >>= 1) v = fmaxf(v, __shfl_xor(v, o, 64));
   return v;
 }
+// place of feature k of row i in the GEMM inputs that both dtypes' kernels
+// write (prefill, and the q|k|v input of a decode step): fragment-major in bf16
+// models, row-major in fp32 ones
+template <typename T>
+__device__ __forceinline__ size_t x_index(int64_t i, int64_t k, int64_t K) {
+  return sizeof(T) == 2 ? (size_t)tiled_index(i, k, K) : (size_t)(i * K + k);
+}
 // sum over a 256-thread block; every thread gets the result
 __device__ float block_sum256(float v, float* red) {
   v = wave_sum(v);
@@ -46,29 +53,6 @@ __device__ float block_sum256(float v, float* red) {
   __syncthreads();
   float r = (red[0] + red[1]) + (red[2] + red[3]);
   return r;
-}
-
-// Fragment-major ("tiled") layout of a [rows][K] bf16 matrix: for each
-// 16-row tile and each 32-wide k step, the 64 lanes' 16-byte MFMA operand
-// fragments lie back to back (lane l holds row l % 16, k 8*(l/16)..+8), so
-// every fragment load of a wave is one contiguous, fully coalesced 1 KiB read
-// and a wave walks its 16 rows as one sequential stream.  The decode rows
-// feeding the q|k|v kernel are written this way.
-__device__ __forceinline__ int64_t tiled_index(int64_t row, int64_t k, int64_t K) {
-  const int64_t tile = row >> 4, ks = k >> 5, lane = (row & 15) + 16 * ((k >> 3) & 3);
-  return ((tile * (K >> 5) + ks) * 64 + lane) * 8 + (k & 7);
-}
-
-// Layout of the bf16 GEMM weights ([rows][K], K a multiple of 64): the same
-// 1 KiB fragments, ordered k-block-major.  K is cut into 64-wide blocks; in
-// block b the n_tiles 16-row tiles lie back to back, each as its two 32-wide
-// k steps.  The waves of a launch walk k at about the same pace, so at any
-// moment they read one contiguous stretch of the matrix (spread over every
-// HBM channel) instead of n_tiles streams a whole tile row apart, which
-// measured 3-18% faster on the decode weight shapes.
-__host__ __device__ __forceinline__ int64_t wtiled_index(int64_t row, int64_t k, int64_t n_tiles) {
-  const int64_t tile = row >> 4, kb = k >> 6, ks = (k >> 5) & 1, lane = (row & 15) + 16 * ((k >> 3) & 3);
-  return (((kb * n_tiles + tile) * 2 + ks) * 64 + lane) * 8 + (k & 7);
 }
 
 // ---------------------------------------------------------------------------
@@ -141,7 +125,7 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
     int32_t* __restrict__ rows_M, int do_embed, const T* __restrict__ embed,
     const float* __restrict__ w, int d, float eps, float* __restrict__ h, T* __restrict__ x,
     int U, int PB, int SB, const float2* __restrict__ rope, int half, float2* __restrict__ row_rope,
-    int x_tiled, AttnItem* __restrict__ items, int32_t* __restrict__ n_items, int spg) {
+    AttnItem* __restrict__ items, int32_t* __restrict__ n_items, int spg) {
   __shared__ float red[4];
   __shared__ int scan[256];
   const int M = ctl->done ? 0 : ctl->M;
@@ -220,7 +204,7 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
     float tot = block_sum256(ss, red);
     float inv = 1.0f / sqrtf(tot / (float)d + eps);
     for (int cc = threadIdx.x; cc < d; cc += 256)
-      st_f32(x, x_tiled ? (size_t)tiled_index(i, cc, d) : (size_t)i * d + cc, h[(size_t)i * d + cc] * inv * w[cc]);
+      st_f32(x, x_index<T>(i, cc, d), h[(size_t)i * d + cc] * inv * w[cc]);
     __syncthreads();   // red[] is reused by the next row
   }
 }
@@ -254,24 +238,23 @@ __global__ __launch_bounds__(256) void k_prefill_rows(const int32_t* __restrict_
   rows[i] = d;
 }
 
-template <typename T>
 __global__ __launch_bounds__(256) void k_embed_norm(const int32_t* __restrict__ M_ptr,
-    const RowDesc* __restrict__ rows, const T* __restrict__ embed, const float* __restrict__ w,
-    int d, float eps, float* __restrict__ h, T* __restrict__ x) {
+    const RowDesc* __restrict__ rows, const float* __restrict__ embed, const float* __restrict__ w,
+    int d, float eps, float* __restrict__ h, float* __restrict__ x) {
   __shared__ float red[4];
   int i = blockIdx.x;
   if (i >= *M_ptr) return;
   int t = rows[i].tok;
   float ss = 0.f;
   for (int c = threadIdx.x; c < d; c += 256) {
-    float v = ld_f32(embed, (size_t)t * d + c);
+    float v = embed[(size_t)t * d + c];
     h[(size_t)i * d + c] = v;
     ss += v * v;
   }
   float tot = block_sum256(ss, red);
   float inv = 1.0f / sqrtf(tot / (float)d + eps);
   for (int c = threadIdx.x; c < d; c += 256)
-    st_f32(x, (size_t)i * d + c, h[(size_t)i * d + c] * inv * w[c]);
+    x[(size_t)i * d + c] = h[(size_t)i * d + c] * inv * w[c];
 }
 
 // ---------------------------------------------------------------------------
@@ -425,9 +408,13 @@ __device__ __forceinline__ void sample_epilogue(const f32x4 (&acc)[NT][MT], int 
 // EPI = 1: SwiGLU epilogue (one split only): the weight rows are interleaved
 //          per 16-row tile as gate (even tiles) and up (odd tiles) of the same
 //          16 features; out receives bf16 silu(g) * u as [m][N/2].
+// XT: X (and the SwiGLU output) is fragment-major (tiled_index), as the
+// prefill writes it, else row-major.  A decode batch stays row-major: with few
+// live rows a fragment-major row is spread over 16 times as many cache lines
+// (gate|up 13.0 -> 13.5 us, LM head 95 -> 104 us at 32 rows).
 // EPI = 2: Gumbel-max sampling epilogue of the LM head (one split only), see
 //          sample_epilogue; out is unused.
-template <int NT, int MT, int KC, int EPI>
+template <int NT, int MT, int KC, int EPI, bool XT>
 __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     void* __restrict__ out, int M, int m_base, int N, int K, int kps, int64_t split_stride,
     uint16_t* __restrict__ xs, const SampleArgs& sa) {
@@ -458,7 +445,9 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
     // threads past the tile repeat its last element (same value, same place)
     int u = min((int)threadIdx.x + 256 * q, MR * C8 - 1);
     int rr = u / C8, c8 = u % C8;
-    xoff[q] = min(m_base + rr, M - 1) * K + 8 * c8 + k_begin;
+    // 8 consecutive k of a row are one 16-byte run in either layout
+    const int m = min(m_base + rr, M - 1);
+    xoff[q] = XT ? (int)tiled_index(m, k_begin + 8 * c8, K) : m * K + 8 * c8 + k_begin;
     xdst[q] = rr * PITCH + 8 * c8;
   }
   // the four pipeline slots are distinct variables (not an indexed array),
@@ -475,7 +464,7 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
   auto load = [&](Stage& st, int chunk) {
     const int ch = max(min(chunk, last), 0);
 #pragma unroll
-    for (int q = 0; q < XU; ++q) st.x[q] = *(const u32x4*)(X + xoff[q] + ch * KC);
+    for (int q = 0; q < XU; ++q) st.x[q] = *(const u32x4*)(X + xoff[q] + ch * (XT ? 1024 : KC));
 #pragma unroll
     for (int nt = 0; nt < NT; ++nt)
 #pragma unroll
@@ -546,7 +535,7 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
             float a1 = g1 / (1.0f + expf(-g1)) * u1;
             pk[q / 2] = (uint32_t)f32_to_bf16(a0) | ((uint32_t)f32_to_bf16(a1) << 16);
           }
-          *(uint2*)(o + (size_t)m * F + f0) = make_uint2(pk[0], pk[1]);
+          *(uint2*)(o + (XT ? (size_t)tiled_index(m, f0, F) : (size_t)m * F + f0)) = make_uint2(pk[0], pk[1]);
         }
       }
     }
@@ -570,7 +559,7 @@ __global__ __launch_bounds__(256, 2) void k_gemm_bf16_lds(const uint16_t* __rest
     const int mt = min(MTMAX, (M - m_base + 15) >> 4);
 #define SARA_MB(c) \
     if constexpr (MTMAX >= c) { \
-      if (mt == c) gemm_mblock<NT, c, KC, EPI>(X, W, out, M, m_base, N, K, kps, split_stride, xs, sa); \
+      if (mt == c) gemm_mblock<NT, c, KC, EPI, PF == 1>(X, W, out, M, m_base, N, K, kps, split_stride, xs, sa); \
     }
     SARA_MB(1) SARA_MB(2) SARA_MB(3) SARA_MB(4) SARA_MB(5) SARA_MB(6) SARA_MB(7) SARA_MB(8)
 #undef SARA_MB
@@ -744,7 +733,7 @@ __global__ __launch_bounds__(256) void k_qkv_epilogue(const int32_t* __restrict_
 template <typename T>
 __global__ __launch_bounds__(1024) void k_residual_norm(const int32_t* __restrict__ M_ptr,
     const float* __restrict__ ws, int splits, int64_t stride, int d, float* __restrict__ h,
-    const float* __restrict__ w, float eps, T* __restrict__ x, int x_tiled) {
+    const float* __restrict__ w, float eps, T* __restrict__ x) {
   __shared__ float red[16];
   const int M = *M_ptr;
   for (int i = blockIdx.x; i < M; i += gridDim.x) {
@@ -764,7 +753,7 @@ __global__ __launch_bounds__(1024) void k_residual_norm(const int32_t* __restric
   float inv = 1.0f / sqrtf(tot / (float)d + eps);
   for (int c = threadIdx.x; c < d; c += 1024) {
     size_t idx = (size_t)i * d + c;
-    st_f32(x, x_tiled ? (size_t)tiled_index(i, c, d) : idx, h[idx] * inv * w[c]);
+    st_f32(x, x_index<T>(i, c, d), h[idx] * inv * w[c]);
   }
   __syncthreads();   // red[] is reused by the next row
   }
@@ -778,7 +767,7 @@ __global__ __launch_bounds__(1024) void k_residual_norm(const int32_t* __restric
 template <typename T, int VPT>
 __global__ __launch_bounds__(256) void k_residual_norm_v(const int32_t* __restrict__ M_ptr,
     const float* __restrict__ ws, int splits, int64_t stride, int d, float* __restrict__ h,
-    const float* __restrict__ w, float eps, T* __restrict__ x, int x_tiled) {
+    const float* __restrict__ w, float eps, T* __restrict__ x) {
   __shared__ float red[4];
   const int M = *M_ptr;
   for (int i = blockIdx.x; i < M; i += gridDim.x) {
@@ -827,7 +816,7 @@ __global__ __launch_bounds__(256) void k_residual_norm_v(const int32_t* __restri
 #pragma unroll
     for (int v = 0; v < VPT; ++v) {
       const int c = threadIdx.x + 256 * v;
-      if (c < d) st_f32(x, x_tiled ? (size_t)tiled_index(i, c, d) : rb + c, hv[v] * inv * wv[v]);
+      if (c < d) st_f32(x, x_index<T>(i, c, d), hv[v] * inv * wv[v]);
     }
     __syncthreads();   // red[] is reused by the next row
   }
@@ -1845,80 +1834,79 @@ __global__ void k_copy_logits(const Ctl* __restrict__ ctl, const RowDesc* __rest
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-static int gemm(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap,
-                int N, int K, int& splits_out, int max_splits = 1 << 30, bool oproj = false) {
-  int64_t stride = (int64_t)M_cap * N;
-  if (c->md.dtype == SARA_BF16) {
-    // weight rows per block: 128 (two 16-row tiles per wave) for the LM head
-    // and long-K GEMMs, 64 otherwise; split K until the grid has about one
-    // block per CU (each split keeps >= 4 k chunks): wide GEMMs need no
-    // split, narrow ones trade fp32 partial traffic for occupancy
-    constexpr int MT = 8;
-    const bool wide = N >= 65536;
-    const bool two = wide || (K >= 4096 && c->in_prefill);
-    const int rows_per_block = two ? 128 : 64;
-    int tiles_n = (N + rows_per_block - 1) / rows_per_block;
-    // one z block per m-block of the capacity; in decode the live row count
-    // is read on the device, and z blocks past it exit at once (blocks are
-    // dispatched z-major, so the live m-blocks start first)
-    int zb = (M_cap + 16 * MT - 1) / (16 * MT);
-    // blocks without a split: weight tiles x m-blocks in prefill (the chunk's
-    // row count is known), weight tiles alone in decode (live rows are few
-    // and known only on the device)
-    const int64_t blocks = (int64_t)tiles_n * (c->in_prefill ? zb : 1);
-    int want = (blocks >= 256) ? 1 : (int)((256 + blocks - 1) / blocks);
-    // 64-wide k chunks: four pipeline slots of X + W fit in registers for NT <= 2
-    const int KC = 64;
-    int chunks = K / KC;
-    int splits = std::min(want, std::max(1, chunks / 4));
-    if (!c->in_prefill) {
-      // decode: an even division of the k chunks keeps the splits balanced
-      // (the last split of an uneven one runs alone); take the largest even
-      // count in [6, kMaxSplitsDec] with >= 4 chunks per split, else the
-      // occupancy target.  Consumers sum at most kMaxSplitsDec partials in
-      // one batch of loads.
-      for (int s = kMaxSplitsDec; s >= 6; --s)
-        if (s <= want && chunks % s == 0 && chunks / s >= 4) { splits = s; break; }
-      splits = std::min(splits, kMaxSplitsDec);
-    }
-    if (splits > max_splits) splits = max_splits;
-    if (splits < 1) splits = 1;
-    int kps = ((chunks + splits - 1) / splits) * KC;
-    splits = (K + kps - 1) / kps;
-    if ((int64_t)splits * stride > c->ws_floats) { splits = 1; kps = K; }
-    dim3 grid(tiles_n, splits, zb);
-    const uint16_t* Xh = (const uint16_t*)X;
-    const uint16_t* Wh = (const uint16_t*)W;
-#define SARA_GEMM(NT_, KC_, PF_) \
-    launch_k(c, c->stream, (k_gemm_bf16_lds<NT_, MT, KC_, 0, PF_>), grid, dim3(256), 0, Xh, Wh, \
-                       (void*)c->ws, M_ptr, N, K, kps, stride, SampleArgs{})
-    if (c->in_prefill) {
-      if (two) SARA_GEMM(2, 64, 1);
-      else SARA_GEMM(1, 64, 1);
-    } else if (two) {
-      SARA_GEMM(2, 64, 0);
-    } else if (oproj) {
-      SARA_GEMM(1, 64, 2);
-    } else {
-      SARA_GEMM(1, 64, 0);
-    }
-#undef SARA_GEMM
-    splits_out = splits;
-  } else {
-    int tiles_n = (N + 15) / 16, zb = (M_cap + 15) / 16;
-    int want = (tiles_n * zb >= 256) ? 1 : (256 + tiles_n * zb - 1) / (tiles_n * zb);
-    int chunks = K / 32;
-    int splits = want < chunks ? want : chunks;
-    if (splits > max_splits) splits = max_splits;
-    if (splits < 1) splits = 1;
-    int kps = ((chunks + splits - 1) / splits) * 32;
-    splits = (K + kps - 1) / kps;
-    if ((int64_t)splits * stride > c->ws_floats) { splits = 1; kps = K; }
-    dim3 grid(tiles_n, splits, zb);
-    launch_k(c, c->stream, k_gemm_f32, grid, dim3(256), 0, (const float*)X, (const float*)W,
-                       c->ws, M_ptr, N, K, kps, stride);
-    splits_out = splits;
+// bf16 GEMM into fp32 partials ws[split][M_cap][N]
+int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
+              int& splits_out, bool oproj) {
+  const int64_t stride = (int64_t)M_cap * N;
+  // weight rows per block: 128 (two 16-row tiles per wave) for long-K GEMMs of
+  // a prefill, 64 otherwise; split K until the grid has about one block per CU
+  // (each split keeps >= 4 k chunks): wide GEMMs need no split, narrow ones
+  // trade fp32 partial traffic for occupancy
+  constexpr int MT = 8;
+  const bool two = K >= 4096 && c->in_prefill;
+  const int rows_per_block = two ? 128 : 64;
+  int tiles_n = (N + rows_per_block - 1) / rows_per_block;
+  // one z block per m-block of the capacity; in decode the live row count
+  // is read on the device, and z blocks past it exit at once (blocks are
+  // dispatched z-major, so the live m-blocks start first)
+  int zb = (M_cap + 16 * MT - 1) / (16 * MT);
+  // blocks without a split: weight tiles x m-blocks in prefill (the chunk's
+  // row count is known), weight tiles alone in decode (live rows are few
+  // and known only on the device)
+  const int64_t blocks = (int64_t)tiles_n * (c->in_prefill ? zb : 1);
+  int want = (blocks >= 256) ? 1 : (int)((256 + blocks - 1) / blocks);
+  // 64-wide k chunks: four pipeline slots of X + W fit in registers for NT <= 2
+  const int KC = 64;
+  int chunks = K / KC;
+  int splits = std::min(want, std::max(1, chunks / 4));
+  if (!c->in_prefill) {
+    // decode: an even division of the k chunks keeps the splits balanced
+    // (the last split of an uneven one runs alone); take the largest even
+    // count in [6, kMaxSplitsDec] with >= 4 chunks per split, else the
+    // occupancy target.  Consumers sum at most kMaxSplitsDec partials in
+    // one batch of loads.
+    for (int s = kMaxSplitsDec; s >= 6; --s)
+      if (s <= want && chunks % s == 0 && chunks / s >= 4) { splits = s; break; }
+    splits = std::min(splits, kMaxSplitsDec);
   }
+  if (splits < 1) splits = 1;
+  int kps = ((chunks + splits - 1) / splits) * KC;
+  splits = (K + kps - 1) / kps;
+  if ((int64_t)splits * stride > c->ws_floats) { splits = 1; kps = K; }
+  dim3 grid(tiles_n, splits, zb);
+#define SARA_GEMM(NT_, PF_)                                                                                       \
+  launch_k(c, c->stream, (k_gemm_bf16_lds<NT_, MT, 64, 0, PF_>), grid, dim3(256), 0, (const uint16_t*)X,          \
+           (const uint16_t*)W, (void*)c->ws, M_ptr, N, K, kps, stride, SampleArgs{})
+  if (c->in_prefill) {
+    if (two) SARA_GEMM(2, 1);
+    else SARA_GEMM(1, 1);
+  } else if (oproj) {
+    SARA_GEMM(1, 2);
+  } else {
+    SARA_GEMM(1, 0);
+  }
+#undef SARA_GEMM
+  splits_out = splits;
+  return SARA_OK;
+}
+
+// fp32 GEMM into partials ws[split][M_cap][N]
+static int gemm_f32(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
+                    int& splits_out, int max_splits = 1 << 30) {
+  const int64_t stride = (int64_t)M_cap * N;
+  int tiles_n = (N + 15) / 16, zb = (M_cap + 15) / 16;
+  int want = (tiles_n * zb >= 256) ? 1 : (256 + tiles_n * zb - 1) / (tiles_n * zb);
+  int chunks = K / 32;
+  int splits = want < chunks ? want : chunks;
+  if (splits > max_splits) splits = max_splits;
+  if (splits < 1) splits = 1;
+  int kps = ((chunks + splits - 1) / splits) * 32;
+  splits = (K + kps - 1) / kps;
+  if ((int64_t)splits * stride > c->ws_floats) { splits = 1; kps = K; }
+  dim3 grid(tiles_n, splits, zb);
+  launch_k(c, c->stream, k_gemm_f32, grid, dim3(256), 0, (const float*)X, (const float*)W,
+                     c->ws, M_ptr, N, K, kps, stride);
+  splits_out = splits;
   return SARA_OK;
 }
 
@@ -1926,8 +1914,9 @@ static int gemm(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr,
 #define PROF_E(c, cls, N, K) do { if ((c)->prof_active) prof_end((c), (cls), (N), (K)); } while (0)
 
 // gate|up GEMM with the SwiGLU epilogue (bf16 models; W_gu rows interleaved
-// per 16-row tile at init), writing a = silu(g) * u to c->xa as [m][ffn]
-static void gemm_swiglu(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap) {
+// per 16-row tile at init), writing a = silu(g) * u to c->xa, fragment-major [m][ffn]
+// (prefill; row-major in decode)
+void gemm_swiglu(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap) {
   constexpr int MT = 8;
   const int N = 2 * c->ffn, K = c->d;
   dim3 grid((N + 127) / 128, 1, (M_cap + 16 * MT - 1) / (16 * MT));
@@ -1955,20 +1944,15 @@ static int qkv_spread(sara_ctx* c, F kernel) {
   return c->qkv_spread;
 }
 
-// h += split-K sum of ws; x = RMSNorm(h) * w
+// h += split-K sum of ws; x = RMSNorm(h) * w (fp32 models, bf16 prefill)
 template <typename T>
-static void residual_norm(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w, int x_tiled = 0) {
+static void residual_norm(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w) {
   const int d = c->d, vpt = (d + 255) / 256;
   const dim3 grid(std::min(M_cap, 1024));
   const int64_t stride = (int64_t)M_cap * d;
   T* x = (T*)c->x;
-  if (sizeof(T) == 2 && !c->in_prefill && sp <= kMaxSplitsDec && d % 4 == 0 && d / 4 <= 1024) {
-    launch_k(c, c->stream, k_residual_norm_f4, grid, dim3((d / 4 + 63) / 64 * 64), 0, M_ptr, c->ws, sp, stride,
-             d, c->h, w, c->md.rms_eps, (uint16_t*)c->x, x_tiled);
-    return;
-  }
 #define SARA_RN(V) launch_k(c, c->stream, (k_residual_norm_v<T, V>), grid, dim3(256), 0, M_ptr, c->ws, \
-                                      sp, stride, d, c->h, w, c->md.rms_eps, x, x_tiled)
+                                      sp, stride, d, c->h, w, c->md.rms_eps, x)
   switch (sp <= kMaxSplitsDec ? vpt : 0) {
     case 1: SARA_RN(1); break;
     case 2: SARA_RN(2); break;
@@ -1978,129 +1962,149 @@ static void residual_norm(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, 
     case 7: case 8: SARA_RN(8); break;
     default:
       launch_k(c, c->stream, k_residual_norm<T>, dim3(std::min(M_cap, 256)), dim3(1024), 0, M_ptr,
-                         c->ws, sp, stride, d, c->h, w, c->md.rms_eps, x, x_tiled);
+                         c->ws, sp, stride, d, c->h, w, c->md.rms_eps, x);
   }
 #undef SARA_RN
 }
-
-template <typename T, int HD>
-static void layers_T(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_norm_out, int chunk) {
-  hipStream_t st = c->stream;
-  const int d = c->d;
-  const int64_t stride_qkv = (int64_t)M_cap * c->nqkv;
-  T* x = (T*)c->x;
-  for (int l = 0; l < c->L; ++l) {
-    int sp = 1;
-    const bool mfma_attn = (c->md.dtype == SARA_BF16);
-    if (mfma_attn && !c->in_prefill) {
-      // decode: q|k|v projection with the RoPE / KV-append epilogue, the
-      // paged attention, then the merge of rows with several context splits
-      PROF_B(c);
-#define SARA_QKV(KS_) \
-      launch_k(c, st, (k_qkv_rope<HD, KS_>), dim3(c->nqkv / 16, 1, (M_cap + 127) / 128), dim3(256), 0, \
-               (const uint16_t*)x, \
-                         (const uint16_t*)c->w_qkv[l], M_ptr, d, c->rows, c->row_rope, c->hq, c->hkv, l, \
-                         c->n_blocks, (uint16_t*)c->qbuf, (uint16_t*)c->kc, (uint16_t*)c->vc, \
-                         qkv_spread(c, k_qkv_rope<HD, KS_>))
-      switch (d / 128) {
-        case 4: SARA_QKV(4); break;
-        case 8: SARA_QKV(8); break;
-        case 12: SARA_QKV(12); break;
-        case 16: SARA_QKV(16); break;
-        case 24: SARA_QKV(24); break;
-        default: SARA_QKV(32); break;
-      }
-#undef SARA_QKV
-      PROF_E(c, kPQkvRope, c->nqkv, d);
-      PROF_B(c);
-      if (c->attn_dec_grid == 0) {
-        // blocks resident at once: every item of a list that short runs in one round
-        int per_cu = 0, dev = 0, n_cu = 0;
-        if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_attn_dec<HD>, 256, 0) != hipSuccess ||
-            hipGetDevice(&dev) != hipSuccess ||
-            hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-          per_cu = 2, n_cu = 256;
-        c->attn_dec_grid = std::max(1, per_cu) * std::max(1, n_cu);
-      }
-      const int cap = M_cap * c->dec_splits_max;
-      const int dg = (int)std::min<int64_t>((int64_t)cap * c->hkv, c->attn_dec_grid);
-      launch_k(c, st, (k_attn_dec<HD>), dim3(dg), dim3(256), 0, (const AttnItem*)c->attn_items,
-                         (const int32_t*)c->attn_nitems, cap, (const uint16_t*)c->kc,
-                         (const uint16_t*)c->vc, l, c->n_blocks, c->hq, c->hkv, c->dec_splits_max,
-                         1.0f / sqrtf((float)HD), (const uint16_t*)c->qbuf, c->attn_part, (uint16_t*)x);
-      PROF_E(c, kPAttn, 0, 0);
-      PROF_B(c);
-      launch_k(c, st, (k_attn_combine<T, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows,
-                         c->attn_part, c->hq, c->hkv, c->dec_splits_max, kDecPages, 1, x);
-      PROF_E(c, kPCombine, 0, 0);
-    } else {
-    PROF_B(c);
-    gemm(c, x, c->w_qkv[l], M_ptr, M_cap, c->nqkv, d, sp);
-    PROF_E(c, kPGemmN1, c->nqkv, d);
-    PROF_B(c);
-    launch_k(c, st, k_qkv_epilogue<T>, dim3(2048), dim3(c->hd / 2), 0, M_ptr,
-                       c->rows, c->ws, sp,
-                       stride_qkv, c->rope, c->hq, c->hkv, c->hd, l, c->n_blocks, c->btab, c->MAXB,
-                       c->PB, (T*)c->qbuf, (T*)c->kc, (T*)c->vc, mfma_attn ? 1 : 0);
-    PROF_E(c, kPQkv, c->nqkv, 0);
-    PROF_B(c);
-    if (mfma_attn) {
-      launch_attn_prefill(c, chunk, l);
-      PROF_E(c, kPAttn, 0, 0);
-    } else {
-      launch_k(c, st, (k_attention<T, HD>), dim3(M_cap, c->hkv, c->attn_splits_max), dim3(256), 0,
-                         M_ptr, c->rows, (const T*)c->qbuf, (const T*)c->kc, (const T*)c->vc, c->btab,
-                         c->MAXB, c->PB, l, c->n_blocks, c->hq, c->hkv, c->attn_splits_max,
-                         1.0f / sqrtf((float)HD), c->attn_part);
-      PROF_E(c, kPAttn, 0, 0);
-      PROF_B(c);
-      launch_k(c, st, (k_attn_combine<T, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows,
-                         c->attn_part, c->hq, c->hkv, c->attn_splits_max, 0, 0, x);
-      PROF_E(c, kPCombine, 0, 0);
-    }
-    }
-    PROF_B(c);
-    gemm(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, sp, 1 << 30, true);
-    PROF_E(c, (c->md.dtype == SARA_BF16 && !c->in_prefill) ? kPGemmO1 : kPGemmN1, d, c->qdim);
-    PROF_B(c);
-    residual_norm<T>(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 1) * d);
-    PROF_E(c, kPResNorm, d, 0);
-    if (c->md.dtype == SARA_BF16) {
-      PROF_B(c);
-      gemm_swiglu(c, x, c->w_gu[l], M_ptr, M_cap);
-      PROF_E(c, kPGemmGU, 2 * c->ffn, d);
-      PROF_B(c);
-      gemm(c, c->xa, c->w_d[l], M_ptr, M_cap, d, c->ffn, sp);
-      PROF_E(c, kPGemmN1, d, c->ffn);
-    } else {
-      PROF_B(c);
-      gemm(c, x, c->w_gu[l], M_ptr, M_cap, 2 * c->ffn, d, sp);
-      PROF_E(c, kPGemmN1, 2 * c->ffn, d);
-      PROF_B(c);
-      launch_k(c, st, k_swiglu<T>, dim3(1024), dim3(256), 0, M_ptr, c->ws,
-                         sp, (int64_t)M_cap * 2 * c->ffn, c->ffn, x);
-      PROF_E(c, kPSwiglu, c->ffn, 0);
-      PROF_B(c);
-      gemm(c, x, c->w_d[l], M_ptr, M_cap, d, c->ffn, sp);
-      PROF_E(c, kPGemmN1, d, c->ffn);
-    }
-    const float* nw = (l + 1 < c->L) ? c->norms + (size_t)(2 * (l + 1)) * d
-                                     : c->norms + (size_t)(2 * c->L) * d;
-    // the last layer's norm output is only needed when logits follow
-    if (l + 1 < c->L || final_norm_out) {
-      PROF_B(c);
-      // in bf16 decode the next layer's q|k|v kernel reads fragment-major rows
-      residual_norm<T>(c, M_ptr, M_cap, sp, nw,
-                       (c->md.dtype == SARA_BF16 && !c->in_prefill && l + 1 < c->L) ? 1 : 0);
-      PROF_E(c, kPResNorm, d, 0);
-    }
-  }
+void residual_norm_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w) {
+  residual_norm<uint16_t>(c, M_ptr, M_cap, sp, w);
+}
+// the same for the rows of a bf16 decode step (d <= 4096, at most
+// kMaxSplitsDec splits)
+static void residual_norm_decode(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w, int x_tiled) {
+  launch_k(c, c->stream, k_residual_norm_f4, dim3(std::min(M_cap, 1024)), dim3((c->d / 4 + 63) / 64 * 64), 0, M_ptr,
+           c->ws, sp, (int64_t)M_cap * c->d, c->d, c->h, w, c->md.rms_eps, (uint16_t*)c->x, x_tiled);
 }
 
 template <typename T>
-static void layers(sara_ctx* c, const int32_t* M_ptr, int M_cap, bool final_norm_out, int chunk = 0) {
-  if (c->hd == 128) layers_T<T, 128>(c, M_ptr, M_cap, final_norm_out, chunk);
-  else layers_T<T, 64>(c, M_ptr, M_cap, final_norm_out, chunk);
+static void qkv_epilogue(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, int l) {
+  launch_k(c, c->stream, k_qkv_epilogue<T>, dim3(2048), dim3(c->hd / 2), 0, M_ptr, c->rows, c->ws, sp,
+           (int64_t)M_cap * c->nqkv, c->rope, c->hq, c->hkv, c->hd, l, c->n_blocks, c->btab, c->MAXB, c->PB,
+           (T*)c->qbuf, (T*)c->kc, (T*)c->vc, sizeof(T) == 2 ? 1 : 0);
+}
+void launch_qkv_epilogue_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int sp, int layer) {
+  qkv_epilogue<uint16_t>(c, M_ptr, M, sp, layer);
+}
+
+// bf16 decode: the live rows of a step through every layer
+template <int HD>
+static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
+  hipStream_t st = c->stream;
+  const int d = c->d;
+  uint16_t* x = (uint16_t*)c->x;
+  for (int l = 0; l < c->L; ++l) {
+    int sp = 1;
+    // q|k|v projection with the RoPE / KV-append epilogue, the paged
+    // attention, then the merge of rows with several context splits
+    PROF_B(c);
+#define SARA_QKV(KS_) \
+    launch_k(c, st, (k_qkv_rope<HD, KS_>), dim3(c->nqkv / 16, 1, (M_cap + 127) / 128), dim3(256), 0, \
+             (const uint16_t*)x, (const uint16_t*)c->w_qkv[l], M_ptr, d, c->rows, c->row_rope, c->hq, c->hkv, l, \
+             c->n_blocks, (uint16_t*)c->qbuf, (uint16_t*)c->kc, (uint16_t*)c->vc, qkv_spread(c, k_qkv_rope<HD, KS_>))
+    switch (d / 128) {
+      case 4: SARA_QKV(4); break;
+      case 8: SARA_QKV(8); break;
+      case 12: SARA_QKV(12); break;
+      case 16: SARA_QKV(16); break;
+      case 24: SARA_QKV(24); break;
+      default: SARA_QKV(32); break;
+    }
+#undef SARA_QKV
+    PROF_E(c, kPQkvRope, c->nqkv, d);
+    PROF_B(c);
+    if (c->attn_dec_grid == 0) {
+      // blocks resident at once: every item of a list that short runs in one round
+      int per_cu = 0, dev = 0, n_cu = 0;
+      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_attn_dec<HD>, 256, 0) != hipSuccess ||
+          hipGetDevice(&dev) != hipSuccess ||
+          hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+        per_cu = 2, n_cu = 256;
+      c->attn_dec_grid = std::max(1, per_cu) * std::max(1, n_cu);
+    }
+    const int cap = M_cap * c->dec_splits_max;
+    const int dg = (int)std::min<int64_t>((int64_t)cap * c->hkv, c->attn_dec_grid);
+    launch_k(c, st, (k_attn_dec<HD>), dim3(dg), dim3(256), 0, (const AttnItem*)c->attn_items,
+             (const int32_t*)c->attn_nitems, cap, (const uint16_t*)c->kc, (const uint16_t*)c->vc, l, c->n_blocks,
+             c->hq, c->hkv, c->dec_splits_max, 1.0f / sqrtf((float)HD), (const uint16_t*)c->qbuf, c->attn_part, x);
+    PROF_E(c, kPAttn, 0, 0);
+    PROF_B(c);
+    launch_k(c, st, (k_attn_combine<uint16_t, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq,
+             c->hkv, c->dec_splits_max, kDecPages, 1, x);
+    PROF_E(c, kPCombine, 0, 0);
+    PROF_B(c);
+    gemm_bf16(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, sp, true);
+    PROF_E(c, kPGemmO1, d, c->qdim);
+    PROF_B(c);
+    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 1) * d, 0);
+    PROF_E(c, kPResNorm, d, 0);
+    PROF_B(c);
+    gemm_swiglu(c, x, c->w_gu[l], M_ptr, M_cap);
+    PROF_E(c, kPGemmGU, 2 * c->ffn, d);
+    PROF_B(c);
+    gemm_bf16(c, c->xa, c->w_d[l], M_ptr, M_cap, d, c->ffn, sp);
+    PROF_E(c, kPGemmN1, d, c->ffn);
+    PROF_B(c);
+    // the next layer's norm (its q|k|v kernel reads fragment-major rows) or the final one
+    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d, l + 1 < c->L ? 1 : 0);
+    PROF_E(c, kPResNorm, d, 0);
+  }
+}
+
+// fp32 models: the rows of a decode step or a prefill chunk through every
+// layer.  A prefill ends with the K and V of the last layer: nothing reads
+// what follows.
+template <int HD>
+static void layers_f32(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
+  hipStream_t st = c->stream;
+  const int d = c->d;
+  float* x = (float*)c->x;
+  for (int l = 0; l < c->L; ++l) {
+    int sp = 1;
+    PROF_B(c);
+    gemm_f32(c, x, c->w_qkv[l], M_ptr, M_cap, c->nqkv, d, sp);
+    PROF_E(c, kPGemmN1, c->nqkv, d);
+    PROF_B(c);
+    qkv_epilogue<float>(c, M_ptr, M_cap, sp, l);
+    PROF_E(c, kPQkv, c->nqkv, 0);
+    if (c->in_prefill && l + 1 == c->L) break;
+    PROF_B(c);
+    launch_k(c, st, (k_attention<float, HD>), dim3(M_cap, c->hkv, c->attn_splits_max), dim3(256), 0, M_ptr, c->rows,
+             (const float*)c->qbuf, (const float*)c->kc, (const float*)c->vc, c->btab, c->MAXB, c->PB, l, c->n_blocks,
+             c->hq, c->hkv, c->attn_splits_max, 1.0f / sqrtf((float)HD), c->attn_part);
+    PROF_E(c, kPAttn, 0, 0);
+    PROF_B(c);
+    launch_k(c, st, (k_attn_combine<float, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq, c->hkv,
+             c->attn_splits_max, 0, 0, x);
+    PROF_E(c, kPCombine, 0, 0);
+    PROF_B(c);
+    gemm_f32(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, sp);
+    PROF_E(c, kPGemmN1, d, c->qdim);
+    PROF_B(c);
+    residual_norm<float>(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 1) * d);
+    PROF_E(c, kPResNorm, d, 0);
+    PROF_B(c);
+    gemm_f32(c, x, c->w_gu[l], M_ptr, M_cap, 2 * c->ffn, d, sp);
+    PROF_E(c, kPGemmN1, 2 * c->ffn, d);
+    PROF_B(c);
+    launch_k(c, st, k_swiglu<float>, dim3(1024), dim3(256), 0, M_ptr, c->ws, sp, (int64_t)M_cap * 2 * c->ffn, c->ffn, x);
+    PROF_E(c, kPSwiglu, c->ffn, 0);
+    PROF_B(c);
+    gemm_f32(c, x, c->w_d[l], M_ptr, M_cap, d, c->ffn, sp);
+    PROF_E(c, kPGemmN1, d, c->ffn);
+    PROF_B(c);
+    residual_norm<float>(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d);   // the next layer's, or the final one
+    PROF_E(c, kPResNorm, d, 0);
+  }
+}
+
+static void run_layers(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
+  if (c->md.dtype == SARA_BF16) {
+    if (c->hd == 128) decode_layers_bf16<128>(c, M_ptr, M_cap);
+    else decode_layers_bf16<64>(c, M_ptr, M_cap);
+  } else {
+    if (c->hd == 128) layers_f32<128>(c, M_ptr, M_cap);
+    else layers_f32<64>(c, M_ptr, M_cap);
+  }
 }
 
 int launch_prefill(sara_ctx* c) {
@@ -2116,14 +2120,11 @@ int launch_prefill(sara_ctx* c) {
     launch_k(c, st, k_prefill_rows, dim3((n + 255) / 256), dim3(256), 0, c->pre, c->U, (int)r0,
                        n, c->tok, c->off, c->S, c->rows, c->rows_M, c->PB);
     if (c->md.dtype == SARA_BF16) {
-      launch_k(c, st, k_embed_norm<uint16_t>, dim3(n), dim3(256), 0, c->rows_M, c->rows,
-                         (const uint16_t*)c->embed, c->norms, c->d, c->md.rms_eps, c->h,
-                         (uint16_t*)c->x);
-      layers<uint16_t>(c, c->rows_M, n, false, chunk);
+      prefill_layers_bf16(c, c->rows_M, n, chunk);
     } else {
-      launch_k(c, st, k_embed_norm<float>, dim3(n), dim3(256), 0, c->rows_M, c->rows,
+      launch_k(c, st, k_embed_norm, dim3(n), dim3(256), 0, c->rows_M, c->rows,
                          (const float*)c->embed, c->norms, c->d, c->md.rms_eps, c->h, (float*)c->x);
-      layers<float>(c, c->rows_M, n, false);
+      run_layers(c, c->rows_M, n);
     }
   }
   c->in_prefill = false;
@@ -2169,19 +2170,19 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
                        c->slot_j, c->slot_gen, c->tok, c->off, c->out_tok, c->k, c->ad.max_new, c->rows,
                        c->rows_M, model_free ? 0 : 1, (const uint16_t*)c->embed, c->norms, c->d,
                        c->md.rms_eps, c->h, (uint16_t*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2,
-                       c->row_rope, 1, model_free ? (AttnItem*)nullptr : c->attn_items, c->attn_nitems,
+                       c->row_rope, model_free ? (AttnItem*)nullptr : c->attn_items, c->attn_nitems,
                        kDecPages);
   else
     launch_k(c, st, k_decode_embed<float>, dim3(eg), dim3(256), 0, c->ctl, c->active, c->slot_uid,
                        c->slot_j, c->slot_gen, c->tok, c->off, c->out_tok, c->k, c->ad.max_new, c->rows,
                        c->rows_M, model_free ? 0 : 1, (const float*)c->embed, c->norms, c->d,
                        c->md.rms_eps, c->h, (float*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2,
-                       c->row_rope, 0, (AttnItem*)nullptr, c->attn_nitems, kDecPages);
+                       c->row_rope, (AttnItem*)nullptr, c->attn_nitems, kDecPages);
   PROF_E(c, kPEmbed, c->d, 0);
   int nchunks = kSampleChunks;
   if (!model_free) {
     if (c->md.dtype == SARA_BF16) {
-      layers<uint16_t>(c, c->rows_M, S, true);
+      run_layers(c, c->rows_M, S);
       // LM head with the Gumbel-max sampling epilogue: per (row, 128-id block)
       // exact winners, reduced by k_sample_final
       const int nb = (c->V + 127) / 128;
@@ -2200,11 +2201,11 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
         nchunks = kSampleChunks;
       }
     } else {
-      layers<float>(c, c->rows_M, S, true);
+      run_layers(c, c->rows_M, S);
       int sp;
       // one K split: ws then holds the logits [M][V] directly
       PROF_B(c);
-      gemm(c, c->x, c->lm_head, c->rows_M, S, c->V, c->d, sp, 1);
+      gemm_f32(c, c->x, c->lm_head, c->rows_M, S, c->V, c->d, sp, 1);
       PROF_E(c, kPGemmLM, c->V, c->d);
       if (c->topp) {
         launch_topp_decode(c, st, c->ws, 0);

@@ -223,8 +223,14 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   c->max_pos = ad->max_prompt + ad->max_new;
   c->Qcap = (int)std::min<int64_t>(ad->budget_N, (int64_t)c->U * c->k);
   c->elt = (md->dtype == SARA_BF16) ? 2 : 4;
+  // rows of a prefill chunk: a pool of up to kPrefillRowsBf16 prompt tokens
+  // runs as one chunk (long chunks fill the 256 x 256 tiles' grids)
   c->prefill_rows = 4096;
-  c->row_cap = std::max(c->S, c->prefill_rows);
+  if (md->dtype == SARA_BF16) {
+    const int64_t pool_rows = (int64_t)c->U * (ad->max_prompt - 1);
+    c->prefill_rows = (int)std::min<int64_t>(kPrefillRowsBf16, std::max<int64_t>(4096, (pool_rows + 255) / 256 * 256));
+  }
+  c->row_cap = (std::max(c->S, c->prefill_rows) + 15) / 16 * 16;   // whole 16-row fragments
   c->attn_splits_max = (c->max_pos + kAttnSplit - 1) / kAttnSplit;
   c->dec_splits_max = (c->MAXB + kDecPages - 1) / kDecPages;
   {
@@ -232,12 +238,11 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
     // falls back to one split when its partials would not fit)
     if (md->dtype == SARA_BF16) {
       // decode: the o and down projections (<= kMaxSplitsDec splits of
-      // [S][d]); prefill: q|k|v, o and down over a chunk, whose weight tiles
-      // and m-blocks fill the GPU without splits except in a short last
-      // chunk (<= 256 blocks' worth of partials).  The LM head, the gate|up
-      // projection and the q|k|v projection of decode write no partials.
+      // [S][d]); prefill: q|k|v, o and down over a short chunk (a long one
+      // writes no partials).  The LM head, the gate|up projection and the
+      // q|k|v projection of decode write no partials.
       const int64_t npf = std::max<int64_t>(c->nqkv, c->d);
-      c->ws_floats = std::max<int64_t>((int64_t)kMaxSplitsDec * c->S * c->d, 2 * (int64_t)c->prefill_rows * npf);
+      c->ws_floats = std::max<int64_t>((int64_t)kMaxSplitsDec * c->S * c->d, 2 * (int64_t)4096 * npf);
     } else {
       // fp32: also the logits [S][V] and the gate|up output [rows][2 ffn]
       int64_t nd = std::max<int64_t>({c->V, c->nqkv, 2 * (int64_t)c->ffn, c->d});
@@ -313,9 +318,10 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->rows, sizeof(RowDesc) * c->row_cap);
   ALLOC(c->rows_M, sizeof(int32_t));
   ALLOC(c->h, sizeof(float) * (size_t)c->row_cap * d);
-  ALLOC(c->x, (size_t)c->row_cap * std::max({c->d, c->ffn, c->qdim}) * E);
+  const bool bf16 = md->dtype == SARA_BF16;   // bf16 models keep the SwiGLU output in xa, fp32 ones in x
+  ALLOC(c->x, (size_t)c->row_cap * std::max({c->d, bf16 ? 0 : c->ffn, c->qdim}) * E);
   ALLOC(c->qbuf, (size_t)c->row_cap * c->qdim * E);
-  ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
+  if (bf16) ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
   ALLOC(c->ws, sizeof(float) * (size_t)c->ws_floats);
   // context-split partials: fp32 attention (every row), bf16 decode rows
   ALLOC(c->attn_part, sizeof(float) *

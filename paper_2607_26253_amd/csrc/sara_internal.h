@@ -20,6 +20,7 @@ constexpr int kAttnSplit = 256;      // tokens per context split (fp32 VALU atte
 constexpr int kDecPpw = 2;           // KV pages per wave in the decode attention
 constexpr int kDecPages = 4 * kDecPpw;  // KV pages per context split in the decode attention
 constexpr int kMaxSplitsDec = 12;    // split-K partials of a decode GEMM (summed in one batch; a multiple of 4)
+constexpr int kPrefillRowsBf16 = 32768;  // most rows of a prefill chunk of a bf16 model
 constexpr int kAttnTile = 64;        // tokens per LDS tile inside a split
 constexpr int kSampleChunks = 16;    // vocabulary chunks per sampled row
 constexpr int kTopPChunks = 16;      // vocabulary chunks per row in the top-p passes
@@ -242,7 +243,13 @@ static void launch_k(sara_ctx* c, hipStream_t st, F kernel, dim3 grid, dim3 bloc
 // launchers (prefill of bf16 models)
 void build_prefill_tiles(sara_ctx* c, const int32_t* pre);
 int64_t max_prefill_tiles(const sara_ctx* c);
-void launch_attn_prefill(sara_ctx* c, int chunk, int layer);
+void prefill_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int chunk);
+// model launchers that the prefill shares
+int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
+              int& splits_out, bool oproj = false);
+void gemm_swiglu(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap);
+void residual_norm_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w);
+void launch_qkv_epilogue_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int sp, int layer);
 // launchers (model)
 int launch_prefill(sara_ctx* c);
 int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_free);
@@ -277,6 +284,30 @@ typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+// Fragment-major ("tiled") layout of a [rows][K] bf16 matrix: for each
+// 16-row tile and each 32-wide k step, the 64 lanes' 16-byte MFMA operand
+// fragments lie back to back (lane l holds row l % 16, k 8*(l/16)..+8), so
+// every fragment load of a wave is one contiguous, fully coalesced 1 KiB read
+// and a wave walks its 16 rows as one sequential stream.  The GEMM inputs of
+// the bf16 prefill and the decode rows feeding the q|k|v kernel are written
+// this way.
+__device__ __forceinline__ int64_t tiled_index(int64_t row, int64_t k, int64_t K) {
+  const int64_t tile = row >> 4, ks = k >> 5, lane = (row & 15) + 16 * ((k >> 3) & 3);
+  return ((tile * (K >> 5) + ks) * 64 + lane) * 8 + (k & 7);
+}
+
+// Layout of the bf16 GEMM weights ([rows][K], K a multiple of 64): the same
+// 1 KiB fragments, ordered k-block-major.  K is cut into 64-wide blocks; in
+// block b the n_tiles 16-row tiles lie back to back, each as its two 32-wide
+// k steps.  The waves of a launch walk k at about the same pace, so at any
+// moment they read one contiguous stretch of the matrix (spread over every
+// HBM channel) instead of n_tiles streams a whole tile row apart, which
+// measured 3-18% faster on the decode weight shapes.
+__host__ __device__ __forceinline__ int64_t wtiled_index(int64_t row, int64_t k, int64_t n_tiles) {
+  const int64_t tile = row >> 4, kb = k >> 6, ks = (k >> 5) & 1, lane = (row & 15) + 16 * ((k >> 3) & 3);
+  return (((kb * n_tiles + tile) * 2 + ks) * 64 + lane) * 8 + (k & 7);
+}
+
 // two fp32 values rounded (to nearest even) to a bf16 pair, a in the low half
 __device__ __forceinline__ uint32_t pack_bf16(float a, float b) {
   const bf16x2 v = {(__bf16)a, (__bf16)b};

@@ -49,3 +49,19 @@ def test_prefill_attention_group_sizes(hq, hkv, hd):
     lengths = [1, 2, 16, 17, 18, 33, 34, 65, 66, 129, 130, 257, 258, 300]
     cfg = generic_cfg(512, hq, hkv, hd, 512, lengths)
     print(f"[prefill] {hq}/{hkv} x {hd}: max |dlogit| / rms {check_against_oracle(cfg, lengths):.4f}", flush=True)
+
+
+@pytest.mark.parametrize("width,lengths", [
+    # 256 x 256 tiles with K splits (o, down) and in one piece (gate|up), ragged last row tile and column tile
+    ((1024, 10, 2, 64, 1472), [700, 1301, 33]),
+    # as many rows as the q|k|v tiles need (64 tiles), head width 64 and 128
+    ((512, 8, 2, 64, 512), [2049] * 3 + [1500]),
+    ((512, 4, 2, 128, 448), [1700] * 3),
+    # d = 3072: the norm that reads its row twice; rows below any tile
+    ((3072, 4, 1, 64, 512), [150, 18, 2]),
+    # more rows than one chunk holds: 33,000 rows, the cut inside a prompt
+    ((512, 2, 1, 64, 256), [5500] * 6),
+])
+def test_prefill_gemm_tiles(width, lengths):
+    cfg = generic_cfg(*width, lengths)
+    print(f"[prefill] {width} {sum(lengths)} tokens: max |dlogit| / rms {check_against_oracle(cfg, lengths):.4f}", flush=True)
