@@ -414,6 +414,8 @@ __device__ __forceinline__ void sample_epilogue(const f32x4 (&acc)[NT][MT], int 
 // (gate|up 13.0 -> 13.5 us, LM head 95 -> 104 us at 32 rows).
 // EPI = 2: Gumbel-max sampling epilogue of the LM head (one split only), see
 //          sample_epilogue; out is unused.
+// EPI = 3: fp32 logits of the LM head to sa.logits[slot][N] (one split only), for
+//          the nucleus sampler; out is unused.
 template <int NT, int MT, int KC, int EPI, bool XT>
 __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     void* __restrict__ out, int M, int m_base, int N, int K, int kps, int64_t split_stride,
@@ -505,6 +507,25 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
   }
   if constexpr (EPI == 2) {
     sample_epilogue<NT, MT>(acc, M, m_base, N, n0, sa, xs);
+  } else if constexpr (EPI == 3) {
+    // a caller's buffer may be 4-byte aligned only
+    const bool wide = (reinterpret_cast<uintptr_t>(sa.logits) & 15) == 0;
+#pragma unroll
+    for (int t = 0; t < MT; ++t) {
+      const int m = m_base + 16 * t + row;
+      if (m >= M) continue;
+      float* o = sa.logits + (size_t)sa.rows[m].slot * N + n0 + 4 * grp;
+#pragma unroll
+      for (int nt = 0; nt < NT; ++nt) {
+        if (n0 + 16 * nt >= N) continue;
+        if (wide) {
+          *(f32x4*)(o + 16 * nt) = acc[nt][t];
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) o[16 * nt + q] = acc[nt][t][q];
+        }
+      }
+    }
   } else if (EPI == 0) {
     float* o = (float*)out + (size_t)blockIdx.y * split_stride;
 #pragma unroll
@@ -2183,22 +2204,28 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
   if (!model_free) {
     if (c->md.dtype == SARA_BF16) {
       run_layers(c, c->rows_M, S);
-      // LM head with the Gumbel-max sampling epilogue: per (row, 128-id block)
-      // exact winners, reduced by k_sample_final
       const int nb = (c->V + 127) / 128;
-      nchunks = nb;
-      // top-p < 1: the GEMM also writes the logits ([slot][V]) for the
-      // nucleus sampler, whose winner replaces the epilogue's
-      float* lg_out = (c->topp && !logits) ? c->topp_logits : logits;
-      PROF_B(c);
-      launch_k(c, st, (k_gemm_bf16_lds<2, 8, 64, 2, 0>), dim3(nb, 1, (S + 127) / 128), dim3(256), 0,
-                         (const uint16_t*)c->x, (const uint16_t*)c->lm_head, (void*)nullptr, c->rows_M, c->V,
-                         c->d, c->d, (int64_t)0,
-                         SampleArgs{c->rows, (const CtlParams*)c->cp_dev, lg_out, c->samp_best, c->samp_idx, S});
-      PROF_E(c, kPGemmLM, c->V, c->d);
+      const dim3 lm_grid(nb, 1, (S + 127) / 128);
       if (c->topp) {
+        // top-p < 1: the GEMM writes the logits ([slot][V]) and the nucleus
+        // sampler draws from them (drawing in the epilogue as well, only to be
+        // replaced: 233 against 104 us at 128 rows)
+        float* lg_out = logits ? logits : c->topp_logits;
+        PROF_B(c);
+        launch_k(c, st, (k_gemm_bf16_lds<2, 8, 64, 3, 0>), lm_grid, dim3(256), 0, (const uint16_t*)c->x,
+                 (const uint16_t*)c->lm_head, (void*)nullptr, c->rows_M, c->V, c->d, c->d, (int64_t)0,
+                 SampleArgs{c->rows, (const CtlParams*)c->cp_dev, lg_out, nullptr, nullptr, S});
+        PROF_E(c, kPGemmLM, c->V, c->d);
         launch_topp_decode(c, st, lg_out, 1);
-        nchunks = kSampleChunks;
+      } else {
+        // LM head with the Gumbel-max sampling epilogue: per (row, 128-id block)
+        // exact winners, reduced by k_sample_final
+        nchunks = nb;
+        PROF_B(c);
+        launch_k(c, st, (k_gemm_bf16_lds<2, 8, 64, 2, 0>), lm_grid, dim3(256), 0, (const uint16_t*)c->x,
+                 (const uint16_t*)c->lm_head, (void*)nullptr, c->rows_M, c->V, c->d, c->d, (int64_t)0,
+                 SampleArgs{c->rows, (const CtlParams*)c->cp_dev, logits, c->samp_best, c->samp_idx, S});
+        PROF_E(c, kPGemmLM, c->V, c->d);
       }
     } else {
       run_layers(c, c->rows_M, S);

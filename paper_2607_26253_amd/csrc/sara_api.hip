@@ -77,8 +77,8 @@ int prof_collect(sara_ctx* c) {
       case kPGemmN1:
       case kPGemmO1:
         by = N * K * E + m * K * E + m * N * 4.0; fl = 2.0 * m * N * K; break;
-      case kPGemmLM:   // bf16: sampling epilogue, one (score, id) per row and 128-id block
-        by = N * K * E + m * K * E + (E == 2 ? m * ((N + 127) / 128) * 8.0 : m * N * 4.0);
+      case kPGemmLM:   // bf16, top_p = 1: sampling epilogue, one (score, id) per row and 128-id block
+        by = N * K * E + m * K * E + (E == 2 && !c->topp ? m * ((N + 127) / 128) * 8.0 : m * N * 4.0);
         fl = 2.0 * m * N * K;
         break;
       case kPGemmGU:   // output is the bf16 SwiGLU product [m][N/2]
