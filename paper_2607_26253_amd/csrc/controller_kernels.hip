@@ -82,8 +82,7 @@ __device__ double thompson_index(const CtlParams& cp, int uid, int n, int s, dou
 // ---------------------------------------------------------------------------
 __global__ void k_reset(Ctl* ctl, const CtlParams* __restrict__ cpp, int64_t budget, int32_t* status, int32_t* n_iss,
                         int32_t* n_done, int32_t* succ, int32_t* infl, double* peff,
-                        int32_t* slot_uid, int32_t* fin, int32_t* r_len, int32_t* r_reward,
-                        int32_t* btab) {
+                        int32_t* slot_uid, int32_t* fin, int32_t* r_len, int32_t* r_reward) {
   const CtlParams cp = *cpp;
   const int tid = blockIdx.x * blockDim.x + threadIdx.x;
   const int nth = gridDim.x * blockDim.x;
@@ -92,11 +91,6 @@ __global__ void k_reset(Ctl* ctl, const CtlParams* __restrict__ cpp, int64_t bud
   }
   for (int s = tid; s < cp.S; s += nth) { slot_uid[s] = -1; fin[s] = 0; }
   for (int r = tid; r < cp.U * cp.k; r += nth) { r_len[r] = 0; r_reward[r] = 0; }
-  // prompt block tables: row S + u holds the prompt's PB pages
-  for (int e = tid; e < cp.U * cp.PB; e += nth) {
-    int u = e / cp.PB, b = e - u * cp.PB;
-    btab[(size_t)(cp.S + u) * cp.MAXB + b] = u * cp.PB + b;
-  }
   if (tid == 0) {
     Ctl z = {};
     z.budget_left = budget;
@@ -239,7 +233,7 @@ __global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, c
     int32_t* __restrict__ status, int32_t* __restrict__ n_iss, int32_t* __restrict__ infl,
     double* __restrict__ peff, int32_t* __restrict__ slot_uid, int32_t* __restrict__ slot_j,
     int32_t* __restrict__ slot_gen, uint64_t* __restrict__ slot_hash,
-    int32_t* __restrict__ active, uint64_t* __restrict__ queue, int32_t* __restrict__ btab,
+    int32_t* __restrict__ active, uint64_t* __restrict__ queue,
     int64_t* __restrict__ log_draw, int64_t* __restrict__ log_asg, const double* __restrict__ prior_p,
     const double* __restrict__ prior_a, const double* __restrict__ prior_b) {
   __shared__ int buf[kCtlThreads];
@@ -346,16 +340,6 @@ __global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, c
     slot_hash[s] = reward_hash_init(cp.seed, cp.step, u);
     int64_t* la = log_asg + (asg_base + e) * 4;
     la[0] = tnext; la[1] = s; la[2] = u; la[3] = j;
-  }
-  // block tables of the newly assigned slots: shared prompt pages, then the
-  // slot's private pages (assigned rows only)
-  for (int e = tid; e < m * cp.MAXB; e += kCtlThreads) {
-    int a = e / cp.MAXB, b = e - a * cp.MAXB;
-    int s = freel[a];
-    uint64_t key = qs[a];
-    int u = (int)((key >> 16) & ((1ull << 26) - 1));
-    int32_t blk = (b < cp.PB) ? (u * cp.PB + b) : (cp.U * cp.PB + s * cp.SB + (b - cp.PB));
-    btab[(size_t)s * cp.MAXB + b] = blk;
   }
   // remaining queue
   for (int e = tid; e < qlen - m; e += kCtlThreads) queue[e] = qs[m + e];
@@ -523,7 +507,7 @@ __global__ void k_warm_decay(double* __restrict__ a, double* __restrict__ b, int
 int launch_reset(sara_ctx* c) {
   hipLaunchKernelGGL(k_reset, dim3(64), dim3(256), 0, c->stream, c->ctl, c->cp_dev, (int64_t)c->ad.budget_N,
                      c->status, c->n_iss, c->n_done, c->succ, c->infl, c->peff, c->slot_uid, c->fin,
-                     c->r_len, c->r_reward, c->btab);
+                     c->r_len, c->r_reward);
   return SARA_OK;
 }
 
@@ -537,7 +521,7 @@ int launch_decide(sara_ctx* c) {
 int launch_refill(sara_ctx* c) {
   hipLaunchKernelGGL(k_refill, dim3(1), dim3(kCtlThreads), 0, c->stream, c->ctl, c->cp_dev, c->status,
                      c->n_iss, c->infl, c->peff, c->slot_uid, c->slot_j, c->slot_gen, c->slot_hash,
-                     c->active, c->queue, c->btab, c->log_draw, c->log_asg, c->prior_p, c->prior_a, c->prior_b);
+                     c->active, c->queue, c->log_draw, c->log_asg, c->prior_p, c->prior_a, c->prior_b);
   return SARA_OK;
 }
 

@@ -194,7 +194,6 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
     r.tok = (g == 0) ? tok[off[u] + P - 1] : out_tok[(size_t)rid * max_new + g - 1];
     r.pos = P - 1 + g;
     r.plen = P - 1;
-    r.tab = s;
     r.slot = s;
     r.rid = rid;
     r.gen = g;
@@ -222,7 +221,7 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
 // Prefill rows of the chunk [r0, r0 + n): global prompt-token row r maps to
 // prompt u (pre[u] <= r < pre[u+1]) and token t = r - pre[u].
 __global__ __launch_bounds__(256) void k_prefill_rows(const int32_t* __restrict__ pre, int U,
-    int r0, int n, const int32_t* __restrict__ tok, const int32_t* __restrict__ off, int S,
+    int r0, int n, const int32_t* __restrict__ tok, const int32_t* __restrict__ off,
     RowDesc* __restrict__ rows, int32_t* __restrict__ rows_M, int PB) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i == 0) *rows_M = n;
@@ -238,7 +237,6 @@ __global__ __launch_bounds__(256) void k_prefill_rows(const int32_t* __restrict_
   d.tok = tok[off[u] + t];
   d.pos = t;
   d.plen = off[u + 1] - off[u] - 1;
-  d.tab = S + u;
   d.slot = -1;
   d.rid = -1;
   d.gen = -1;
@@ -672,33 +670,139 @@ __global__ void k_tile_weights_pairs(const uint16_t* __restrict__ src, uint16_t*
   }
 }
 
-// fp32 VALU GEMM for the fp32 model: 16x16 output tile per 256-thread block.
-__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ X,
-    const float* __restrict__ W, float* __restrict__ out, const int32_t* __restrict__ M_ptr,
-    int N, int K, int kps, int64_t split_stride) {
-  __shared__ float xs[16][33];
-  __shared__ float wsm[16][33];
-  const int M = *M_ptr;
-  const int m0 = blockIdx.z * 16, n0 = blockIdx.x * 16;
-  if (m0 >= M) return;
-  const int ty = threadIdx.x >> 4, tx = threadIdx.x & 15;
-  const int k_begin = blockIdx.y * kps, k_end = min(K, k_begin + kps);
-  float acc = 0.f;
-  for (int kk = k_begin; kk < k_end; kk += 32) {
-    for (int e = threadIdx.x; e < 16 * 32; e += 256) {
-      int r = e >> 5, c = e & 31;
-      int m = min(m0 + r, M - 1), n = min(n0 + r, N - 1);
-      bool in = kk + c < k_end;
-      xs[r][c] = in ? X[(size_t)m * K + kk + c] : 0.f;
-      wsm[r][c] = in ? W[(size_t)n * K + kk + c] : 0.f;
-    }
-    __syncthreads();
-#pragma unroll
-    for (int c = 0; c < 32; ++c) acc = fmaf(xs[ty][c], wsm[tx][c], acc);
-    __syncthreads();
+// fp32 GEMM on v_mfma_f32_16x16x4_f32 (fp32 products and sums) for the fp32
+// models: out[m][n] = sum_k X[m][k] W[n][k], K a multiple of 64, N of 16.
+// Block = 16 MT rows x 2 weight tiles of 16 rows; its 4 waves take a quarter of
+// K each, every lane loading 4 consecutive k of a row at a time (the k order
+// inside the MFMA is the same for X and W, so it is moot), D steps of 16 k in
+// flight, and meet in LDS in wave order.  Small batches are latency bound: the
+// loads wait for nothing (not even the live row count), K is not split over
+// blocks, and the epilogues replace passes of their own:
+// EPI 0: out[m][n], tiles 2b and 2b + 1.
+// EPI 1: SwiGLU; tile b of the gate rows and of the up rows (N = 2 ffn), out[m][ffn].
+// EPI 2: q|k|v; tiles b and b + half / 16 of a head: rotate-half RoPE of q and k,
+//        q to qbuf, k and v to the row's KV page.
+// 32 rows of 256 -> 2048: 5 us, where 16 x 16 tiles on the vector unit with a
+// barrier every 32 k took 10.
+struct F32Epi {
+  const RowDesc* rows;
+  const float2* rope;
+  float *qbuf, *kc, *vc;
+  int hq, hkv, hd, layer;
+  int64_t n_blocks;
+};
+template <int MT, int EPI>
+__global__ __launch_bounds__(256) void k_gemm_f32(const float* __restrict__ X, const float* __restrict__ W,
+    float* __restrict__ out, const int32_t* __restrict__ M_ptr, int M_cap, int N, int K, F32Epi ep) {
+  constexpr int D = 4;                                  // steps of 16 k in flight
+  __shared__ f32x4 red[4][2][MT][64];
+  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  const int row = lane & 15, grp = lane >> 4;
+  const int m0 = blockIdx.y * 16 * MT, ntl = N >> 4;
+  int t0, t1;                                           // the block's two weight tiles
+  if (EPI == 0) {
+    t0 = 2 * blockIdx.x;
+    t1 = min(t0 + 1, ntl - 1);
+  } else if (EPI == 1) {
+    t0 = blockIdx.x;
+    t1 = t0 + (ntl >> 1);
+  } else {
+    const int ht = ep.hd >> 5;                          // tiles in half a head
+    t0 = (blockIdx.x / ht) * 2 * ht + blockIdx.x % ht;
+    t1 = t0 + ht;
   }
-  int m = m0 + ty, n = n0 + tx;
-  if (m < M && n < N) out[(size_t)blockIdx.y * split_stride + (size_t)m * N + n] = acc;
+  const int kq = K >> 2, steps = kq >> 4;
+  const float* w0 = W + (size_t)(16 * t0 + row) * K + wave * kq + 4 * grp;
+  const float* w1 = W + (size_t)(16 * t1 + row) * K + wave * kq + 4 * grp;
+  const float* xp[MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t)   // rows past the live ones are computed and dropped
+    xp[t] = X + (size_t)min(m0 + 16 * t + row, M_cap - 1) * K + wave * kq + 4 * grp;
+  struct Stage { f32x4 a, b, x[MT]; };
+  Stage st[D];
+  auto load = [&](Stage& s, int j) {
+    const int o = 16 * min(j, steps - 1);
+    s.a = *(const f32x4*)(w0 + o);
+    s.b = *(const f32x4*)(w1 + o);
+#pragma unroll
+    for (int t = 0; t < MT; ++t) s.x[t] = *(const f32x4*)(xp[t] + o);
+  };
+#pragma unroll
+  for (int j = 0; j < D; ++j) load(st[j], j);
+  const int M = *M_ptr;
+  if (m0 >= M) return;
+  f32x4 acc[2][MT];
+#pragma unroll
+  for (int t = 0; t < MT; ++t) acc[0][t] = acc[1][t] = f32x4{0.f, 0.f, 0.f, 0.f};
+  for (int base = 0; base < steps; base += D) {
+#pragma unroll
+    for (int j = 0; j < D; ++j) {
+      if (base + j < steps) {
+#pragma unroll
+        for (int t = 0; t < MT; ++t)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            acc[0][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[j].a[q], st[j].x[t][q], acc[0][t], 0, 0, 0);
+            acc[1][t] = __builtin_amdgcn_mfma_f32_16x16x4f32(st[j].b[q], st[j].x[t][q], acc[1][t], 0, 0, 0);
+          }
+      }
+      if (base + D < steps) load(st[j], base + D + j);
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < MT; ++t) {
+    red[wave][0][t][lane] = acc[0][t];
+    red[wave][1][t][lane] = acc[1][t];
+  }
+  __syncthreads();
+  // wave w finishes (weight tile, row tile) pairs: lane (row, grp) holds row m, columns 4 grp ..+3
+  if (EPI == 0) {
+    for (int e = wave; e < 2 * MT; e += 4) {
+      const int i = e & 1, t = e >> 1, m = m0 + 16 * t + row;
+      const f32x4 v = ((red[0][i][t][lane] + red[1][i][t][lane]) + red[2][i][t][lane]) + red[3][i][t][lane];
+      if (m < M) *(f32x4*)(out + (size_t)m * N + 16 * (i ? t1 : t0) + 4 * grp) = v;
+    }
+    return;
+  }
+  for (int t = wave; t < MT; t += 4) {
+    const int m = m0 + 16 * t + row;
+    const f32x4 a = ((red[0][0][t][lane] + red[1][0][t][lane]) + red[2][0][t][lane]) + red[3][0][t][lane];
+    const f32x4 b = ((red[0][1][t][lane] + red[1][1][t][lane]) + red[2][1][t][lane]) + red[3][1][t][lane];
+    if (m >= M) continue;
+    if (EPI == 1) {
+      f32x4 r;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) r[q] = a[q] / (1.0f + expf(-a[q])) * b[q];
+      *(f32x4*)(out + (size_t)m * (N >> 1) + 16 * t0 + 4 * grp) = r;
+    } else {
+      const int hd = ep.hd, half = hd >> 1, h = 16 * t0 / hd, c = 16 * t0 % hd + 4 * grp;
+      const RowDesc r = ep.rows[m];
+      // page of the row's own position
+      const int rel = r.pos - r.plen;
+      const size_t pg = (size_t)ep.layer * ep.n_blocks + (rel < 0 ? r.kv0 + (r.pos >> 4) : r.kv1 + (rel >> 4));
+      const int tok = (rel < 0 ? r.pos : rel) & 15;
+      if (h < ep.hq + ep.hkv) {
+        f32x4 ra, rb;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float2 cs = ep.rope[(size_t)r.pos * half + c + q];
+          ra[q] = a[q] * cs.x - b[q] * cs.y;
+          rb[q] = b[q] * cs.x + a[q] * cs.y;
+        }
+        float* dst = h < ep.hq ? ep.qbuf + ((size_t)m * ep.hq + h) * hd
+                               : ep.kc + ((pg * ep.hkv + (h - ep.hq)) * kBlockTok + tok) * hd;
+        *(f32x4*)(dst + c) = ra;
+        *(f32x4*)(dst + c + half) = rb;
+      } else {
+        float* vp = ep.vc + (pg * ep.hkv + (h - ep.hq - ep.hkv)) * (size_t)hd * kBlockTok + tok;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          vp[(size_t)(c + q) * kBlockTok] = a[q];
+          vp[(size_t)(c + half + q) * kBlockTok] = b[q];
+        }
+      }
+    }
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -730,66 +834,33 @@ __device__ __forceinline__ float split_sum(const float* ws, int splits, int64_t 
 // serialise the memory round trips.
 __device__ __forceinline__ float mask01(bool keep) { return keep ? 1.0f : 0.0f; }
 
-// Page of position pos: block-table entries [0, PB) map the shared prompt
-// segment (positions < plen), entries [PB, MAXB) the private segment that
-// starts at position plen.
-__device__ __forceinline__ size_t kv_index(const RowDesc& r, const int32_t* btab, int MAXB, int PB,
-                                           int layer, int64_t n_blocks, int hkv, int g, int hd,
-                                           int dim, int pos) {
-  int e, o;
-  if (pos < r.plen) { e = pos >> 4; o = pos & 15; }
-  else { int q = pos - r.plen; e = PB + (q >> 4); o = q & 15; }
-  int64_t b = btab[(size_t)r.tab * MAXB + e];
-  return ((((size_t)layer * n_blocks + b) * hkv + g) * kBlockTok + o) * hd + dim;
-}
-
-// V pages are stored transposed, [hd][16 tokens] per (page, KV head), so that
-// the PV product reads 4 consecutive tokens of one dimension per lane.
-__device__ __forceinline__ size_t vt_index(const RowDesc& r, const int32_t* btab, int MAXB, int PB,
-                                           int layer, int64_t n_blocks, int hkv, int g, int hd,
-                                           int dim, int pos) {
-  int e, o;
-  if (pos < r.plen) { e = pos >> 4; o = pos & 15; }
-  else { int q = pos - r.plen; e = PB + (q >> 4); o = q & 15; }
-  int64_t b = btab[(size_t)r.tab * MAXB + e];
-  return ((((size_t)layer * n_blocks + b) * hkv + g) * hd + dim) * kBlockTok + o;
-}
-
-// Split-K sum of the fused q|k|v output, rotate-half RoPE on q and k,
-// q -> bf16 buffer, k and v -> the row's KV page.  pair = 1: the GEMM output
-// columns are in rotation-pair order (bf16 weights, see qkv_pair_col).
-template <typename T>
+// Split-K sum of the fused q|k|v output of a short prefill chunk (columns in
+// rotation-pair order, see qkv_pair_col), rotate-half RoPE on q and k, q -> bf16
+// buffer, k and v -> the row's prompt page.  V pages are stored transposed,
+// [hd][16 tokens] per (page, KV head), so that the PV product reads
+// consecutive tokens of one dimension per lane.
 __global__ __launch_bounds__(256) void k_qkv_epilogue(const int32_t* __restrict__ M_ptr,
     const RowDesc* __restrict__ rows, const float* __restrict__ ws, int splits, int64_t stride,
     const float2* __restrict__ rope, int hq, int hkv, int hd, int layer, int64_t n_blocks,
-    const int32_t* __restrict__ btab, int MAXB, int PB, T* __restrict__ qbuf, T* __restrict__ kc,
-    T* __restrict__ vc, int pair) {
+    uint16_t* __restrict__ qbuf, uint16_t* __restrict__ kc, uint16_t* __restrict__ vc) {
   const int half = hd >> 1, nh = hq + 2 * hkv, N = nh * hd;
   const int M = *M_ptr;
   for (int item = blockIdx.x; item < M * nh; item += gridDim.x) {
     const int i = item / nh, h = item - i * nh, c = threadIdx.x;
     const RowDesc r = rows[i];
-    const int ca = pair ? qkv_pair_col(h, c, hd) : h * hd + c;
-    const int cb = pair ? qkv_pair_col(h, c + half, hd) : h * hd + c + half;
-    float a = split_sum(ws, splits, stride, (size_t)i * N + ca);
-    float b = split_sum(ws, splits, stride, (size_t)i * N + cb);
+    float a = split_sum(ws, splits, stride, (size_t)i * N + qkv_pair_col(h, c, hd));
+    float b = split_sum(ws, splits, stride, (size_t)i * N + qkv_pair_col(h, c + half, hd));
+    const size_t pg = (size_t)layer * n_blocks + r.kv0 + (r.pos >> 4);
+    const int tok = r.pos & 15;
     if (h < hq + hkv) {
       float2 cs = rope[(size_t)r.pos * half + c];
-      float ra = a * cs.x - b * cs.y;
-      float rb = b * cs.x + a * cs.y;
-      if (h < hq) {
-        size_t q = ((size_t)i * hq + h) * hd;
-        st_f32(qbuf, q + c, ra);
-        st_f32(qbuf, q + c + half, rb);
-      } else {
-        int g = h - hq;
-        st_f32(kc, kv_index(r, btab, MAXB, PB, layer, n_blocks, hkv, g, hd, c, r.pos), ra);
-        st_f32(kc, kv_index(r, btab, MAXB, PB, layer, n_blocks, hkv, g, hd, c + half, r.pos), rb);
-      }
+      uint16_t* dst = h < hq ? qbuf + ((size_t)i * hq + h) * hd : kc + ((pg * hkv + (h - hq)) * kBlockTok + tok) * hd;
+      dst[c] = f32_to_bf16(a * cs.x - b * cs.y);
+      dst[c + half] = f32_to_bf16(b * cs.x + a * cs.y);
     } else {
-      int g = h - hq - hkv;
-      st_f32(vc, vt_index(r, btab, MAXB, PB, layer, n_blocks, hkv, g, hd, c, r.pos), a);
-      st_f32(vc, vt_index(r, btab, MAXB, PB, layer, n_blocks, hkv, g, hd, c + half, r.pos), b);
+      uint16_t* vp = vc + (pg * hkv + (h - hq - hkv)) * (size_t)hd * kBlockTok + tok;
+      vp[(size_t)c * kBlockTok] = f32_to_bf16(a);
+      vp[(size_t)(c + half) * kBlockTok] = f32_to_bf16(b);
     }
   }
 }
@@ -888,8 +959,6 @@ __global__ __launch_bounds__(256) void k_residual_norm_v(const int32_t* __restri
   }
 }
 
-// a = silu(g) * u from the fused gate|up output ([m][2*ffn]); grid-stride
-// over the M * ffn outputs of the live rows
 // bf16 decode variant of the residual norm: one row per block, one float4
 // of the row per thread (blockDim = d/4 rounded up to whole waves).  The
 // residual, the norm weight and the row's split-K partials of that float4
@@ -948,38 +1017,25 @@ __global__ __launch_bounds__(1024) void k_residual_norm_f4(const int32_t* __rest
   }
 }
 
-template <typename T>
-__global__ __launch_bounds__(256) void k_swiglu(const int32_t* __restrict__ M_ptr,
-    const float* __restrict__ ws, int splits, int64_t stride, int ffn, T* __restrict__ a) {
-  const size_t total = (size_t)(*M_ptr) * ffn;
-  for (size_t e = (size_t)blockIdx.x * 256 + threadIdx.x; e < total; e += (size_t)gridDim.x * 256) {
-    size_t i = e / ffn, f = e - i * ffn;
-    size_t base = i * 2 * ffn;
-    float g = split_sum(ws, splits, stride, base + f);
-    float u = split_sum(ws, splits, stride, base + ffn + f);
-    float sg = g / (1.0f + expf(-g));
-    st_f32(a, e, sg * u);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // paged GQA attention
 // ---------------------------------------------------------------------------
-// Block (row i, KV head g, context split c) attends the G query heads of KV
-// head g over positions [c*SPLIT, min(ctx, (c+1)*SPLIT)) of the row's
-// sequence with an online softmax, tiles of 64 tokens staged in LDS; the
+// fp32 models.  Block (row i, KV head g, context split c) attends the G query
+// heads of KV head g over positions [c*SPLIT, min(ctx, (c+1)*SPLIT)) of the row's
+// sequence with an online softmax, tiles of 64 tokens staged in LDS.  A context
+// of at most one split (n_splits == 1) writes its output; otherwise the
 // unnormalised output, running max and sum go to a partial buffer that the
-// combine kernel merges across splits.  Pages come from the block table:
-// positions below plen live in the prompt's shared pages, later ones in the
-// row's private pages.
-template <typename T, int HD>
+// combine kernel merges across splits.  Positions below plen live in the
+// prompt's shared pages (kv0 + e), later ones in the row's private pages (kv1 +
+// e).
+template <int HD>
 __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M_ptr,
-    const RowDesc* __restrict__ rows, const T* __restrict__ qbuf, const T* __restrict__ kc,
-    const T* __restrict__ vc, const int32_t* __restrict__ btab, int MAXB, int PB, int layer,
-    int64_t n_blocks, int hq, int hkv, int n_splits, float scale, float* __restrict__ part) {
+    const RowDesc* __restrict__ rows, const float* __restrict__ qbuf, const float* __restrict__ kc,
+    const float* __restrict__ vc, int layer, int64_t n_blocks, int hq, int hkv, int n_splits, float scale,
+    float* __restrict__ part, float* __restrict__ out) {
   __shared__ float q_s[kMaxGroup][HD];
   __shared__ float k_s[kAttnTile][HD + 1];
-  __shared__ float v_s[kAttnTile][HD];
+  __shared__ float v_s[HD][kAttnTile + 1];
   __shared__ float p_s[kMaxGroup][kAttnTile];
   __shared__ float m_s[kMaxGroup], l_s[kMaxGroup], al_s[kMaxGroup];
   const int i = blockIdx.x, g = blockIdx.y, c = blockIdx.z;
@@ -992,9 +1048,16 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
   const int G = hq / hkv;
   const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
   constexpr int DPT = HD / 64;  // dims per thread in the PV product
+  // (page, offset) of position pos as the offset of its 16-token page slice plus the token
+  auto page_of = [&](int pos, int& tok) {
+    const int rel = pos - r.plen;
+    tok = (rel < 0 ? pos : rel) & 15;
+    const size_t b = (size_t)layer * n_blocks + (rel < 0 ? r.kv0 + (pos >> 4) : r.kv1 + (rel >> 4));
+    return (b * hkv + g) * (size_t)(kBlockTok * HD);
+  };
   for (int e = tid; e < G * HD; e += 256) {
     int gh = e / HD, dd = e - gh * HD;
-    q_s[gh][dd] = ld_f32(qbuf, ((size_t)i * hq + g * G + gh) * HD + dd);
+    q_s[gh][dd] = qbuf[((size_t)i * hq + g * G + gh) * HD + dd];
   }
   if (tid < kMaxGroup) { m_s[tid] = -INFINITY; l_s[tid] = 0.f; }
   float o[2][DPT];
@@ -1005,13 +1068,30 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
   __syncthreads();
   for (int ts = t0; ts < t1; ts += kAttnTile) {
     const int n = min(kAttnTile, t1 - ts);
-    for (int e = tid; e < n * HD; e += 256) {
-      int tk = e / HD, dd = e - tk * HD;
-      k_s[tk][dd] = ld_f32(kc, kv_index(r, btab, MAXB, PB, layer, n_blocks, hkv, g, HD, dd, ts + tk));
-      v_s[tk][dd] = ld_f32(vc, vt_index(r, btab, MAXB, PB, layer, n_blocks, hkv, g, HD, dd, ts + tk));
+    {
+      // K: thread (token tid / 4, a quarter of its dims); V: thread (token lane,
+      // every fourth dim); tokens past the tile repeat its last
+      constexpr int KQ = HD / 16, VQ = HD / 4;
+      int tok;
+      const float* kp = kc + page_of(min(ts + (tid >> 2), t1 - 1), tok) + (tid & 3) * (HD / 4);
+      kp += tok * HD;
+      f32x4 kv[KQ];
+#pragma unroll
+      for (int e = 0; e < KQ; ++e) kv[e] = *(const f32x4*)(kp + 4 * e);
+      const size_t vpg = page_of(min(ts + lane, t1 - 1), tok);
+      const float* vp = vc + vpg + tok;
+      float vv[VQ];
+#pragma unroll
+      for (int e = 0; e < VQ; ++e) vv[e] = vp[(wave + 4 * e) * kBlockTok];
+#pragma unroll
+      for (int e = 0; e < KQ; ++e)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) k_s[tid >> 2][(tid & 3) * (HD / 4) + 4 * e + q] = kv[e][q];
+#pragma unroll
+      for (int e = 0; e < VQ; ++e) v_s[wave + 4 * e][lane] = vv[e];
     }
     __syncthreads();
-    // scores: thread (token lane, head wave / wave + 4)
+    // scores and online softmax update: thread (token lane), heads wave and wave + 4
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
       int gh = wave + 4 * a;
@@ -1023,16 +1103,6 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
           for (int dd = 0; dd < HD; ++dd) acc = fmaf(q_s[gh][dd], k_s[lane][dd], acc);
           sc = acc * scale;
         }
-        p_s[gh][lane] = sc;
-      }
-    }
-    __syncthreads();
-    // online softmax update, one wave per head pair
-#pragma unroll
-    for (int a = 0; a < 2; ++a) {
-      int gh = wave + 4 * a;
-      if (gh < G) {
-        float sc = p_s[gh][lane];
         float mt = wave_max(sc);
         float mo = m_s[gh];
         float mn = fmaxf(mo, mt);
@@ -1048,7 +1118,7 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
       }
     }
     __syncthreads();
-    // o = o * alpha + P V ; thread (dims lane*DPT.., heads wave, wave + 4)
+    // o = o * alpha + P V ; thread (dims lane, lane + 64, heads wave, wave + 4)
 #pragma unroll
     for (int a = 0; a < 2; ++a) {
       int gh = wave + 4 * a;
@@ -1059,7 +1129,7 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
         for (int tk = 0; tk < n; ++tk) {
           float pv = p_s[gh][tk];
 #pragma unroll
-          for (int b = 0; b < DPT; ++b) o[a][b] = fmaf(pv, v_s[tk][lane * DPT + b], o[a][b]);
+          for (int b = 0; b < DPT; ++b) o[a][b] = fmaf(pv, v_s[lane + 64 * b][tk], o[a][b]);
         }
       }
     }
@@ -1070,9 +1140,15 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
   for (int a = 0; a < 2; ++a) {
     int gh = wave + 4 * a;
     if (gh < G) {
+      if (n_splits == 1) {
+        float* dst = out + ((size_t)i * hq + g * G + gh) * HD;
+#pragma unroll
+        for (int b = 0; b < DPT; ++b) dst[lane + 64 * b] = o[a][b] / l_s[gh];
+        continue;
+      }
       float* dst = part + ((((size_t)i * hkv + g) * n_splits + c) * kMaxGroup + gh) * (HD + 2);
 #pragma unroll
-      for (int b = 0; b < DPT; ++b) dst[lane * DPT + b] = o[a][b];
+      for (int b = 0; b < DPT; ++b) dst[lane + 64 * b] = o[a][b];
       if (lane == 0) { dst[HD] = m_s[gh]; dst[HD + 1] = l_s[gh]; }
     }
   }
@@ -1982,24 +2058,21 @@ int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, i
   return SARA_OK;
 }
 
-// fp32 GEMM into partials ws[split][M_cap][N]
-static int gemm_f32(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
-                    int& splits_out, int max_splits = 1 << 30) {
-  const int64_t stride = (int64_t)M_cap * N;
-  int tiles_n = (N + 15) / 16, zb = (M_cap + 15) / 16;
-  int want = (tiles_n * zb >= 256) ? 1 : (256 + tiles_n * zb - 1) / (tiles_n * zb);
-  int chunks = K / 32;
-  int splits = want < chunks ? want : chunks;
-  if (splits > max_splits) splits = max_splits;
-  if (splits < 1) splits = 1;
-  int kps = ((chunks + splits - 1) / splits) * 32;
-  splits = (K + kps - 1) / kps;
-  if ((int64_t)splits * stride > c->ws_floats) { splits = 1; kps = K; }
-  dim3 grid(tiles_n, splits, zb);
-  launch_k(c, c->stream, k_gemm_f32, grid, dim3(256), 0, (const float*)X, (const float*)W,
-                     c->ws, M_ptr, N, K, kps, stride);
-  splits_out = splits;
-  return SARA_OK;
+// fp32 GEMM into out (see k_gemm_f32).  Four row tiles a block in a prefill,
+// two in decode, where few rows are live and the row count is known on the
+// device only.
+template <int EPI>
+static void gemm_f32(sara_ctx* c, const void* X, const void* W, float* out, const int32_t* M_ptr, int M_cap, int N,
+                     int K, int layer = 0) {
+  const F32Epi ep{c->rows, c->rope, (float*)c->qbuf, (float*)c->kc, (float*)c->vc, c->hq, c->hkv, c->hd, layer,
+                  c->n_blocks};
+  const int bx = EPI == 0 ? (N / 16 + 1) / 2 : N / 32;
+  if (c->in_prefill)
+    launch_k(c, c->stream, (k_gemm_f32<4, EPI>), dim3(bx, (M_cap + 63) / 64), dim3(256), 0, (const float*)X,
+             (const float*)W, out, M_ptr, M_cap, N, K, ep);
+  else
+    launch_k(c, c->stream, (k_gemm_f32<2, EPI>), dim3(bx, (M_cap + 31) / 32), dim3(256), 0, (const float*)X,
+             (const float*)W, out, M_ptr, M_cap, N, K, ep);
 }
 
 #define PROF_B(c) do { if ((c)->prof_active) prof_begin(c); } while (0)
@@ -2068,14 +2141,10 @@ static void residual_norm_decode(sara_ctx* c, const int32_t* M_ptr, int M_cap, i
            c->ws, sp, (int64_t)M_cap * c->d, c->d, c->h, w, c->md.rms_eps, (uint16_t*)c->x, x_tiled);
 }
 
-template <typename T>
-static void qkv_epilogue(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, int l) {
-  launch_k(c, c->stream, k_qkv_epilogue<T>, dim3(2048), dim3(c->hd / 2), 0, M_ptr, c->rows, c->ws, sp,
-           (int64_t)M_cap * c->nqkv, c->rope, c->hq, c->hkv, c->hd, l, c->n_blocks, c->btab, c->MAXB, c->PB,
-           (T*)c->qbuf, (T*)c->kc, (T*)c->vc, sizeof(T) == 2 ? 1 : 0);
-}
 void launch_qkv_epilogue_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int sp, int layer) {
-  qkv_epilogue<uint16_t>(c, M_ptr, M, sp, layer);
+  launch_k(c, c->stream, k_qkv_epilogue, dim3(2048), dim3(c->hd / 2), 0, M_ptr, c->rows, c->ws, sp,
+           (int64_t)M * c->nqkv, c->rope, c->hq, c->hkv, c->hd, layer, c->n_blocks, (uint16_t*)c->qbuf,
+           (uint16_t*)c->kc, (uint16_t*)c->vc);
 }
 
 // bf16 decode: the live rows of a step through every layer
@@ -2151,40 +2220,35 @@ static void layers_f32(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
   const int d = c->d;
   float* x = (float*)c->x;
   for (int l = 0; l < c->L; ++l) {
-    int sp = 1;
     PROF_B(c);
-    gemm_f32(c, x, c->w_qkv[l], M_ptr, M_cap, c->nqkv, d, sp);
-    PROF_E(c, kPGemmN1, c->nqkv, d);
-    PROF_B(c);
-    qkv_epilogue<float>(c, M_ptr, M_cap, sp, l);
-    PROF_E(c, kPQkv, c->nqkv, 0);
+    gemm_f32<2>(c, x, c->w_qkv[l], nullptr, M_ptr, M_cap, c->nqkv, d, l);
+    PROF_E(c, kPQkvRope, c->nqkv, d);
     if (c->in_prefill && l + 1 == c->L) break;
     PROF_B(c);
-    launch_k(c, st, (k_attention<float, HD>), dim3(M_cap, c->hkv, c->attn_splits_max), dim3(256), 0, M_ptr, c->rows,
-             (const float*)c->qbuf, (const float*)c->kc, (const float*)c->vc, c->btab, c->MAXB, c->PB, l, c->n_blocks,
-             c->hq, c->hkv, c->attn_splits_max, 1.0f / sqrtf((float)HD), c->attn_part);
+    launch_k(c, st, (k_attention<HD>), dim3(M_cap, c->hkv, c->attn_splits_max), dim3(256), 0, M_ptr, c->rows,
+             (const float*)c->qbuf, (const float*)c->kc, (const float*)c->vc, l, c->n_blocks, c->hq, c->hkv,
+             c->attn_splits_max, 1.0f / sqrtf((float)HD), c->attn_part, x);
     PROF_E(c, kPAttn, 0, 0);
+    if (c->attn_splits_max > 1) {
+      PROF_B(c);
+      launch_k(c, st, (k_attn_combine<float, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq, c->hkv,
+               c->attn_splits_max, 0, 0, x);
+      PROF_E(c, kPCombine, 0, 0);
+    }
     PROF_B(c);
-    launch_k(c, st, (k_attn_combine<float, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq, c->hkv,
-             c->attn_splits_max, 0, 0, x);
-    PROF_E(c, kPCombine, 0, 0);
-    PROF_B(c);
-    gemm_f32(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, sp);
+    gemm_f32<0>(c, x, c->w_o[l], c->ws, M_ptr, M_cap, d, c->qdim);
     PROF_E(c, kPGemmN1, d, c->qdim);
     PROF_B(c);
-    residual_norm<float>(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 1) * d);
+    residual_norm<float>(c, M_ptr, M_cap, 1, c->norms + (size_t)(2 * l + 1) * d);
     PROF_E(c, kPResNorm, d, 0);
     PROF_B(c);
-    gemm_f32(c, x, c->w_gu[l], M_ptr, M_cap, 2 * c->ffn, d, sp);
-    PROF_E(c, kPGemmN1, 2 * c->ffn, d);
+    gemm_f32<1>(c, x, c->w_gu[l], (float*)c->xa, M_ptr, M_cap, 2 * c->ffn, d);
+    PROF_E(c, kPGemmGU, 2 * c->ffn, d);
     PROF_B(c);
-    launch_k(c, st, k_swiglu<float>, dim3(1024), dim3(256), 0, M_ptr, c->ws, sp, (int64_t)M_cap * 2 * c->ffn, c->ffn, x);
-    PROF_E(c, kPSwiglu, c->ffn, 0);
-    PROF_B(c);
-    gemm_f32(c, x, c->w_d[l], M_ptr, M_cap, d, c->ffn, sp);
+    gemm_f32<0>(c, c->xa, c->w_d[l], c->ws, M_ptr, M_cap, d, c->ffn);
     PROF_E(c, kPGemmN1, d, c->ffn);
     PROF_B(c);
-    residual_norm<float>(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d);   // the next layer's, or the final one
+    residual_norm<float>(c, M_ptr, M_cap, 1, c->norms + (size_t)(2 * l + 2) * d);   // the next layer's, or the final one
     PROF_E(c, kPResNorm, d, 0);
   }
 }
@@ -2210,7 +2274,7 @@ int launch_prefill(sara_ctx* c) {
   for (int64_t r0 = 0; r0 < rows_total; r0 += c->prefill_rows, ++chunk) {
     int n = (int)((rows_total - r0 < c->prefill_rows) ? rows_total - r0 : c->prefill_rows);
     launch_k(c, st, k_prefill_rows, dim3((n + 255) / 256), dim3(256), 0, c->pre, c->U, (int)r0,
-                       n, c->tok, c->off, c->S, c->rows, c->rows_M, c->PB);
+                       n, c->tok, c->off, c->rows, c->rows_M, c->PB);
     if (c->md.dtype == SARA_BF16) {
       prefill_layers_bf16(c, c->rows_M, n, chunk);
     } else {
@@ -2308,10 +2372,8 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
       }
     } else {
       run_layers(c, c->rows_M, S);
-      int sp;
-      // one K split: ws then holds the logits [M][V] directly
       PROF_B(c);
-      gemm_f32(c, c->x, c->lm_head, c->rows_M, S, c->V, c->d, sp, 1);
+      gemm_f32<0>(c, c->x, c->lm_head, c->ws, c->rows_M, S, c->V, c->d);   // logits [M][V]
       PROF_E(c, kPGemmLM, c->V, c->d);
       if (c->topp) {
         launch_topp_decode(c, st, c->ws, 0);

@@ -35,7 +35,7 @@ static int einval(const std::string& msg) {
 
 const char* const kProfNames[kPNumClasses] = {
     "k_gemm_bf16_lds<1,8,64,0,0>", "k_gemm_bf16_lds<2,8,64,1,0>", "k_gemm_bf16_lds<2,8,64,2,0>",
-    "k_attn_dec<128>", "k_attn_combine", "k_qkv_epilogue", "k_residual_norm_f4", "k_swiglu",
+    "k_attn_dec<128>", "k_attn_combine", "k_residual_norm_f4",
     "k_embed_norm", "k_sample_partial", "k_sample_final", "k_decode_rows", "k_copy_logits", "k_qkv_rope",
     "k_topp_max", "k_topp_hist", "k_topp_pick", "k_gemm_bf16_lds<1,8,64,0,2>",
     ".gemm[q|k|v]", ".gemm[o]", ".gemm[gate|up]", ".gemm[down]", ".gemm[lm_head]"};
@@ -88,11 +88,9 @@ int prof_collect(sara_ctx* c) {
         fl = 4.0 * sum_ctx * c->qdim;
         break;
       case kPCombine: by = m * c->qdim * (4.0 + E); break;
-      case kPQkv: by = m * N * (4.0 + E); break;
       case kPQkvRope:   // fused q|k|v weights, normed input rows, q and the appended k, v
         by = N * K * E + m * K * E + m * N * E; fl = 2.0 * m * N * K; break;
       case kPResNorm: by = m * N * (12.0 + E); break;
-      case kPSwiglu: by = m * N * (8.0 + E); break;
       case kPEmbed: by = m * N * (2.0 * E + 4.0); break;
       case kPSampleP: by = m * N * 4.0; break;
       case kPToppMax: by = m * N * 4.0; break;   // the row's fp32 logits, once
@@ -244,10 +242,8 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
       const int64_t npf = std::max<int64_t>(c->nqkv, c->d);
       c->ws_floats = std::max<int64_t>((int64_t)kMaxSplitsDec * c->S * c->d, 2 * (int64_t)4096 * npf);
     } else {
-      // fp32: also the logits [S][V] and the gate|up output [rows][2 ffn]
-      int64_t nd = std::max<int64_t>({c->V, c->nqkv, 2 * (int64_t)c->ffn, c->d});
-      int64_t np = std::max<int64_t>({c->nqkv, 2 * (int64_t)c->ffn, c->d});
-      c->ws_floats = std::max<int64_t>((int64_t)c->S * nd, (int64_t)c->prefill_rows * np);
+      // fp32: the o and down outputs [rows][d], the logits [S][V]
+      c->ws_floats = std::max<int64_t>((int64_t)c->S * std::max(c->V, c->d), (int64_t)c->prefill_rows * c->d);
     }
   }
   const size_t E = (size_t)c->elt;
@@ -268,11 +264,10 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
     ALLOC(c->w_d[l], (size_t)d * c->ffn * E);
   }
   ALLOC(c->norms, sizeof(float) * (2 * c->L + 1) * d);
-  // KV cache and tables
+  // KV cache and rotation tables
   size_t kv_bytes = (size_t)c->L * c->n_blocks * c->hkv * kBlockTok * c->hd * E;
   ALLOC(c->kc, kv_bytes);
   ALLOC(c->vc, kv_bytes);
-  ALLOC(c->btab, sizeof(int32_t) * (size_t)(c->S + c->U) * c->MAXB);
   ALLOC(c->rope, sizeof(float2) * (size_t)c->max_pos * (c->hd / 2));
   ALLOC(c->row_rope, sizeof(float2) * (size_t)c->S * (c->hd / 2));
   ALLOC(c->prior_a, sizeof(double) * (size_t)c->U);
@@ -318,10 +313,9 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->rows, sizeof(RowDesc) * c->row_cap);
   ALLOC(c->rows_M, sizeof(int32_t));
   ALLOC(c->h, sizeof(float) * (size_t)c->row_cap * d);
-  const bool bf16 = md->dtype == SARA_BF16;   // bf16 models keep the SwiGLU output in xa, fp32 ones in x
-  ALLOC(c->x, (size_t)c->row_cap * std::max({c->d, bf16 ? 0 : c->ffn, c->qdim}) * E);
+  ALLOC(c->x, (size_t)c->row_cap * std::max(c->d, c->qdim) * E);
   ALLOC(c->qbuf, (size_t)c->row_cap * c->qdim * E);
-  if (bf16) ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
+  ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
   ALLOC(c->ws, sizeof(float) * (size_t)c->ws_floats);
   // context-split partials: fp32 attention (every row), bf16 decode rows
   ALLOC(c->attn_part, sizeof(float) *

@@ -51,14 +51,13 @@ struct RowDesc {
   int32_t tok;      // input token id
   int32_t pos;      // position of the token (KV append position)
   int32_t plen;     // tokens of the sequence's shared prompt segment (P - 1)
-  int32_t tab;      // block-table row
   int32_t slot;     // decode: slot index; prefill: -1
   int32_t rid;      // decode: rollout id uid*k + j
   int32_t gen;      // decode: generated index i
   int32_t uid;
   // KV extents: page ids of a sequence are kv0 + e for its shared prompt
-  // segment (entries e < PB of its block-table row) and kv1 + e for its
-  // private segment (decode rows; -1 for prefill rows)
+  // segment and kv1 + e for its private segment (decode rows; -1 for prefill
+  // rows)
   int32_t kv0;
   int32_t kv1;
 };
@@ -111,10 +110,9 @@ struct sara_ctx {
   std::vector<void*> w_qkv, w_o, w_gu, w_d;
   float* norms = nullptr;         // [2L+1][d]: attn l, ffn l, final
 
-  // KV cache [L][n_blocks][hkv][16][hd], block tables [(S+U)][MAXB]
+  // KV cache [L][n_blocks][hkv][16][hd] (V transposed, [hd][16])
   void* kc = nullptr;
   void* vc = nullptr;
-  int32_t* btab = nullptr;
   float2* rope = nullptr;         // [max_pos][hd/2] (cos, sin)
   float2* row_rope = nullptr;     // [S][hd/2] (cos, sin) at each decode row's position
   sara::AttnItem* attn_items = nullptr; // [S * dec_splits_max] decode attention work list of the step
@@ -213,7 +211,7 @@ namespace sara {
 
 // one class per kernel (per template instance for the GEMMs, as a kernel
 // trace names them), then a breakdown of the GEMMs by weight matrix
-enum ProfClass { kPGemmN1, kPGemmGU, kPGemmLM, kPAttn, kPCombine, kPQkv, kPResNorm, kPSwiglu,
+enum ProfClass { kPGemmN1, kPGemmGU, kPGemmLM, kPAttn, kPCombine, kPResNorm,
                  kPEmbed, kPSampleP, kPSampleF, kPRows, kPCopy, kPQkvRope, kPToppMax, kPToppHist, kPToppSel,
                  kPGemmO1, kPGemmQkv, kPGemmO, kPGemmGu, kPGemmD, kPGemmLm, kPNumClasses };
 extern const char* const kProfNames[kPNumClasses];

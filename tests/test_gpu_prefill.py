@@ -65,3 +65,27 @@ def test_prefill_attention_group_sizes(hq, hkv, hd):
 def test_prefill_gemm_tiles(width, lengths):
     cfg = generic_cfg(*width, lengths)
     print(f"[prefill] {width} {sum(lengths)} tokens: max |dlogit| / rms {check_against_oracle(cfg, lengths):.4f}", flush=True)
+
+
+@pytest.mark.parametrize("width,lengths,max_new", [
+    # rows around the 32- and 64-row blocks, K of one step a wave, odd column-tile counts
+    ((64, 1, 1, 64, 64), [1, 2, 17, 40, 65], 3),
+    ((192, 3, 1, 128, 320), [33, 64, 66, 5], 4),
+    # contexts of several 256-token splits, a tile across the prompt's end; 33 rows
+    ((128, 8, 1, 64, 192), [600, 257, 258] + [3] * 30, 20),
+])
+def test_f32_layers(width, lengths, max_new):
+    d, hq, hkv, hd, ffn = width
+    cfg = generic_cfg(d, hq, hkv, hd, ffn, lengths, vocab=528, max_new=max_new)
+    cfg["model"].update(dtype="f32", eos_id=-1)
+    w, pool, seed = W.make_weights(cfg), W.pool_with_lengths(cfg, lengths), W.sampling_seed(cfg)
+    ora = ORUN.run_step(cfg, w, pool, seed, keep_logits=lambda u, j, i: True)
+    ctx, _ = device_setup(cfg, w)
+    gpu = run_gpu_step(ctx, cfg, pool, forced=forced_table(cfg, ora["rollouts_detail"]), capture_logits=True)
+    ctx.close()
+    compare_logs(gpu["logs"], ora)
+    # fp32 against the fp64 oracle: K <= 1024 products a sum and a few layers leave ~1e-6 of the
+    # logits' rms; the package's bound for fp32 models is 1e-3
+    worst = max(float(np.max(np.abs(gpu["logits"][t][s] - ora["logits"][key]))) for (t, s), key in slot_rows(gpu).items())
+    print(f"[f32] {width}: max |dlogit| {worst:.2e}", flush=True)
+    assert worst <= 1e-4
