@@ -49,16 +49,23 @@ __device__ double pow_seq(double x, int e) {
   for (int i = 0; i < e; ++i) p = p * x;
   return p;
 }
-__device__ double thompson_index(const CtlParams& cp, int uid, int n, int s, double a0, double b0) {
+// Out of line, like peff_call: the fp64 lgammas and the Philox rounds would
+// otherwise cost the phases around them their registers (several hundred
+// spilled) on every step, for calls that few steps make.
+__device__ __attribute__((noinline)) double peff_call(int n, int s, int k, double a0, double b0) {
+  return peff_dev(n, s, k, a0, b0);
+}
+__device__ __attribute__((noinline)) double thompson_index(const CtlParams* cpp, int uid, int n, int s, double a0,
+                                                           double b0) {
   if (s >= 1 && n - s >= 1) return 1.0;
-  const int r = cp.k - n;
+  const int k = cpp->k, r = k - n;
   if (r <= 0) return 0.0;
   const double a = a0 + (double)s, b = b0 + (double)(n - s);
   if (a != floor(a) || b != floor(b) || a < 1.0 || b < 1.0 || a + b - 1.0 > (double)kThompsonMaxM)
-    return peff_dev(n, s, cp.k, a0, b0);
+    return peff_call(n, s, k, a0, b0);
   const int ia = (int)a, m = (int)(a + b) - 1;
   uint32_t k0, k1;
-  sampler_key(cp.seed, cp.step, k0, k1);
+  sampler_key(cpp->seed, cpp->step, k0, k1);
   uint32_t lo = 0u, hi = 0xFFFFFFFFu;
   while (lo < hi) {
     const uint32_t mid = lo + ((hi - lo) >> 1);
@@ -72,7 +79,7 @@ __device__ double thompson_index(const CtlParams& cp, int uid, int n, int s, dou
     else lo = mid + 1u;
   }
   const double g = ((double)lo + 0.5) * 0x1p-32;
-  if (n == 0) return (1.0 - pow_seq(g, cp.k)) - pow_seq(1.0 - g, cp.k);
+  if (n == 0) return (1.0 - pow_seq(g, k)) - pow_seq(1.0 - g, k);
   if (s == 0) return 1.0 - pow_seq(1.0 - g, r);
   return 1.0 - pow_seq(g, r);
 }
@@ -100,18 +107,35 @@ __global__ void k_reset(Ctl* ctl, const CtlParams* __restrict__ cpp, int64_t bud
   }
 }
 
+// what the decide and refill phases read and write
+struct CtlState {
+  Ctl* ctl;
+  const CtlParams* cpp;
+  int32_t *status, *n_iss, *n_done, *succ, *infl;
+  double* peff;
+  int32_t *slot_uid, *slot_j, *slot_gen, *slot_tok;
+  uint64_t* slot_hash;
+  int32_t *fin, *r_len, *r_reward;
+  ActiveRow* active;
+  uint64_t* queue;
+  int64_t *log_dec, *log_draw, *log_asg, *log_fin;
+  const double *prior_p, *prior_a, *prior_b;
+  const int32_t *tok, *off;
+};
+
 // ---------------------------------------------------------------------------
 // decide: apply finished rollouts, then Eq. decide for quiescent prompts
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kCtlThreads) void k_decide(Ctl* __restrict__ ctl, const CtlParams* __restrict__ cpp,
-    int32_t* __restrict__ status, int32_t* __restrict__ n_iss, int32_t* __restrict__ n_done,
-    int32_t* __restrict__ succ, int32_t* __restrict__ infl, double* __restrict__ peff,
-    int32_t* __restrict__ slot_uid, const int32_t* __restrict__ slot_j,
-    int32_t* __restrict__ fin, const int32_t* __restrict__ r_len,
-    const int32_t* __restrict__ r_reward, uint64_t* __restrict__ queue,
-    int64_t* __restrict__ log_dec, int64_t* __restrict__ log_fin,
-    const double* __restrict__ prior_a, const double* __restrict__ prior_b) {
-  __shared__ int buf[kCtlThreads];
+__device__ __forceinline__ void decide(const CtlState& st, int* buf) {
+  Ctl* ctl = st.ctl;
+  const CtlParams* cpp = st.cpp;
+  int32_t *status = st.status, *n_iss = st.n_iss, *n_done = st.n_done, *succ = st.succ, *infl = st.infl;
+  double* peff = st.peff;
+  int32_t *slot_uid = st.slot_uid, *slot_j = st.slot_j, *fin = st.fin;
+  const int32_t *r_len = st.r_len, *r_reward = st.r_reward;
+  uint64_t* queue = st.queue;
+  int64_t *log_dec = st.log_dec, *log_fin = st.log_fin;
+  const double *prior_a = st.prior_a, *prior_b = st.prior_b;
   __shared__ int s_nfin, s_ndec, s_qlen, s_dC, s_dA, s_dAb, s_more;
   __shared__ unsigned long long s_refund;
   __shared__ int s_done;
@@ -174,7 +198,7 @@ __global__ __launch_bounds__(kCtlThreads) void k_decide(Ctl* __restrict__ ctl, c
       pred = 1;
       n = atomicAdd(&n_done[u], 0);
       s = atomicAdd(&succ[u], 0);
-      pe = cp.has_prior ? peff_dev(n, s, cp.k, prior_a[u], prior_b[u]) : peff_dev(n, s, cp.k, cp.a0, cp.b0);
+      pe = peff_call(n, s, cp.k, cp.has_prior ? prior_a[u] : cp.a0, cp.has_prior ? prior_b[u] : cp.b0);
       bool mixed = (s >= 1) && (n - s >= 1);
       if (mixed && n >= cp.commit_min) code = SARA_COMMIT;
       else if (n >= cp.k) code = SARA_ABANDON;
@@ -200,7 +224,7 @@ __global__ __launch_bounds__(kCtlThreads) void k_decide(Ctl* __restrict__ ctl, c
       } else {
         int j0 = n_iss[u];
         const double qi = (cp.mode == SARA_MODE_SARA_THOMPSON)
-            ? thompson_index(cp, u, n, s, cp.has_prior ? prior_a[u] : cp.a0, cp.has_prior ? prior_b[u] : cp.b0)
+            ? thompson_index(cpp, u, n, s, cp.has_prior ? prior_a[u] : cp.a0, cp.has_prior ? prior_b[u] : cp.b0)
             : pe;
         for (int e = 0; e < more; ++e)
           queue[s_qlen + exm + e] = queue_key(qi, cp.bits, u, j0 + e);
@@ -229,14 +253,15 @@ __global__ __launch_bounds__(kCtlThreads) void k_decide(Ctl* __restrict__ ctl, c
 // ---------------------------------------------------------------------------
 // refill: draws, priority sort, slot assignment, active list, done flag
 // ---------------------------------------------------------------------------
-__global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, const CtlParams* __restrict__ cpp,
-    int32_t* __restrict__ status, int32_t* __restrict__ n_iss, int32_t* __restrict__ infl,
-    double* __restrict__ peff, int32_t* __restrict__ slot_uid, int32_t* __restrict__ slot_j,
-    int32_t* __restrict__ slot_gen, uint64_t* __restrict__ slot_hash,
-    int32_t* __restrict__ active, uint64_t* __restrict__ queue,
-    int64_t* __restrict__ log_draw, int64_t* __restrict__ log_asg, const double* __restrict__ prior_p,
-    const double* __restrict__ prior_a, const double* __restrict__ prior_b) {
-  __shared__ int buf[kCtlThreads];
+__device__ __forceinline__ void refill(const CtlState& st, int* buf) {
+  Ctl* ctl = st.ctl;
+  const CtlParams* cpp = st.cpp;
+  int32_t *status = st.status, *n_iss = st.n_iss, *infl = st.infl;
+  double* peff = st.peff;
+  int32_t *slot_uid = st.slot_uid, *slot_j = st.slot_j;
+  uint64_t* queue = st.queue;
+  int64_t *log_draw = st.log_draw, *log_asg = st.log_asg;
+  const double *prior_p = st.prior_p, *prior_a = st.prior_a, *prior_b = st.prior_b;
   __shared__ uint64_t qs[kMaxQueue];
   __shared__ int freel[kMaxSlots];
   __shared__ unsigned char occ[kMaxSlots];
@@ -292,7 +317,7 @@ __global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, c
       int q = e - s_qlen;
       const int uq = nu0 + q / cp.n0;
       const double qi = (cp.mode == SARA_MODE_SARA_THOMPSON)
-          ? thompson_index(cp, uq, 0, 0, cp.has_prior ? prior_a[uq] : cp.a0, cp.has_prior ? prior_b[uq] : cp.b0)
+          ? thompson_index(cpp, uq, 0, 0, cp.has_prior ? prior_a[uq] : cp.a0, cp.has_prior ? prior_b[uq] : cp.b0)
           : (cp.has_prior ? prior_p[uq] : cp.prior);
       key = queue_key(qi, cp.bits, uq, q % cp.n0);
     }
@@ -336,8 +361,9 @@ __global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, c
     occ[s] = 1;
     slot_uid[s] = u;
     slot_j[s] = j;
-    slot_gen[s] = 0;
-    slot_hash[s] = reward_hash_init(cp.seed, cp.step, u);
+    st.slot_gen[s] = 0;
+    st.slot_tok[s] = st.tok[st.off[u + 1] - 1];   // the prompt's last token is the first decode input
+    st.slot_hash[s] = reward_hash_init(cp.seed, cp.step, u);
     int64_t* la = log_asg + (asg_base + e) * 4;
     la[0] = tnext; la[1] = s; la[2] = u; la[3] = j;
   }
@@ -353,7 +379,10 @@ __global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, c
     int f = (s < cp.S && occ[s]) ? 1 : 0;
     int tot;
     int ex = block_scan_excl(f, buf, tot);
-    if (f) active[s_M + ex] = s;
+    if (f) {
+      const int u = slot_uid[s];
+      st.active[s_M + ex] = ActiveRow{s, u, slot_j[s], st.off[u + 1] - st.off[u] - 1};
+    }
     __syncthreads();
     if (tid == 0) s_M += tot;
     __syncthreads();
@@ -372,6 +401,24 @@ __global__ __launch_bounds__(kCtlThreads) void k_refill(Ctl* __restrict__ ctl, c
     ctl->t = tnext;
     ctl->dirty = 0;
   }
+}
+
+__global__ __launch_bounds__(kCtlThreads) void k_decide(CtlState st) {
+  __shared__ int buf[kCtlThreads];
+  decide(st, buf);
+}
+__global__ __launch_bounds__(kCtlThreads) void k_refill(CtlState st) {
+  __shared__ int buf[kCtlThreads];
+  refill(st, buf);
+}
+// both phases in one launch, as the captured loop runs them (a launch less a
+// step: 1.7 us)
+__global__ __launch_bounds__(kCtlThreads) void k_decide_refill(CtlState st) {
+  __shared__ int buf[kCtlThreads];
+  decide(st, buf);
+  __threadfence_block();
+  __syncthreads();
+  refill(st, buf);
 }
 
 // ---------------------------------------------------------------------------
@@ -511,17 +558,24 @@ int launch_reset(sara_ctx* c) {
   return SARA_OK;
 }
 
+static CtlState ctl_state(const sara_ctx* c) {
+  return CtlState{c->ctl, c->cp_dev, c->status, c->n_iss, c->n_done, c->succ, c->infl, c->peff, c->slot_uid, c->slot_j,
+                  c->slot_gen, c->slot_tok, c->slot_hash, c->fin, c->r_len, c->r_reward, c->active, c->queue,
+                  c->log_dec, c->log_draw, c->log_asg, c->log_fin, c->prior_p, c->prior_a, c->prior_b, c->tok, c->off};
+}
+
 int launch_decide(sara_ctx* c) {
-  hipLaunchKernelGGL(k_decide, dim3(1), dim3(kCtlThreads), 0, c->stream, c->ctl, c->cp_dev, c->status,
-                     c->n_iss, c->n_done, c->succ, c->infl, c->peff, c->slot_uid, c->slot_j, c->fin,
-                     c->r_len, c->r_reward, c->queue, c->log_dec, c->log_fin, c->prior_a, c->prior_b);
+  hipLaunchKernelGGL(k_decide, dim3(1), dim3(kCtlThreads), 0, c->stream, ctl_state(c));
   return SARA_OK;
 }
 
 int launch_refill(sara_ctx* c) {
-  hipLaunchKernelGGL(k_refill, dim3(1), dim3(kCtlThreads), 0, c->stream, c->ctl, c->cp_dev, c->status,
-                     c->n_iss, c->infl, c->peff, c->slot_uid, c->slot_j, c->slot_gen, c->slot_hash,
-                     c->active, c->queue, c->log_draw, c->log_asg, c->prior_p, c->prior_a, c->prior_b);
+  hipLaunchKernelGGL(k_refill, dim3(1), dim3(kCtlThreads), 0, c->stream, ctl_state(c));
+  return SARA_OK;
+}
+
+int launch_decide_refill(sara_ctx* c) {
+  hipLaunchKernelGGL(k_decide_refill, dim3(1), dim3(kCtlThreads), 0, c->stream, ctl_state(c));
   return SARA_OK;
 }
 

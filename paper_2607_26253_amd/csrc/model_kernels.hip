@@ -44,6 +44,24 @@ template <typename T>
 __device__ __forceinline__ size_t x_index(int64_t i, int64_t k, int64_t K) {
   return sizeof(T) == 2 ? (size_t)tiled_index(i, k, K) : (size_t)(i * K + k);
 }
+// 8 consecutive stored values (16-byte aligned) as fp32, and back
+__device__ __forceinline__ void load8(const float* p, float (&e)[8]) {
+  const f32x4 a = *(const f32x4*)p, b = *(const f32x4*)(p + 4);
+#pragma unroll
+  for (int q = 0; q < 4; ++q) { e[q] = a[q]; e[q + 4] = b[q]; }
+}
+__device__ __forceinline__ void load8(const uint16_t* p, float (&e)[8]) {
+  const u32x4 a = *(const u32x4*)p;
+#pragma unroll
+  for (int q = 0; q < 4; ++q) { e[2 * q] = __uint_as_float(a[q] << 16); e[2 * q + 1] = __uint_as_float(a[q] & 0xFFFF0000u); }
+}
+__device__ __forceinline__ void store8(float* p, float a, float b, float c, float d, float e, float f, float g, float h) {
+  *(f32x4*)p = f32x4{a, b, c, d};
+  *(f32x4*)(p + 4) = f32x4{e, f, g, h};
+}
+__device__ __forceinline__ void store8(uint16_t* p, float a, float b, float c, float d, float e, float f, float g, float h) {
+  *(u32x4*)p = u32x4{pack_bf16(a, b), pack_bf16(c, d), pack_bf16(e, f), pack_bf16(g, h)};
+}
 // sum over a 256-thread block; every thread gets the result
 __device__ float block_sum256(float v, float* red) {
   v = wave_sum(v);
@@ -125,95 +143,115 @@ struct SampleArgs {
 // embedding gather + first RMSNorm (decode and prefill rows)
 // ---------------------------------------------------------------------------
 // Decode rows + embedding gather + first RMSNorm in one launch: row i of the
-// batch is occupied slot active[i]; the device row count goes to rows_M.
+// batch is occupied slot active[i]; the device row count goes to rows_M.  A
+// row costs three dependent loads: its slot, the slot's count and input token,
+// the embedding row; a thread takes 8 features at a time and keeps them in
+// registers between the sum of squares and the norm.  The last block lists the
+// decode attention's items meanwhile.
 template <typename T>
 __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ctl,
-    const int32_t* __restrict__ active, const int32_t* __restrict__ slot_uid,
-    const int32_t* __restrict__ slot_j, const int32_t* __restrict__ slot_gen,
-    const int32_t* __restrict__ tok, const int32_t* __restrict__ off,
-    const int32_t* __restrict__ out_tok, int k, int max_new, RowDesc* __restrict__ rows,
-    int32_t* __restrict__ rows_M, int do_embed, const T* __restrict__ embed,
+    const ActiveRow* __restrict__ active, const int32_t* __restrict__ slot_gen, const int32_t* __restrict__ slot_tok,
+    int k, RowDesc* __restrict__ rows, int32_t* __restrict__ rows_M, int do_embed, const T* __restrict__ embed,
     const float* __restrict__ w, int d, float eps, float* __restrict__ h, T* __restrict__ x,
     int U, int PB, int SB, const float2* __restrict__ rope, int half, float2* __restrict__ row_rope,
     AttnItem* __restrict__ items, int32_t* __restrict__ n_items, int spg) {
   __shared__ float red[4];
-  __shared__ int scan[256];
+  __shared__ int scan[4];
   const int M = ctl->done ? 0 : ctl->M;
   if (blockIdx.x == 0 && threadIdx.x == 0) *rows_M = M;
   if (items != nullptr && blockIdx.x == gridDim.x - 1) {
     // The decode attention's work list for this step (the same for every
-    // layer): the context splits of spg pages of every row, row-major.
-    // Thread t lists rows [t * per, (t + 1) * per) at the exclusive prefix
-    // sum of the earlier threads' split counts.
-    const int per = (M + 255) / 256;
-    const int i0 = min(M, (int)threadIdx.x * per), i1 = min(M, i0 + per);
-    auto item_of = [&](int i, int cc) {
-      const int s = active[i];
-      const int u = slot_uid[s], g = slot_gen[s];
-      AttnItem it;
-      it.i = i;
-      it.c = cc;
-      it.kv0 = u * PB;
-      it.kv1 = U * PB + s * SB;
-      it.pl = off[u + 1] - off[u] - 1;    // context P + g exceeds the P - 1 prompt positions
-      it.vcnt = g + 1;
-      it.pad0 = it.pad1 = 0;
-      return it;
-    };
-    auto splits_of = [&](const AttnItem& it) {
-      const int nch = ((it.pl + 15) >> 4) + ((it.vcnt + 15) >> 4);
-      return (nch + spg - 1) / spg;
-    };
-    int cnt = 0;
-    for (int i = i0; i < i1; ++i) cnt += splits_of(item_of(i, 0));
-    scan[threadIdx.x] = cnt;
-    __syncthreads();
-    for (int o = 1; o < 256; o <<= 1) {
-      const int v = (int)threadIdx.x >= o ? scan[threadIdx.x - o] : 0;
+    // layer): the context splits of spg pages of every row, row-major.  256 rows
+    // at a time, thread t lists one at the prefix sum of the earlier ones' split
+    // counts.
+    int done = 0;
+    for (int base = 0; base < M; base += 256) {
+      const int i = base + (int)threadIdx.x;
+      AttnItem it{};
+      int ns = 0;
+      if (i < M) {
+        const ActiveRow a = active[i];
+        it.i = i;
+        it.kv0 = a.uid * PB;
+        it.kv1 = U * PB + a.slot * SB;
+        it.pl = a.plen;                     // context P + g exceeds the P - 1 prompt positions
+        it.vcnt = slot_gen[a.slot] + 1;
+        const int nch = ((it.pl + 15) >> 4) + ((it.vcnt + 15) >> 4);
+        ns = (nch + spg - 1) / spg;
+      }
+      int incl = ns;
+#pragma unroll
+      for (int o = 1; o < 64; o <<= 1) {
+        const int v = __shfl_up(incl, o, 64);
+        if ((int)(threadIdx.x & 63) >= o) incl += v;
+      }
+      if ((threadIdx.x & 63) == 63) scan[threadIdx.x >> 6] = incl;
       __syncthreads();
-      scan[threadIdx.x] += v;
-      __syncthreads();
-    }
-    int at = scan[threadIdx.x] - cnt;
-    for (int i = i0; i < i1; ++i) {
-      AttnItem it = item_of(i, 0);
-      const int ns = splits_of(it);
+      int at = done + incl - ns, total = 0;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        if (q < (int)(threadIdx.x >> 6)) at += scan[q];
+        total += scan[q];
+      }
       for (int cc = 0; cc < ns; ++cc) {
         it.c = cc;
         items[at++] = it;
       }
+      done += total;
+      __syncthreads();   // scan[] is reused by the next rows
     }
-    if (threadIdx.x == 255) *n_items = scan[255];
+    if (threadIdx.x == 0) *n_items = done;
   }
+  constexpr int VPT = 2;                    // 8-feature groups a thread takes: d <= 4096 in registers
   for (int i = blockIdx.x; i < M; i += gridDim.x) {
-    const int s = active[i];
-    const int u = slot_uid[s], j = slot_j[s], g = slot_gen[s];
-    const int P = off[u + 1] - off[u];
-    const int rid = u * k + j;
+    const ActiveRow a = active[i];
+    const int g = slot_gen[a.slot], tok = slot_tok[a.slot];
     RowDesc r;
-    r.tok = (g == 0) ? tok[off[u] + P - 1] : out_tok[(size_t)rid * max_new + g - 1];
-    r.pos = P - 1 + g;
-    r.plen = P - 1;
-    r.slot = s;
-    r.rid = rid;
+    r.tok = tok;
+    r.pos = a.plen + g;
+    r.plen = a.plen;
+    r.slot = a.slot;
+    r.rid = a.uid * k + a.j;
     r.gen = g;
-    r.uid = u;
-    r.kv0 = u * PB;
-    r.kv1 = U * PB + s * SB;
+    r.uid = a.uid;
+    r.kv0 = a.uid * PB;
+    r.kv1 = U * PB + a.slot * SB;
     if (threadIdx.x == 0) rows[i] = r;
     // rotation angles of this row's position, read by every layer's q|k|v kernel
     for (int e = threadIdx.x; e < half; e += 256) row_rope[(size_t)i * half + e] = rope[(size_t)r.pos * half + e];
     if (!do_embed) continue;
+    const T* er = embed + (size_t)tok * d;
+    float* hr = h + (size_t)i * d;
+    float v[VPT][8];
     float ss = 0.f;
-    for (int cc = threadIdx.x; cc < d; cc += 256) {
-      float v = ld_f32(embed, (size_t)r.tok * d + cc);
-      h[(size_t)i * d + cc] = v;
-      ss += v * v;
+    // groups past VPT (fp32 models wider than 4096) are read again below
+    for (int u = 0, c = 8 * (int)threadIdx.x; c < d; ++u, c += 2048) {
+      float e[8];
+      load8(er + c, e);
+#pragma unroll
+      for (int q = 0; q < 8; ++q) ss += e[q] * e[q];
+#pragma unroll
+      for (int t = 0; t < VPT; ++t)
+        if (u == t)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) v[t][q] = e[q];
     }
     float tot = block_sum256(ss, red);
     float inv = 1.0f / sqrtf(tot / (float)d + eps);
-    for (int cc = threadIdx.x; cc < d; cc += 256)
-      st_f32(x, x_index<T>(i, cc, d), h[(size_t)i * d + cc] * inv * w[cc]);
+    for (int u = 0, c = 8 * (int)threadIdx.x; c < d; ++u, c += 2048) {
+      float e[8];
+      if (u >= VPT) load8(er + c, e);
+#pragma unroll
+      for (int t = 0; t < VPT; ++t)
+        if (u == t)
+#pragma unroll
+          for (int q = 0; q < 8; ++q) e[q] = v[t][q];
+      *(f32x4*)(hr + c) = f32x4{e[0], e[1], e[2], e[3]};
+      *(f32x4*)(hr + c + 4) = f32x4{e[4], e[5], e[6], e[7]};
+      const f32x4 w0 = *(const f32x4*)(w + c), w1 = *(const f32x4*)(w + c + 4);
+      store8(x + x_index<T>(i, c, d), e[0] * inv * w0[0], e[1] * inv * w0[1], e[2] * inv * w0[2], e[3] * inv * w0[3],
+             e[4] * inv * w1[0], e[5] * inv * w1[1], e[6] * inv * w1[2], e[7] * inv * w1[3]);
+    }
     __syncthreads();   // red[] is reused by the next row
   }
 }
@@ -1905,8 +1943,8 @@ __global__ __launch_bounds__(256) void k_sample_final(const Ctl* __restrict__ ct
     const int32_t* __restrict__ bidx, int nchunks, int cstride, int rstride, const int32_t* __restrict__ forced,
     const int32_t* __restrict__ flen, int model_free, const CtlParams* __restrict__ cpp,
     const double* __restrict__ p, int32_t* __restrict__ out_tok, int32_t* __restrict__ samp_tok,
-    int32_t* __restrict__ slot_gen, uint64_t* __restrict__ slot_hash, int32_t* __restrict__ fin,
-    int32_t* __restrict__ r_len, int32_t* __restrict__ r_reward) {
+    int32_t* __restrict__ slot_gen, int32_t* __restrict__ slot_tok, uint64_t* __restrict__ slot_hash,
+    int32_t* __restrict__ fin, int32_t* __restrict__ r_len, int32_t* __restrict__ r_reward) {
   __shared__ float sb[256];
   __shared__ int si[256];
   const int M = ctl->done ? 0 : ctl->M;
@@ -1954,6 +1992,7 @@ __global__ __launch_bounds__(256) void k_sample_final(const Ctl* __restrict__ ct
       uint64_t hsh = mix64(slot_hash[s] ^ (uint64_t)(uint32_t)(tok + 1));
       slot_hash[s] = hsh;
       slot_gen[s] = gen + 1;
+      slot_tok[s] = tok;
       if (done) {
         r_len[rid] = gen + 1;
         double u = (double)(hsh >> 11) * 0x1p-53;
@@ -2329,19 +2368,14 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
   const int S = c->S;
   PROF_B(c);
   const int eg = std::min(S, 512);
-  if (c->md.dtype == SARA_BF16)
-    launch_k(c, st, k_decode_embed<uint16_t>, dim3(eg), dim3(256), 0, c->ctl, c->active, c->slot_uid,
-                       c->slot_j, c->slot_gen, c->tok, c->off, c->out_tok, c->k, c->ad.max_new, c->rows,
-                       c->rows_M, model_free ? 0 : 1, (const uint16_t*)c->embed, c->norms, c->d,
-                       c->md.rms_eps, c->h, (uint16_t*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2,
-                       c->row_rope, model_free ? (AttnItem*)nullptr : c->attn_items, c->attn_nitems,
-                       kDecPages);
-  else
-    launch_k(c, st, k_decode_embed<float>, dim3(eg), dim3(256), 0, c->ctl, c->active, c->slot_uid,
-                       c->slot_j, c->slot_gen, c->tok, c->off, c->out_tok, c->k, c->ad.max_new, c->rows,
-                       c->rows_M, model_free ? 0 : 1, (const float*)c->embed, c->norms, c->d,
-                       c->md.rms_eps, c->h, (float*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2,
-                       c->row_rope, (AttnItem*)nullptr, c->attn_nitems, kDecPages);
+#define SARA_EMBED(T_, items_)                                                                                    \
+  launch_k(c, st, k_decode_embed<T_>, dim3(eg), dim3(256), 0, c->ctl, (const ActiveRow*)c->active, c->slot_gen,      \
+           c->slot_tok, c->k, c->rows, c->rows_M, model_free ? 0 : 1, (const T_*)c->embed, c->norms, c->d,           \
+           c->md.rms_eps, c->h, (T_*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2, c->row_rope, items_, c->attn_nitems, \
+           kDecPages)
+  if (c->md.dtype == SARA_BF16) SARA_EMBED(uint16_t, model_free ? (AttnItem*)nullptr : c->attn_items);
+  else SARA_EMBED(float, (AttnItem*)nullptr);
+#undef SARA_EMBED
   PROF_E(c, kPEmbed, c->d, 0);
   int nchunks = kSampleChunks;
   if (!model_free) {
@@ -2397,7 +2431,7 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
   launch_k(c, st, k_sample_final, dim3(std::min(S, 1024)), dim3(256), 0, c->ctl, c->rows,
                      c->samp_best, c->samp_idx, nchunks, fused ? S : 1, fused ? 1 : nchunks, forced, c->flen,
                      model_free,
-                     (const CtlParams*)c->cp_dev, c->p, c->out_tok, c->samp_tok, c->slot_gen, c->slot_hash, c->fin,
+                     (const CtlParams*)c->cp_dev, c->p, c->out_tok, c->samp_tok, c->slot_gen, c->slot_tok, c->slot_hash, c->fin,
                      c->r_len, c->r_reward);
   PROF_E(c, kPSampleF, 0, 0);
   return SARA_OK;

@@ -297,7 +297,8 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->slot_gen, sizeof(int32_t) * c->S);
   ALLOC(c->fin, sizeof(int32_t) * c->S);
   ALLOC(c->slot_hash, sizeof(uint64_t) * c->S);
-  ALLOC(c->active, sizeof(int32_t) * c->S);
+  ALLOC(c->active, sizeof(ActiveRow) * c->S);
+  ALLOC(c->slot_tok, sizeof(int32_t) * c->S);
   ALLOC(c->queue, sizeof(uint64_t) * std::max(1, c->Qcap));
   const size_t nroll = (size_t)c->U * c->k;
   ALLOC(c->out_tok, sizeof(int32_t) * nroll * ad->max_new);
@@ -570,8 +571,7 @@ static int build_graph(sara_ctx* c, const int32_t* forced, int iters) {
   c->prof_active = false;
   for (int i = 0; i < iters; ++i) {
     launch_decode(c, forced, nullptr, 0);
-    launch_decide(c);
-    launch_refill(c);
+    launch_decide_refill(c);
   }
   c->capturing = false;
   HIP_TRY(hipStreamEndCapture(c->stream, &c->graph), "end capture");

@@ -62,6 +62,12 @@ struct RowDesc {
   int32_t kv1;
 };
 
+// An occupied slot, ascending (rebuilt by the refill when slots change): what
+// a decode step needs of it besides its generated count and next input token.
+struct ActiveRow {
+  int32_t slot, uid, j, plen;   // plen: tokens of the shared prompt segment (P - 1)
+};
+
 // One work item of the decode attention: context split c of decode row i,
 // with the row's page extents and segment lengths, so that an attention
 // block needs no further load before its page loads.
@@ -149,7 +155,8 @@ struct sara_ctx {
   bool warm_step = false;         // the current step began with warm start set
   int32_t *slot_uid = nullptr, *slot_j = nullptr, *slot_gen = nullptr, *fin = nullptr;
   uint64_t* slot_hash = nullptr;
-  int32_t* active = nullptr;
+  sara::ActiveRow* active = nullptr;
+  int32_t* slot_tok = nullptr;    // input token of the slot's next decode step
   uint64_t* queue = nullptr;
   int32_t *out_tok = nullptr, *samp_tok = nullptr, *r_len = nullptr, *r_reward = nullptr;
   int64_t *log_dec = nullptr, *log_draw = nullptr, *log_asg = nullptr, *log_fin = nullptr;
@@ -257,6 +264,7 @@ int launch_decide(sara_ctx* c);
 int launch_warm_priors(sara_ctx* c);
 int launch_warm_update(sara_ctx* c, double lambda);
 int launch_refill(sara_ctx* c);
+int launch_decide_refill(sara_ctx* c);
 int launch_finish(sara_ctx* c, float eps);
 int launch_peff(const double* alpha, const double* beta, const int32_t* n, const int32_t* s, int k, int count,
                 double* out, hipStream_t st);
