@@ -117,6 +117,8 @@ struct CtlState {
   uint64_t* slot_hash;
   int32_t *fin, *r_len, *r_reward;
   ActiveRow* active;
+  PromptPlace* places;           // null: no prompt order wanted
+  int32_t *grp_n, *grp_at;
   uint64_t* queue;
   int64_t *log_dec, *log_draw, *log_asg, *log_fin;
   const double *prior_p, *prior_a, *prior_b;
@@ -253,6 +255,45 @@ __device__ __forceinline__ void decide(const CtlState& st, int* buf) {
 // ---------------------------------------------------------------------------
 // refill: draws, priority sort, slot assignment, active list, done flag
 // ---------------------------------------------------------------------------
+// The live rows by prompt.  Ranks within a prompt come from atomics in any
+// order: they only choose which rows share an attention block, and in which
+// MFMA column, neither of which a row's result depends on.
+__device__ __forceinline__ void order_by_prompt(const CtlState& st, int M, int* buf) {
+  constexpr int R = kMaxSlots / kCtlThreads;
+  const int tid = threadIdx.x;
+  int uid[R], rank[R];
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    const int e = tid + j * kCtlThreads;
+    uid[j] = e < M ? st.active[e].uid : -1;
+    rank[j] = -1;
+    if (uid[j] >= 0) atomicExch(&st.grp_n[uid[j]], 0);
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+    if (uid[j] >= 0) rank[j] = atomicAdd(&st.grp_n[uid[j]], 1);
+  __syncthreads();
+  int n[R], base = 0;
+#pragma unroll
+  for (int j = 0; j < R; ++j) {
+    n[j] = uid[j] >= 0 ? atomicAdd(&st.grp_n[uid[j]], 0) : 0;
+    if (j * kCtlThreads < M) {                           // uniform
+      int tot;
+      const int at = base + block_scan_excl(rank[j] == 0 ? n[j] : 0, buf, tot);
+      if (rank[j] == 0) atomicExch(&st.grp_at[uid[j]], at);
+      base += tot;
+    }
+  }
+  __syncthreads();
+#pragma unroll
+  for (int j = 0; j < R; ++j)
+    if (uid[j] >= 0) {
+      const int at = atomicAdd(&st.grp_at[uid[j]], 0) + rank[j];
+      st.places[at] = PromptPlace{(uint16_t)(tid + j * kCtlThreads), (uint16_t)rank[j], n[j]};
+    }
+}
+
 __device__ __forceinline__ void refill(const CtlState& st, int* buf) {
   Ctl* ctl = st.ctl;
   const CtlParams* cpp = st.cpp;
@@ -387,6 +428,7 @@ __device__ __forceinline__ void refill(const CtlState& st, int* buf) {
     if (tid == 0) s_M += tot;
     __syncthreads();
   }
+  if (st.places) order_by_prompt(st, s_M, buf);
   if (tid == 0) {
     ctl->next_uid = nu0 + d;
     ctl->nA += d;
@@ -560,7 +602,8 @@ int launch_reset(sara_ctx* c) {
 
 static CtlState ctl_state(const sara_ctx* c) {
   return CtlState{c->ctl, c->cp_dev, c->status, c->n_iss, c->n_done, c->succ, c->infl, c->peff, c->slot_uid, c->slot_j,
-                  c->slot_gen, c->slot_tok, c->slot_hash, c->fin, c->r_len, c->r_reward, c->active, c->queue,
+                  c->slot_gen, c->slot_tok, c->slot_hash, c->fin, c->r_len, c->r_reward, c->active, c->places,
+                  c->grp_n, c->grp_at, c->queue,
                   c->log_dec, c->log_draw, c->log_asg, c->log_fin, c->prior_p, c->prior_a, c->prior_b, c->tok, c->off};
 }
 

@@ -142,6 +142,17 @@ struct SampleArgs {
 // ---------------------------------------------------------------------------
 // embedding gather + first RMSNorm (decode and prefill rows)
 // ---------------------------------------------------------------------------
+// sum of v over a 256-thread block (buf: 4 ints; ends with a barrier)
+__device__ __forceinline__ int block_count256(int v, int* buf) {
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o, 64);
+  if ((threadIdx.x & 63) == 0) buf[threadIdx.x >> 6] = v;
+  __syncthreads();
+  const int r = (buf[0] + buf[1]) + (buf[2] + buf[3]);
+  __syncthreads();
+  return r;
+}
+
 // Decode rows + embedding gather + first RMSNorm in one launch: row i of the
 // batch is occupied slot active[i]; the device row count goes to rows_M.  A
 // row costs three dependent loads: its slot, the slot's count and input token,
@@ -154,32 +165,59 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
     int k, RowDesc* __restrict__ rows, int32_t* __restrict__ rows_M, int do_embed, const T* __restrict__ embed,
     const float* __restrict__ w, int d, float eps, float* __restrict__ h, T* __restrict__ x,
     int U, int PB, int SB, const float2* __restrict__ rope, int half, float2* __restrict__ row_rope,
-    AttnItem* __restrict__ items, int32_t* __restrict__ n_items, int spg) {
+    AttnItem* __restrict__ items, int32_t* __restrict__ n_items, int spg, const PromptPlace* __restrict__ places,
+    int hkv, int rows_per_item, int resident) {
   __shared__ float red[4];
   __shared__ int scan[4];
   const int M = ctl->done ? 0 : ctl->M;
   if (blockIdx.x == 0 && threadIdx.x == 0) *rows_M = M;
   if (items != nullptr && blockIdx.x == gridDim.x - 1) {
     // The decode attention's work list for this step (the same for every
-    // layer): the context splits of spg pages of every row, row-major.  256 rows
-    // at a time, thread t lists one at the prefix sum of the earlier ones' split
-    // counts.
+    // layer): the context splits of spg pages of every row.  256 rows at a
+    // time, thread t lists one at the prefix sum of the earlier ones' counts.
+    // As long as all items are resident at once (items x hkv <= resident), each
+    // row has its own, row-major.  Beyond that K and V traffic counts, not
+    // latency, and rows of one prompt share the items of the splits that lie
+    // wholly in its prompt pages, up to rows_per_item rows each, in prompt
+    // order; the splits and so the results are the same.
     int done = 0;
+    bool shared = M > 256;
     for (int base = 0; base < M; base += 256) {
-      const int i = base + (int)threadIdx.x;
+      const int j = base + (int)threadIdx.x;
       AttnItem it{};
-      int ns = 0;
-      if (i < M) {
+      int first = 0, ns = 0, lead = 0;      // own splits [first, ns), shared splits [0, lead) that it lists
+      auto row_item = [&](int i) {
         const ActiveRow a = active[i];
         it.i = i;
+        it.n = 1;
         it.kv0 = a.uid * PB;
         it.kv1 = U * PB + a.slot * SB;
         it.pl = a.plen;                     // context P + g exceeds the P - 1 prompt positions
         it.vcnt = slot_gen[a.slot] + 1;
         const int nch = ((it.pl + 15) >> 4) + ((it.vcnt + 15) >> 4);
         ns = (nch + spg - 1) / spg;
+      };
+      if (!shared) {
+        if (j < M) row_item(j);
+        // M <= 256: the whole batch's item count
+        const int all = block_count256(ns, scan);
+        shared = all * hkv > resident;
       }
-      int incl = ns;
+      int members = 1;
+      if (shared) {
+        ns = 0;
+        if (j < M) {
+          const PromptPlace p = places[j];
+          row_item(p.row);
+          const int at = p.rank % rows_per_item;
+          members = min(rows_per_item, p.n - ((int)p.rank - at));
+          if (members > 1) {
+            first = ((it.pl + 15) >> 4) / spg;
+            if (at == 0) lead = first;
+          }
+        }
+      }
+      int incl = ns - first + lead;
 #pragma unroll
       for (int o = 1; o < 64; o <<= 1) {
         const int v = __shfl_up(incl, o, 64);
@@ -187,13 +225,20 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
       }
       if ((threadIdx.x & 63) == 63) scan[threadIdx.x >> 6] = incl;
       __syncthreads();
-      int at = done + incl - ns, total = 0;
+      int at = done + incl - (ns - first + lead), total = 0;
 #pragma unroll
       for (int q = 0; q < 4; ++q) {
         if (q < (int)(threadIdx.x >> 6)) at += scan[q];
         total += scan[q];
       }
-      for (int cc = 0; cc < ns; ++cc) {
+      AttnItem sh = it;
+      sh.i = j;
+      sh.n = members;
+      for (int cc = 0; cc < lead; ++cc) {
+        sh.c = cc;
+        items[at++] = sh;
+      }
+      for (int cc = first; cc < ns; ++cc) {
         it.c = cc;
         items[at++] = it;
       }
@@ -1366,56 +1411,69 @@ __global__ __launch_bounds__(256) void k_qkv_rope(const uint16_t* __restrict__ X
 // q|k|v kernel has already rotated q and appended this position's k and v).
 // Work item = (entry e of the step's work list, KV head g): entry e names a
 // row and one of its context splits of kDecPages pages; wave w owns pages
-// w, w + 4, .. of the split, all K and V loads issued before any compute, so
+// w and w + 4 of the split, all K and V loads issued before any compute, so
 // a split costs one HBM round trip.  The entry carries the row's two KV
 // extents (kv0 + e: shared prompt pages, kv1 + e: private pages), so the
-// page loads wait on that one load only; the grid is the number of blocks
-// that are resident at once, so up to that many items all run in one
-// round.  Per page (16 tokens):
-//   S^T = K q^T  (v_mfma_f32_16x16x32_bf16; G <= 8 query heads padded to 16;
-//                 lane (token l%16, k-group l/16) of K meets head l%16 of q
-//                 over the same HD/4 dims, so the k order inside the MFMA is moot)
-//   online softmax per head over the 4 lanes holding its 16 scores
-//   O += P V     (v_mfma_f32_16x16x16bf16_1k; the score registers already
-//                 have the A-operand layout and transposed V pages give the
-//                 B operand; P enters as a bf16 hi + lo pair, so the product
+// page loads wait on that one load only, and a block's next entry is loaded
+// while it computes; the grid is the number of blocks that are resident at
+// once, so up to that many items all run in one round.  Per wave, its two
+// pages (32 tokens) at once:
+//   S^T = K q^T  (v_mfma_f32_16x16x32_bf16; G <= 8 query heads a row, 16
+//                 columns; lane (token l%16, k-group l/16) of K meets column l%16
+//                 of q over the same HD/4 dims, so the k order inside the MFMA is moot)
+//   softmax per column in base 2 over the 4 lanes holding its 32 scores
+//   O^T = V^T P^T (the score registers already have the B-operand layout, four
+//                 tokens of each page a lane, and transposed V pages give the A
+//                 operand; P enters as a bf16 hi + lo pair, so the product
 //                 keeps fp32 accuracy without a bf16 rounding point)
-// The 4 waves' (max, sum, O) merge in LDS.  A row with a single split writes
-// its normalised output to `out` ([row][hq][HD], bf16); other rows leave a
-// partial per split for k_attn_combine.
+// An entry of n > 1 rows (at most 16 / G) is a split of whole prompt pages that
+// the rows share: G columns each; a column's arithmetic is the same wherever it
+// stands.  The 4 waves' (max, sum, O) merge in LDS, four consecutive dims of a
+// column a thread, its four weights computed once.  A row with a single split
+// writes its normalised output to `out` ([row][hq][HD], bf16); other rows leave
+// a partial per split for k_attn_combine.
+// With many rows it is bound by the vector unit, with few by its load round
+// trips.  512 rows of 16 heads at contexts near 660: 37 us, where masks, two
+// softmax steps and natural exponentials per merged element took 59 (and 61
+// with the prompts' rows sharing items); 32 rows at contexts near 3,800: 14.4
+// against 21.9 us; 32 rows near 350: 6.3 against 6.8.
 template <int HD>
 __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict__ items,
-    const int32_t* __restrict__ n_items, int cap, const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
+    const int32_t* __restrict__ n_items, const PromptPlace* __restrict__ places, int cap,
+    const uint16_t* __restrict__ kc, const uint16_t* __restrict__ vc,
     int layer, int64_t n_blocks, int hq, int hkv, int n_splits, float scale,
     const uint16_t* __restrict__ qb, float* __restrict__ part, uint16_t* __restrict__ out) {
-  typedef short short4_ __attribute__((ext_vector_type(4)));
   typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
-  constexpr int DPL = HD / 4, NCC = HD / 32, NT = HD / 16, PPW = kDecPpw, SPG = kDecPages;
+  constexpr int DPL = HD / 4, NCC = HD / 32, NT = HD / 16, SPG = kDecPages;
+  static_assert(kDecPpw == 2, "a wave takes two pages of a split");
+  constexpr int PITCH = HD + 4;
+  constexpr int TPC = HD / 4, CPP = 256 / TPC;              // merge: threads per column, columns per pass
   __shared__ float m_w[4][16], l_w[4][16];
-  __shared__ float o_w[4][16][HD + 1];
+  __shared__ __attribute__((aligned(16))) float o_w[4][16][PITCH];
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int row = lane & 15, grp = lane >> 4;
   const int G = hq / hkv;
-  for (int item = blockIdx.x; item < cap * hkv; item += gridDim.x) {
-    // the list length and the entry are loaded together (the loop bound
-    // keeps the entry index below the list's capacity)
-    const int n = *n_items;
-    const int4 e0 = *(const int4*)&items[item / hkv].i;
-    const int2 e1 = *(const int2*)&items[item / hkv].pl;
-    if (item >= n * hkv) break;
-    const int i = e0.x, c = e0.y, g = item % hkv;
-    // q operand (head `row` of this KV group, zero beyond G): independent of
-    // the row descriptor, loaded first
+  const int cr = row / G, chd = row - cr * G;               // this column's row within the item, and head
+  const float sl2 = scale * 1.4426950408889634f;
+  // the list length and the first entry are loaded together (the entry index
+  // stays below the list's capacity); every later entry an item ahead
+  const int n = *n_items;
+  int item = blockIdx.x;
+  if (item >= cap * hkv) return;
+  int4 e0 = *(const int4*)&items[item / hkv].i, e1 = *(const int4*)&items[item / hkv].pl;
+  while (item < n * hkv) {
+    const int next = item + gridDim.x, ni = min(next / hkv, cap - 1);
+    const int4 f0 = *(const int4*)&items[ni].i, f1 = *(const int4*)&items[ni].pl;
+    const int c = e0.y, g = item % hkv, nr = e1.z;
+    // row r of the item (a single row's item names it directly)
+    auto row_of = [&](int r) { return nr == 1 ? e0.x : (int)places[e0.x + r].row; };
+    // q operand: independent of anything but the entry, loaded first
+    const bool on = cr < nr;
     uint4 qv[NCC];
     {
-      const int hh = min(row, G - 1);
-      const uint4* qp = (const uint4*)(qb + ((size_t)i * hq + g * G + hh) * HD + DPL * grp);
+      const uint4* qp = (const uint4*)(qb + ((size_t)row_of(on ? cr : 0) * hq + g * G + chd) * HD + DPL * grp);
 #pragma unroll
       for (int cc = 0; cc < NCC; ++cc) qv[cc] = qp[cc];
-      if (row >= G) {
-#pragma unroll
-        for (int cc = 0; cc < NCC; ++cc) qv[cc] = make_uint4(0, 0, 0, 0);
-      }
     }
     const int kv0 = e0.z, kv1 = e0.w;
     const int pl = e1.x;                                   // prompt positions attended
@@ -1423,18 +1481,17 @@ __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict_
     const int vcnt = e1.y;                                 // private positions (>= 1)
     const int nch = pc + ((vcnt + 15) >> 4);
     const int ch0 = c * SPG;
-    if (ch0 >= nch) continue;
     const int ch1 = min(nch, ch0 + SPG);
     struct Pg { u32x4 k[NCC]; u32x2 v[NT]; int n; };
-    Pg pg[PPW];
+    Pg pg[2];
 #pragma unroll
-    for (int p = 0; p < PPW; ++p) {
+    for (int p = 0; p < 2; ++p) {
       const int ch = ch0 + wave + 4 * p;
       const int cv = (ch < ch1) ? ch : ch0;                // pages past the split re-read its first
-      int n;
-      if (cv < pc) n = min(16, pl - 16 * cv);
-      else n = min(16, vcnt - 16 * (cv - pc));
-      pg[p].n = (ch < ch1) ? n : 0;
+      int m;
+      if (cv < pc) m = min(16, pl - 16 * cv);
+      else m = min(16, vcnt - 16 * (cv - pc));
+      pg[p].n = (ch < ch1) ? m : 0;
       const int blk = (cv < pc) ? kv0 + cv : kv1 + (cv - pc);
       const size_t pgi = ((size_t)layer * n_blocks + blk) * hkv + g;
       const u32x4* kp = (const u32x4*)(kc + (pgi * kBlockTok + row) * HD + DPL * grp);
@@ -1444,95 +1501,102 @@ __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict_
 #pragma unroll
       for (int t = 0; t < NT; ++t) pg[p].v[t] = *(const u32x2*)(vp + (size_t)(16 * t + row) * kBlockTok);
     }
-    float m_run = -INFINITY, l_run = 0.f;
+    if (!on) {
+#pragma unroll
+      for (int cc = 0; cc < NCC; ++cc) qv[cc] = make_uint4(0, 0, 0, 0);
+    }
+    float mx = -INFINITY, ls = 0.f;
     f32x4 o[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) o[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+    if (pg[0].n > 0) {
+      f32x4 sc[2];
 #pragma unroll
-    for (int p = 0; p < PPW; ++p) {
-      const int n = pg[p].n;
-      if (n == 0) continue;
-      f32x4 sc = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int p = 0; p < 2; ++p) {
+        sc[p] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-      for (int cc = 0; cc < NCC; ++cc)
-        sc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pg[p].k[cc]),
-                                                     __builtin_bit_cast(bf16x8, qv[cc]), sc, 0, 0, 0);
-      // lane holds tokens 4*grp + q (q < 4) of head `row`
-      float sv[4];
-      float mt = -INFINITY;
-#pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        sv[q] = (4 * grp + q < n) ? sc[q] * scale : -INFINITY;
-        mt = fmaxf(mt, sv[q]);
+        for (int cc = 0; cc < NCC; ++cc)
+          sc[p] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, pg[p].k[cc]),
+                                                          __builtin_bit_cast(bf16x8, qv[cc]), sc[p], 0, 0, 0);
       }
-      mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
-      mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
-      const float mn = fmaxf(m_run, mt);
-      const float alpha = expf(m_run - mn);
-      float ps = 0.f;
-      uint16_t pb[4], plo[4];
+      // lane holds tokens 4*grp + q (q < 4) of both pages, column `row`; tokens
+      // beyond a page's valid ones may hold stale bits: their scores count
+      // nothing and their V is zeroed
+      if (pg[0].n + pg[1].n < 32) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float pv = expf(sv[q] - mn);
-        const uint16_t bb = f32_to_bf16(pv);
-        pb[q] = bb;
-        plo[q] = f32_to_bf16(pv - bf16_to_f32(bb));
-        ps += pv;
+        for (int p = 0; p < 2; ++p) {
+          const int left = pg[p].n - 4 * grp;               // valid tokens of this lane's four
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            if (q >= left) sc[p][q] = -INFINITY;
+          const uint32_t v0 = (left > 0 ? 0xFFFFu : 0u) | (left > 1 ? 0xFFFF0000u : 0u);
+          const uint32_t v1 = (left > 2 ? 0xFFFFu : 0u) | (left > 3 ? 0xFFFF0000u : 0u);
+#pragma unroll
+          for (int t = 0; t < NT; ++t) { pg[p].v[t].x &= v0; pg[p].v[t].y &= v1; }
+        }
       }
-      ps += __shfl_xor(ps, 16, 64);
-      ps += __shfl_xor(ps, 32, 64);
-      l_run = l_run * alpha + ps;
-      m_run = mn;
-      // rows of O are heads 4*grp + q: fetch their rescale factors
-      float al[4];
 #pragma unroll
-      for (int q = 0; q < 4; ++q) al[q] = __shfl(alpha, 4 * grp + q, 64);
-      short4_ pa, pa_lo;
+      for (int p = 0; p < 2; ++p)
+        mx = fmaxf(mx, fmaxf(fmaxf(sc[p][0], sc[p][1]), fmaxf(sc[p][2], sc[p][3])));
+      mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
+      mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+      const float mc = mx * sl2;
+      u32x4 ph, plo;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) { pa[q] = (short)pb[q]; pa_lo[q] = (short)plo[q]; }
+      for (int p = 0; p < 2; ++p)
+#pragma unroll
+        for (int q = 0; q < 4; q += 2) {
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[p][q], sl2, -mc));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[p][q + 1], sl2, -mc));
+          ls += p0 + p1;
+          const uint32_t hi = pack_bf16(p0, p1);
+          ph[2 * p + (q >> 1)] = hi;
+          plo[2 * p + (q >> 1)] = pack_bf16(p0 - __uint_as_float(hi << 16), p1 - __uint_as_float(hi & 0xFFFF0000u));
+        }
+      ls += __shfl_xor(ls, 16, 64);
+      ls += __shfl_xor(ls, 32, 64);
 #pragma unroll
       for (int t = 0; t < NT; ++t) {
-        // positions beyond the page's n valid tokens may hold stale bits: zero them
-        short4_ vb;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const uint32_t w = (q < 2) ? pg[p].v[t].x : pg[p].v[t].y;
-          const uint16_t hv = (uint16_t)((q & 1) ? (w >> 16) : (w & 0xFFFF));
-          vb[q] = (short)((4 * grp + q < n) ? hv : (uint16_t)0);
-        }
-#pragma unroll
-        for (int q = 0; q < 4; ++q) o[t][q] *= al[q];
-        o[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa, vb, o[t], 0, 0, 0);
-        o[t] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(pa_lo, vb, o[t], 0, 0, 0);
+        const u32x4 vw = {pg[0].v[t].x, pg[0].v[t].y, pg[1].v[t].x, pg[1].v[t].y};
+        const bf16x8 vf = __builtin_bit_cast(bf16x8, vw);
+        o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, ph), o[t], 0, 0, 0);
+        o[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(vf, __builtin_bit_cast(bf16x8, plo), o[t], 0, 0, 0);
       }
     }
-    // merge the 4 waves: lane `row` (grp 0) holds head row's (m, l); O rows are heads 4*grp + q
-    if (grp == 0) { m_w[wave][row] = m_run; l_w[wave][row] = l_run; }
+    // merge the 4 waves: lane (row, grp) holds dims 16 t + 4 grp ..+3 of column row
+    const int cols = nr * G;
+    if (grp == 0) { m_w[wave][row] = mx; l_w[wave][row] = ls; }
+    if (row < cols) {
 #pragma unroll
-    for (int t = 0; t < NT; ++t)
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o_w[wave][4 * grp + q][16 * t + row] = o[t][q];
+      for (int t = 0; t < NT; ++t) *(f32x4*)&o_w[wave][row][16 * t + 4 * grp] = o[t];
+    }
     __syncthreads();
-    const int ns = (nch + SPG - 1) / SPG;
-    for (int e = threadIdx.x; e < G * HD; e += 256) {
-      const int hh = e / HD, dd = e - hh * HD;
-      const float mx = fmaxf(fmaxf(m_w[0][hh], m_w[1][hh]), fmaxf(m_w[2][hh], m_w[3][hh]));
-      float num = 0.f, den = 0.f;
+    const bool single = nch <= SPG;
+    for (int col = (int)threadIdx.x / TPC; col < cols; col += CPP) {
+      const int rr = col / G, head = col - rr * G, i = row_of(rr), d4 = 4 * ((int)threadIdx.x % TPC);
+      const float m = fmaxf(fmaxf(m_w[0][col], m_w[1][col]), fmaxf(m_w[2][col], m_w[3][col]));
+      f32x4 num = {0.f, 0.f, 0.f, 0.f};
+      float den = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const float wt = (m_w[w][hh] == -INFINITY) ? 0.f : expf(m_w[w][hh] - mx);
-        num += wt * o_w[w][hh][dd];
-        den += wt * l_w[w][hh];
+        const float wt = __builtin_amdgcn_exp2f((m_w[w][col] - m) * sl2);   // 0 for a wave without pages
+        num += wt * *(const f32x4*)&o_w[w][col][d4];
+        den += wt * l_w[w][col];
       }
-      if (ns == 1) {
-        out[((size_t)i * hq + g * G + hh) * HD + dd] = f32_to_bf16(num / den);
+      if (single) {
+        *(uint2*)(out + ((size_t)i * hq + g * G + head) * HD + d4) =
+            make_uint2(pack_bf16(num[0] / den, num[1] / den), pack_bf16(num[2] / den, num[3] / den));
       } else {
-        float* dst = part + ((((size_t)i * hkv + g) * n_splits + c) * kMaxGroup + hh) * (HD + 2);
-        dst[dd] = num;
-        if (dd == 0) { dst[HD] = mx; dst[HD + 1] = den; }
+        float* dst = part + ((((size_t)i * hkv + g) * n_splits + c) * kMaxGroup + head) * (HD + 2);
+        *(float2*)(dst + d4) = make_float2(num[0], num[1]);
+        *(float2*)(dst + d4 + 2) = make_float2(num[2], num[3]);
+        if (d4 == 0) *(float2*)(dst + HD) = make_float2(m * scale, den);
       }
     }
     __syncthreads();   // LDS is reused by the next item
+    item = next;
+    e0 = f0;
+    e1 = f1;
   }
 }
 
@@ -2148,6 +2212,21 @@ static int qkv_spread(sara_ctx* c, F kernel) {
   return c->qkv_spread;
 }
 
+// blocks of the decode attention that are resident at once (every item of a
+// list that short runs in one round), computed once per context
+static int attn_resident(sara_ctx* c) {
+  if (c->attn_dec_grid == 0) {
+    int per_cu = 0, dev = 0, n_cu = 0;
+    const hipError_t e = c->hd == 128 ? hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_attn_dec<128>, 256, 0)
+                                      : hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_attn_dec<64>, 256, 0);
+    if (e != hipSuccess || hipGetDevice(&dev) != hipSuccess ||
+        hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
+      per_cu = 2, n_cu = 256;
+    c->attn_dec_grid = std::max(1, per_cu) * std::max(1, n_cu);
+  }
+  return c->attn_dec_grid;
+}
+
 // h += split-K sum of ws; x = RMSNorm(h) * w (fp32 models, bf16 prefill)
 template <typename T>
 static void residual_norm(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w) {
@@ -2212,19 +2291,10 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
 #undef SARA_QKV
     PROF_E(c, kPQkvRope, c->nqkv, d);
     PROF_B(c);
-    if (c->attn_dec_grid == 0) {
-      // blocks resident at once: every item of a list that short runs in one round
-      int per_cu = 0, dev = 0, n_cu = 0;
-      if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, k_attn_dec<HD>, 256, 0) != hipSuccess ||
-          hipGetDevice(&dev) != hipSuccess ||
-          hipDeviceGetAttribute(&n_cu, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess)
-        per_cu = 2, n_cu = 256;
-      c->attn_dec_grid = std::max(1, per_cu) * std::max(1, n_cu);
-    }
     const int cap = M_cap * c->dec_splits_max;
-    const int dg = (int)std::min<int64_t>((int64_t)cap * c->hkv, c->attn_dec_grid);
+    const int dg = (int)std::min<int64_t>((int64_t)cap * c->hkv, attn_resident(c));
     launch_k(c, st, (k_attn_dec<HD>), dim3(dg), dim3(256), 0, (const AttnItem*)c->attn_items,
-             (const int32_t*)c->attn_nitems, cap, (const uint16_t*)c->kc, (const uint16_t*)c->vc, l, c->n_blocks,
+             (const int32_t*)c->attn_nitems, (const PromptPlace*)c->places, cap, (const uint16_t*)c->kc, (const uint16_t*)c->vc, l, c->n_blocks,
              c->hq, c->hkv, c->dec_splits_max, 1.0f / sqrtf((float)HD), (const uint16_t*)c->qbuf, c->attn_part, x);
     PROF_E(c, kPAttn, 0, 0);
     PROF_B(c);
@@ -2372,7 +2442,7 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
   launch_k(c, st, k_decode_embed<T_>, dim3(eg), dim3(256), 0, c->ctl, (const ActiveRow*)c->active, c->slot_gen,      \
            c->slot_tok, c->k, c->rows, c->rows_M, model_free ? 0 : 1, (const T_*)c->embed, c->norms, c->d,           \
            c->md.rms_eps, c->h, (T_*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2, c->row_rope, items_, c->attn_nitems, \
-           kDecPages)
+           kDecPages, (const PromptPlace*)c->places, c->hkv, 16 / c->G, attn_resident(c))
   if (c->md.dtype == SARA_BF16) SARA_EMBED(uint16_t, model_free ? (AttnItem*)nullptr : c->attn_items);
   else SARA_EMBED(float, (AttnItem*)nullptr);
 #undef SARA_EMBED

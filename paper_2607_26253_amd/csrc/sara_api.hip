@@ -299,6 +299,11 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->slot_hash, sizeof(uint64_t) * c->S);
   ALLOC(c->active, sizeof(ActiveRow) * c->S);
   ALLOC(c->slot_tok, sizeof(int32_t) * c->S);
+  if (md->dtype == SARA_BF16) {
+    ALLOC(c->places, sizeof(PromptPlace) * c->S);
+    ALLOC(c->grp_n, sizeof(int32_t) * c->U);
+    ALLOC(c->grp_at, sizeof(int32_t) * c->U);
+  }
   ALLOC(c->queue, sizeof(uint64_t) * std::max(1, c->Qcap));
   const size_t nroll = (size_t)c->U * c->k;
   ALLOC(c->out_tok, sizeof(int32_t) * nroll * ad->max_new);

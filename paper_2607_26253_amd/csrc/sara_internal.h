@@ -70,10 +70,19 @@ struct ActiveRow {
 
 // One work item of the decode attention: context split c of decode row i,
 // with the row's page extents and segment lengths, so that an attention
-// block needs no further load before its page loads.
+// block needs no further load before its page loads.  n > 1: a split that lies
+// wholly in the prompt segment of n rows of one prompt, places i .. i + n - 1 of
+// the prompt order.
 struct AttnItem {
-  int32_t i, c, kv0, kv1;   // row, split, page extents (as in RowDesc)
-  int32_t pl, vcnt, pad0, pad1;  // prompt positions attended, private positions
+  int32_t i, c, kv0, kv1;   // row (or place), split, page extents (as in RowDesc)
+  int32_t pl, vcnt, n, pad; // prompt positions attended, private positions, rows
+};
+
+// One place of the live rows ordered by prompt (rebuilt with the active rows):
+// the row, its rank among the rows of its prompt, and how many those are.
+struct PromptPlace {
+  uint16_t row, rank;
+  int32_t n;
 };
 
 // Parameters every controller kernel reads.
@@ -156,6 +165,8 @@ struct sara_ctx {
   int32_t *slot_uid = nullptr, *slot_j = nullptr, *slot_gen = nullptr, *fin = nullptr;
   uint64_t* slot_hash = nullptr;
   sara::ActiveRow* active = nullptr;
+  sara::PromptPlace* places = nullptr;  // [S] live rows by prompt (bf16 models)
+  int32_t *grp_n = nullptr, *grp_at = nullptr;  // [U] live rows of a prompt, its first place
   int32_t* slot_tok = nullptr;    // input token of the slot's next decode step
   uint64_t* queue = nullptr;
   int32_t *out_tok = nullptr, *samp_tok = nullptr, *r_len = nullptr, *r_reward = nullptr;

@@ -1,0 +1,54 @@
+"""Decode attention of many rows: the rollouts of a prompt share the blocks of
+its prompt pages, and every row's logits stay bit-identical to a small batch's,
+whose rows have blocks of their own."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from tests.gpu_harness import device_setup, slot_rows, upload_pool
+from tests.test_gpu_prefill import generic_cfg
+
+pytestmark = pytest.mark.gpu
+
+
+def logits_by_rollout(cfg, w, pool, slots, forced, steps):
+    cfg["alloc"]["n_slots"] = slots
+    ctx, _ = device_setup(cfg, w)
+    d_tok, d_p, _ = upload_pool(pool)
+    ctx.sara_begin_step(d_tok, pool["offsets"], d_p, None, 0)
+    k, bufs = cfg["alloc"]["k"], []
+    for _ in range(steps):
+        buf = torch.full((slots, cfg["model"]["vocab"]), -7.0, dtype=torch.float32, device="cuda")
+        ctx.sara_decode_step(forced, buf)
+        bufs.append(buf)
+        ctx.sara_posterior_decide()
+        ctx.sara_refill()
+    asg = ctx.read_logs()["assigns"]
+    ctx.close()
+    return {(u, j): [b[s] for b in bufs] for t, s, u, j in asg if t == 0}, k
+
+
+@pytest.mark.parametrize("hq,hkv,hd,n0,prompts", [
+    (8, 1, 64, 8, 40),      # 2 rows a tile, 8 an item
+    (12, 2, 128, 8, 33),    # 6 columns a row
+    (10, 2, 64, 7, 40),     # 3 rows a tile, 12 an item
+    (8, 2, 128, 5, 60),     # 4 rows a tile
+    (2, 2, 64, 9, 30),      # 16 rows a tile, one head a group
+    (7, 1, 64, 3, 90),
+])
+def test_shared_prompt_splits_are_bit_identical(hq, hkv, hd, n0, prompts):
+    # prompt pages: none, below a split of 8, exactly 1 and 2 splits, a partial last page, several splits
+    lens = [2, 100, 129, 257, 250, 390, 700]
+    lengths = [lens[u % len(lens)] for u in range(prompts)]
+    cfg = generic_cfg(512, hq, hkv, hd, 512, lengths, k=max(2, n0), n0=n0, budget_N=prompts * max(2, n0), max_new=40)
+    w, pool = W.make_weights(cfg), W.pool_with_lengths(cfg, lengths)
+    g = np.random.default_rng(3)
+    forced = torch.from_numpy(g.integers(0, 500, (prompts * max(2, n0), 40)).astype(np.int32)).cuda()
+    steps = 18
+    many, _ = logits_by_rollout(cfg, w, pool, prompts * n0, forced, steps)
+    few, k = logits_by_rollout(cfg, w, pool, 7 * n0, forced, steps)
+    assert len(many) == prompts * n0 > 256 and len(few) == 7 * n0
+    for key, rows in few.items():
+        for t, (a, b) in enumerate(zip(rows, many[key])):
+            assert bool(torch.isfinite(a).all()) and torch.equal(a, b), (key, t)
