@@ -15,6 +15,7 @@
 // so results do not depend on scheduling.  The fp32 model uses a VALU GEMM.
 #include <mutex>
 
+#include "gemm_tile.h"
 #include "sara_internal.h"
 
 #include <math.h>
@@ -128,16 +129,6 @@ __device__ __forceinline__ float gumbel_candidate_floor(float smax) {
   if (smax == INFINITY) return smax;   // only infinite scores can win
   return smax - 2.0f * kGumbelFastErr - (fabsf(smax) + 1.0f) * 0x1p-20f;
 }
-
-// Operands of the LM-head GEMM's sampling epilogue.
-struct SampleArgs {
-  const RowDesc* rows;       // decode rows (rid, gen, slot)
-  const CtlParams* cp;       // seed, step index, temperature
-  float* logits;             // optional [slots][V] copy of the logits (parity runs), else null
-  float* best;               // [gridDim.x][ld] exact best score of the block's vocabulary range per row
-  int32_t* idx;              // [gridDim.x][ld] its token id
-  int ld;                    // row stride of best / idx (>= the live row count)
-};
 
 // ---------------------------------------------------------------------------
 // embedding gather + first RMSNorm (decode and prefill rows)
@@ -378,11 +369,15 @@ __device__ __attribute__((noinline)) float exact_score(float a, uint32_t rid, ui
 }
 
 // One round of the sampling epilogue over activation tiles T0 .. T0 + TC - 1
-// (compile-time tile indices, so the accumulators stay in registers).
+// (compile-time tile indices, so the accumulators stay in registers).  wave:
+// this wave's quarter of the ids, tid: the thread among the four waves that
+// share the rows, xs: their LDS, chunk: the vocabulary block.  Every wave of the
+// thread block takes part in the same rounds.
 template <int NT, int MT, int TC, int T0, bool UNIT>
 __device__ __forceinline__ void sample_round(const f32x4 (&acc)[NT][MT], int M, int m_base, int N, int n0,
-    const SampleArgs& sa, float temp, uint32_t k0, uint32_t k1, uint16_t* __restrict__ xs) {
-  const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
+    const SampleArgs& sa, float temp, uint32_t k0, uint32_t k1, void* xs, int wave, int tid, int chunk) {
+  static_assert(NT * TC <= 8, "one bit a (tile, id) place of a lane");
+  const int lane = threadIdx.x & 63;
   const int row = lane & 15, grp = lane >> 4;
   float* red_max = (float*)xs;                          // [4][TC][16]
   float* red_s = red_max + 4 * TC * 16;                 // [4][TC][16]
@@ -487,15 +482,15 @@ __device__ __forceinline__ void sample_round(const f32x4 (&acc)[NT][MT], int M, 
     if (grp == 0) { red_s[(wave * TC + tt) * 16 + row] = bs[tt]; red_i[(wave * TC + tt) * 16 + row] = bi[tt]; }
   }
   __syncthreads();
-  if (threadIdx.x < TC * 16) {
-    const int tt = threadIdx.x >> 4, r = threadIdx.x & 15, m = m_base + 16 * (T0 + tt) + r;
+  if (tid < TC * 16) {
+    const int tt = tid >> 4, r = tid & 15, m = m_base + 16 * (T0 + tt) + r;
     if (m < M) {
       float bs = -INFINITY;
       int bi = 0x7FFFFFFF;
 #pragma unroll
       for (int w = 0; w < 4; ++w) better(bs, bi, red_s[(w * TC + tt) * 16 + r], red_i[(w * TC + tt) * 16 + r]);
-      sa.best[(size_t)blockIdx.x * sa.ld + m] = bs;
-      sa.idx[(size_t)blockIdx.x * sa.ld + m] = bi;
+      sa.best[(size_t)chunk * sa.ld + m] = bs;
+      sa.idx[(size_t)chunk * sa.ld + m] = bi;
     }
   }
 }
@@ -510,7 +505,9 @@ __device__ __forceinline__ void sample_epilogue(const f32x4 (&acc)[NT][MT], int 
   uint32_t k0, k1;
   sampler_key(cp->seed, cp->step, k0, k1);
 #define SARA_SR(r, U) \
-  if constexpr (MT > (r) * TC) sample_round<NT, MT, TC, (r) * TC, U>(acc, M, m_base, N, n0, sa, temp, k0, k1, xs);
+  if constexpr (MT > (r) * TC) \
+    sample_round<NT, MT, TC, (r) * TC, U>(acc, M, m_base, N, n0, sa, temp, k0, k1, xs, threadIdx.x >> 6, threadIdx.x, \
+                                          blockIdx.x);
   if (temp == 1.0f) {
     SARA_SR(0, true) SARA_SR(1, true) SARA_SR(2, true) SARA_SR(3, true)
     SARA_SR(4, true) SARA_SR(5, true) SARA_SR(6, true) SARA_SR(7, true)
@@ -678,9 +675,7 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
           for (int q = 0; q < 4; q += 2) {
             float g0 = acc[0][t][q], u0 = acc[NT - 1][t][q];
             float g1 = acc[0][t][q + 1], u1 = acc[NT - 1][t][q + 1];
-            float a0 = g0 / (1.0f + expf(-g0)) * u0;
-            float a1 = g1 / (1.0f + expf(-g1)) * u1;
-            pk[q / 2] = (uint32_t)f32_to_bf16(a0) | ((uint32_t)f32_to_bf16(a1) << 16);
+            pk[q / 2] = pack_bf16(silu_mul(g0, u0), silu_mul(g1, u1));
           }
           *(uint2*)(o + (XT ? (size_t)tiled_index(m, f0, F) : (size_t)m * F + f0)) = make_uint2(pk[0], pk[1]);
         }
@@ -694,8 +689,9 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
 // enough 16-row tiles (ceil(rows / 16)), so small batches spend no MFMA,
 // LDS or X traffic on empty tiles.  Launches have one z block per m-block of
 // the row capacity; z blocks past the live rows exit after reading M.
-// PF only labels the instance in profiles: 0 decode, 1 prefill, 2 the decode
-// attention-output projection (so every decode weight matrix has a class).
+// PF: 0 decode, 1 prefill (fragment-major X), 2 as 0 for the decode
+// attention-output projection (a label in profiles, so that every decode
+// weight matrix has a class).
 template <int NT, int MTMAX, int KC, int EPI, int PF>
 __global__ __launch_bounds__(256, 2) void k_gemm_bf16_lds(const uint16_t* __restrict__ X,
     const uint16_t* __restrict__ W, void* __restrict__ out, const int32_t* __restrict__ M_ptr,
@@ -2105,60 +2101,79 @@ __global__ void k_copy_logits(const Ctl* __restrict__ ctl, const RowDesc* __rest
 // ---------------------------------------------------------------------------
 // host launchers
 // ---------------------------------------------------------------------------
-// bf16 GEMM into fp32 partials ws[split][M_cap][N]
-int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
-              int& splits_out, bool oproj) {
-  const int64_t stride = (int64_t)M_cap * N;
-  // weight rows per block: 128 (two 16-row tiles per wave) for long-K GEMMs of
-  // a prefill, 64 otherwise; split K until the grid has about one block per CU
-  // (each split keeps >= 4 k chunks): wide GEMMs need no split, narrow ones
-  // trade fp32 partial traffic for occupancy
-  constexpr int MT = 8;
-  const bool two = K >= 4096 && c->in_prefill;
-  const int rows_per_block = two ? 128 : 64;
-  int tiles_n = (N + rows_per_block - 1) / rows_per_block;
-  // one z block per m-block of the capacity; in decode the live row count
-  // is read on the device, and z blocks past it exit at once (blocks are
-  // dispatched z-major, so the live m-blocks start first)
-  int zb = (M_cap + 16 * MT - 1) / (16 * MT);
-  // blocks without a split: weight tiles x m-blocks in prefill (the chunk's
-  // row count is known), weight tiles alone in decode (live rows are few
-  // and known only on the device)
-  const int64_t blocks = (int64_t)tiles_n * (c->in_prefill ? zb : 1);
-  int want = (blocks >= 256) ? 1 : (int)((256 + blocks - 1) / blocks);
-  // 64-wide k chunks: four pipeline slots of X + W fit in registers for NT <= 2
-  const int KC = 64;
-  int chunks = K / KC;
+// K splits of a decode GEMM into fp32 partials: until 64-row weight blocks reach
+// one block per CU (the live rows are few and known only on the device), as an
+// even division of the k chunks (the last split of an uneven one runs alone):
+// the largest count in [6, kMaxSplitsDec] with >= 4 chunks per split, else the
+// occupancy target.  Consumers sum at most kMaxSplitsDec partials in one batch
+// of loads.  Returns the K range of a split.
+static int decode_split_k(const sara_ctx* c, int M_cap, int N, int K) {
+  const int tiles_n = (N + 63) / 64, chunks = K / 64;
+  const int want = (tiles_n >= 256) ? 1 : (256 + tiles_n - 1) / tiles_n;
   int splits = std::min(want, std::max(1, chunks / 4));
-  if (!c->in_prefill) {
-    // decode: an even division of the k chunks keeps the splits balanced
-    // (the last split of an uneven one runs alone); take the largest even
-    // count in [6, kMaxSplitsDec] with >= 4 chunks per split, else the
-    // occupancy target.  Consumers sum at most kMaxSplitsDec partials in
-    // one batch of loads.
-    for (int s = kMaxSplitsDec; s >= 6; --s)
-      if (s <= want && chunks % s == 0 && chunks / s >= 4) { splits = s; break; }
-    splits = std::min(splits, kMaxSplitsDec);
-  }
-  if (splits < 1) splits = 1;
-  int kps = ((chunks + splits - 1) / splits) * KC;
+  for (int s = kMaxSplitsDec; s >= 6; --s)
+    if (s <= want && chunks % s == 0 && chunks / s >= 4) { splits = s; break; }
+  splits = std::max(1, std::min(splits, kMaxSplitsDec));
+  const int kps = ((chunks + splits - 1) / splits) * 64;
+  return (int64_t)((K + kps - 1) / kps) * M_cap * N > c->ws_floats ? K : kps;
+}
+
+// bf16 GEMM of a short prefill chunk into fp32 partials ws[split][M][N]
+int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M, int N, int K, int& splits_out) {
+  const int64_t stride = (int64_t)M * N;
+  // weight rows per block: 128 (two 16-row tiles per wave) for long K, 64
+  // otherwise; split K until the grid has about one block per CU (each split
+  // keeps >= 4 k chunks): wide GEMMs need no split, narrow ones trade fp32
+  // partial traffic for occupancy
+  constexpr int MT = 8;
+  const bool two = K >= 4096;
+  const int rows_per_block = two ? 128 : 64;
+  const int tiles_n = (N + rows_per_block - 1) / rows_per_block, zb = (M + 16 * MT - 1) / (16 * MT);
+  const int64_t blocks = (int64_t)tiles_n * zb;
+  const int want = (blocks >= 256) ? 1 : (int)((256 + blocks - 1) / blocks);
+  const int chunks = K / 64;
+  int splits = std::max(1, std::min(want, std::max(1, chunks / 4)));
+  int kps = ((chunks + splits - 1) / splits) * 64;
   splits = (K + kps - 1) / kps;
   if ((int64_t)splits * stride > c->ws_floats) { splits = 1; kps = K; }
-  dim3 grid(tiles_n, splits, zb);
-#define SARA_GEMM(NT_, PF_)                                                                                       \
-  launch_k(c, c->stream, (k_gemm_bf16_lds<NT_, MT, 64, 0, PF_>), grid, dim3(256), 0, (const uint16_t*)X,          \
+  const dim3 grid(tiles_n, splits, zb);
+#define SARA_GEMM(NT_)                                                                                            \
+  launch_k(c, c->stream, (k_gemm_bf16_lds<NT_, MT, 64, 0, 1>), grid, dim3(256), 0, (const uint16_t*)X,            \
            (const uint16_t*)W, (void*)c->ws, M_ptr, N, K, kps, stride, SampleArgs{})
-  if (c->in_prefill) {
-    if (two) SARA_GEMM(2, 1);
-    else SARA_GEMM(1, 1);
-  } else if (oproj) {
-    SARA_GEMM(1, 2);
-  } else {
-    SARA_GEMM(1, 0);
-  }
+  if (two) SARA_GEMM(2);
+  else SARA_GEMM(1);
 #undef SARA_GEMM
   splits_out = splits;
   return SARA_OK;
+}
+
+// bf16 GEMM of a decode step into fp32 partials ws[split][M_cap][N]; returns
+// the splits.  One z block per m-block of the capacity; the live row count is
+// read on the device, and z blocks past it exit at once (blocks are dispatched
+// z-major, so the live m-blocks start first).
+static int gemm_decode(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
+                       bool oproj) {
+  const int64_t stride = (int64_t)M_cap * N;
+  const int kps = decode_split_k(c, M_cap, N, K), splits = (K + kps - 1) / kps;
+  // down on tiles (512 rows of 11008 -> 2048: 40 us against 49); the o
+  // projection's splits are too short for them (8 steps: 19 us against 17)
+  if (c->tile_rows && !oproj) {
+    GemmTileArgs a{};
+    a.M_ptr = M_ptr;
+    a.out = c->ws;
+    a.split_stride = stride;
+    a.steps = kps / 32;
+    gemm_tile<0>(c, X, W, M_cap, N, K, a);
+    return splits;
+  }
+  const dim3 grid((N + 63) / 64, splits, (M_cap + 127) / 128);
+#define SARA_GEMM(PF_)                                                                                            \
+  launch_k(c, c->stream, (k_gemm_bf16_lds<1, 8, 64, 0, PF_>), grid, dim3(256), 0, (const uint16_t*)X,             \
+           (const uint16_t*)W, (void*)c->ws, M_ptr, N, K, kps, stride, SampleArgs{})
+  if (oproj) SARA_GEMM(2);
+  else SARA_GEMM(0);
+#undef SARA_GEMM
+  return splits;
 }
 
 // fp32 GEMM into out (see k_gemm_f32).  Four row tiles a block in a prefill,
@@ -2187,6 +2202,14 @@ static void gemm_f32(sara_ctx* c, const void* X, const void* W, float* out, cons
 void gemm_swiglu(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap) {
   constexpr int MT = 8;
   const int N = 2 * c->ffn, K = c->d;
+  if (!c->in_prefill && c->tile_rows) {
+    GemmTileArgs a{};
+    a.M_ptr = M_ptr;
+    a.steps = K / 32;
+    a.xa = (uint16_t*)c->xa;
+    gemm_tile<1>(c, X, W, M_cap, N, K, a);
+    return;
+  }
   dim3 grid((N + 127) / 128, 1, (M_cap + 16 * MT - 1) / (16 * MT));
   if (c->in_prefill)
     launch_k(c, c->stream, (k_gemm_bf16_lds<2, MT, 64, 1, 1>), grid, dim3(256), 0, (const uint16_t*)X,
@@ -2271,6 +2294,10 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
   hipStream_t st = c->stream;
   const int d = c->d;
   uint16_t* x = (uint16_t*)c->x;
+  // many rows: the tile GEMMs' inputs fragment-major (a row-major stride of a
+  // power of two sends a fragment's 16 rows to few channels: gate|up of 512
+  // rows of d 2048 57 us against 44)
+  const int xt = c->tile_rows ? 1 : 0;
   for (int l = 0; l < c->L; ++l) {
     int sp = 1;
     // q|k|v projection with the RoPE / KV-append epilogue, the paged
@@ -2302,20 +2329,20 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
              c->hkv, c->dec_splits_max, kDecPages, 1, x);
     PROF_E(c, kPCombine, 0, 0);
     PROF_B(c);
-    gemm_bf16(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, sp, true);
+    sp = gemm_decode(c, x, c->w_o[l], M_ptr, M_cap, d, c->qdim, true);
     PROF_E(c, kPGemmO1, d, c->qdim);
     PROF_B(c);
-    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 1) * d, 0);
+    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 1) * d, xt);
     PROF_E(c, kPResNorm, d, 0);
     PROF_B(c);
     gemm_swiglu(c, x, c->w_gu[l], M_ptr, M_cap);
     PROF_E(c, kPGemmGU, 2 * c->ffn, d);
     PROF_B(c);
-    gemm_bf16(c, c->xa, c->w_d[l], M_ptr, M_cap, d, c->ffn, sp);
+    sp = gemm_decode(c, c->xa, c->w_d[l], M_ptr, M_cap, d, c->ffn, false);
     PROF_E(c, kPGemmN1, d, c->ffn);
     PROF_B(c);
     // the next layer's norm (its q|k|v kernel reads fragment-major rows) or the final one
-    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d, l + 1 < c->L ? 1 : 0);
+    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d, l + 1 < c->L ? 1 : xt);
     PROF_E(c, kPResNorm, d, 0);
   }
 }
@@ -2467,11 +2494,20 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
       } else {
         // LM head with the Gumbel-max sampling epilogue: per (row, 128-id block)
         // exact winners, reduced by k_sample_final
+        const SampleArgs sa{c->rows, (const CtlParams*)c->cp_dev, logits, c->samp_best, c->samp_idx, S};
         nchunks = nb;
         PROF_B(c);
+        if (c->tile_rows) {
+          nchunks = (c->V + 255) / 256;
+          GemmTileArgs a{};
+          a.M_ptr = c->rows_M;
+          a.steps = c->d / 32;
+          a.sample = sa;
+          gemm_tile<5>(c, c->x, c->lm_head, S, c->V, c->d, a);
+        } else
         launch_k(c, st, (k_gemm_bf16_lds<2, 8, 64, 2, 0>), lm_grid, dim3(256), 0, (const uint16_t*)c->x,
                  (const uint16_t*)c->lm_head, (void*)nullptr, c->rows_M, c->V, c->d, c->d, (int64_t)0,
-                 SampleArgs{c->rows, (const CtlParams*)c->cp_dev, logits, c->samp_best, c->samp_idx, S});
+                 sa);
         PROF_E(c, kPGemmLM, c->V, c->d);
       }
     } else {

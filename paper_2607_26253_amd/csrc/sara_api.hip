@@ -1,5 +1,6 @@
 // C ABI of libsara: context lifetime, step driving, graph replay, readback.
 #include <math.h>
+#include <stddef.h>
 #include <string.h>
 
 #include <algorithm>
@@ -349,9 +350,9 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->g_n, sizeof(int32_t));
 #undef ALLOC
   {
-    hipError_t e = hipHostMalloc((void**)&c->h_done, 2 * sizeof(int32_t), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&c->h_done, 6 * sizeof(int32_t), hipHostMallocDefault);
     if (e != hipSuccess) { sara_destroy(c); return hip_fail(e, "hipHostMalloc"); }
-    c->h_done[0] = c->h_done[1] = 0;
+    memset(c->h_done, 0, 6 * sizeof(int32_t));
   }
 
   hipStream_t st = c->stream;
@@ -477,6 +478,12 @@ extern "C" int sara_begin_step(sara_ctx* c, const int32_t* d_tokens, const int32
   launch_prefill(c);
   launch_refill(c);
   HIP_TRY(hipGetLastError(), "begin_step launch");
+  {
+    // rows of the first draws (the refill's rule on a fresh step)
+    int64_t d = std::min<int64_t>(c->U, c->ad.budget_N / c->k);
+    if (c->ad.mode != SARA_MODE_FIXED_K) d = std::min<int64_t>(d, c->ad.B);
+    c->run_M = (int)std::min<int64_t>(c->S, std::max<int64_t>(d, 0) * c->ad.n0);
+  }
   c->in_step = true;
   c->warm_step = c->warm_ids != nullptr;
   return SARA_OK;
@@ -568,21 +575,32 @@ extern "C" int sara_refill(sara_ctx* c) {
   return SARA_OK;
 }
 
-static int build_graph(sara_ctx* c, const int32_t* forced, int iters) {
-  if (c->graph_exec) { (void)hipGraphExecDestroy(c->graph_exec); c->graph_exec = nullptr; }
-  if (c->graph) { (void)hipGraphDestroy(c->graph); c->graph = nullptr; }
+// sara_run copies (done, error, M) in one piece
+static_assert(offsetof(Ctl, error) == offsetof(Ctl, done) + 4 && offsetof(Ctl, M) == offsetof(Ctl, done) + 8,
+              "polled fields are adjacent");
+
+static void drop_graph(sara_ctx::LoopGraph& g) {
+  if (g.exec) (void)hipGraphExecDestroy(g.exec);
+  if (g.graph) (void)hipGraphDestroy(g.graph);
+  g = sara_ctx::LoopGraph{};
+}
+
+static int build_graph(sara_ctx* c, sara_ctx::LoopGraph& g, bool tile_rows, const int32_t* forced, int iters) {
+  drop_graph(g);
   HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal), "begin capture");
   c->capturing = true;
   c->prof_active = false;
+  c->tile_rows = tile_rows;
   for (int i = 0; i < iters; ++i) {
     launch_decode(c, forced, nullptr, 0);
     launch_decide_refill(c);
   }
+  c->tile_rows = false;
   c->capturing = false;
-  HIP_TRY(hipStreamEndCapture(c->stream, &c->graph), "end capture");
-  HIP_TRY(hipGraphInstantiate(&c->graph_exec, c->graph, nullptr, nullptr, 0), "graph instantiate");
-  c->graph_iters = iters;
-  c->graph_forced = forced;
+  HIP_TRY(hipStreamEndCapture(c->stream, &g.graph), "end capture");
+  HIP_TRY(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0), "graph instantiate");
+  g.iters = iters;
+  g.forced = forced;
   return SARA_OK;
 }
 
@@ -591,35 +609,43 @@ extern "C" int sara_run(sara_ctx* c, const int32_t* d_forced_tok, int32_t graph_
   if (!c) return einval("null context");
   if (!c->in_step) { set_error("sara_run before sara_begin_step"); return SARA_ESTATE; }
   if (graph_iters < 1 || graph_iters > 4096) return einval("graph_iters must be in [1, 4096]");
-  if (!c->graph_exec || c->graph_iters != graph_iters || c->graph_forced != d_forced_tok) {
-    int rc = build_graph(c, d_forced_tok, graph_iters);
-    if (rc) return rc;
-  }
   hipEvent_t ev[2];
   HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming), "event");
   HIP_TRY(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming), "event");
-  c->h_done[0] = c->h_done[1] = 0;
+  memset(c->h_done, 0, 6 * sizeof(int32_t));
   int64_t iters = 0;
   int n = 0;
   int rc = SARA_OK;
+  volatile int32_t* h = c->h_done;   // per slot: done flag, error word, live rows
   while (iters < max_iters) {
-    hipError_t e = hipGraphLaunch(c->graph_exec, c->stream);
+    // The loop with the tile GEMMs for more than kTileRows live rows, as known
+    // when the launch before the last one ended.  Either graph is right for any
+    // row count, with bit-identical results; only the speed differs.
+    const bool many = c->md.dtype == SARA_BF16 && c->run_M > kTileRows;
+    sara_ctx::LoopGraph& g = c->loop_graph[many ? 1 : 0];
+    if (!g.exec || g.iters != graph_iters || g.forced != d_forced_tok) {
+      rc = build_graph(c, g, many, d_forced_tok, graph_iters);
+      if (rc) break;
+    }
+    hipError_t e = hipGraphLaunch(g.exec, c->stream);
     if (e != hipSuccess) { rc = hip_fail(e, "graph launch"); break; }
     iters += graph_iters;
     int slot = n & 1;
-    e = hipMemcpyAsync(&c->h_done[slot], &c->ctl->done, sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(&c->h_done[3 * slot], &c->ctl->done, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipEventRecord(ev[slot], c->stream);
     if (e != hipSuccess) { rc = hip_fail(e, "poll"); break; }
     if (n > 0) {
       int prev = (n - 1) & 1;
       e = hipEventSynchronize(ev[prev]);
       if (e != hipSuccess) { rc = hip_fail(e, "poll wait"); break; }
-      if (((volatile int32_t*)c->h_done)[prev]) break;
+      c->run_M = h[3 * prev + 2];
+      if (h[3 * prev]) break;
     }
     ++n;
   }
   hipError_t e = hipStreamSynchronize(c->stream);
   if (e != hipSuccess && rc == SARA_OK) rc = hip_fail(e, "run sync");
+  if (e == hipSuccess && iters > 0) c->run_M = std::max(h[2], h[5]);
   (void)hipEventDestroy(ev[0]);
   (void)hipEventDestroy(ev[1]);
   if (iters_out) *iters_out = iters;
@@ -807,8 +833,7 @@ extern "C" int sara_gumbel_fast_max_error(double* h_out, void* stream) {
 extern "C" void sara_destroy(sara_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
-  if (c->graph_exec) (void)hipGraphExecDestroy(c->graph_exec);
-  if (c->graph) (void)hipGraphDestroy(c->graph);
+  for (auto& g : c->loop_graph) drop_graph(g);
   if (c->h_done) (void)hipHostFree(c->h_done);
   for (hipEvent_t e : c->prof_events) (void)hipEventDestroy(e);
   for (void* p : c->owned) (void)hipFree(p);

@@ -21,6 +21,7 @@ constexpr int kDecPpw = 2;           // KV pages per wave in the decode attentio
 constexpr int kDecPages = 4 * kDecPpw;  // KV pages per context split in the decode attention
 constexpr int kMaxSplitsDec = 12;    // split-K partials of a decode GEMM (summed in one batch; a multiple of 4)
 constexpr int kPrefillRowsBf16 = 32768;  // most rows of a prefill chunk of a bf16 model
+constexpr int kTileRows = 256;       // decode batches beyond this many rows take 256-row GEMM tiles
 constexpr int kAttnTile = 64;        // tokens per LDS tile inside a split
 constexpr int kSampleChunks = 16;    // vocabulary chunks per sampled row
 constexpr int kTopPChunks = 16;      // vocabulary chunks per row in the top-p passes
@@ -83,6 +84,17 @@ struct AttnItem {
 struct PromptPlace {
   uint16_t row, rank;
   int32_t n;
+};
+
+struct CtlParams;
+// Operands of the LM-head GEMM's sampling epilogue.
+struct SampleArgs {
+  const RowDesc* rows;       // decode rows (rid, gen, slot)
+  const CtlParams* cp;       // seed, step index, temperature
+  float* logits;             // optional [slots][V] copy of the logits (parity runs), else null
+  float* best;               // [vocabulary block][ld] exact best score of the block's ids per row
+  int32_t* idx;              // [vocabulary block][ld] its token id
+  int ld;                    // row stride of best / idx (>= the live row count)
 };
 
 // Parameters every controller kernel reads.
@@ -199,12 +211,17 @@ struct sara_ctx {
   float* g_adv = nullptr;
   int32_t* g_n = nullptr;         // committed count used for the CSR
 
-  // graph replay
-  hipGraphExec_t graph_exec = nullptr;
-  hipGraph_t graph = nullptr;
-  int graph_iters = 0;
-  const int32_t* graph_forced = nullptr;
-  int32_t* h_done = nullptr;      // pinned
+  // graph replay: the loop captured with the few-row kernels [0] and, for
+  // batches of more than kTileRows live rows, the 256 x 256 tile GEMMs [1]
+  struct LoopGraph {
+    hipGraphExec_t exec = nullptr;
+    hipGraph_t graph = nullptr;
+    int iters = 0;
+    const int32_t* forced = nullptr;
+  } loop_graph[2];
+  int run_M = 0;                  // live rows as last known to the host
+  bool tile_rows = false;         // launch_decode uses the tile GEMMs (capture of loop_graph[1])
+  int32_t* h_done = nullptr;      // pinned: 2 x (done flag, error word, live rows)
 
   std::vector<void*> owned;       // device allocations freed by sara_destroy
   // per-launch profiling of eager decode steps
@@ -261,8 +278,7 @@ void build_prefill_tiles(sara_ctx* c, const int32_t* pre);
 int64_t max_prefill_tiles(const sara_ctx* c);
 void prefill_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int chunk);
 // model launchers that the prefill shares
-int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap, int N, int K,
-              int& splits_out, bool oproj = false);
+int gemm_bf16(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M, int N, int K, int& splits_out);
 void gemm_swiglu(sara_ctx* c, const void* X, const void* W, const int32_t* M_ptr, int M_cap);
 void residual_norm_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, const float* w);
 void launch_qkv_epilogue_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int sp, int layer);
@@ -368,6 +384,11 @@ __device__ __forceinline__ U32x4 philox4x32_10(uint32_t c0, uint32_t c1, uint32_
 __device__ __forceinline__ void sampler_key(uint64_t seed, int32_t step, uint32_t& k0, uint32_t& k1) {
   k0 = (uint32_t)seed;
   k1 = (uint32_t)(seed >> 32) ^ (uint32_t)step;
+}
+
+// silu(g) * u on the hardware exponential and reciprocal (each within 1 ulp)
+__device__ __forceinline__ float silu_mul(float g, float u) {
+  return g * u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
 }
 
 // SplitMix64 output finalizer (Steele, Lea, Flood, OOPSLA'14).

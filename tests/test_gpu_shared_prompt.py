@@ -52,3 +52,35 @@ def test_shared_prompt_splits_are_bit_identical(hq, hkv, hd, n0, prompts):
     for key, rows in few.items():
         for t, (a, b) in enumerate(zip(rows, many[key])):
             assert bool(torch.isfinite(a).all()) and torch.equal(a, b), (key, t)
+
+
+@pytest.mark.parametrize("width,n0,prompts", [((512, 8, 2, 64, 512), 8, 40), ((1024, 6, 1, 128, 1472), 7, 73)])
+def test_many_row_graph_is_bit_identical(width, n0, prompts):
+    """More than 256 live rows: sara_run replays the loop with the 256-row tile
+    GEMMs, the eager calls run the few-row kernels; sampled tokens, logs and
+    the state both leave behind are the same, also once rollouts have ended
+    and few rows are left."""
+    lengths = [2 + (7 * u) % 60 for u in range(prompts)]
+    cfg = generic_cfg(*width, lengths, vocab=1008, k=8, n0=n0, budget_N=prompts * 8, max_new=40)
+    cfg["alloc"].update(n_slots=prompts * n0, commit_min=8, forced_eos_u32=(1 << 32) // 24, pool_U=prompts)
+    w, pool, seed = W.make_weights(cfg), W.pool_with_lengths(cfg, lengths), None
+    out = []
+    for graph in (True, False):
+        ctx, _ = device_setup(cfg, w)
+        d_tok, d_p, _ = upload_pool(pool)
+        ctx.sara_begin_step(d_tok, pool["offsets"], d_p, None, 0)
+        if graph:
+            ctx.sara_run(None, graph_iters=3)
+        else:
+            while not ctx.sara_query()["done"]:
+                ctx.sara_decode_step()
+                ctx.sara_posterior_decide()
+                ctx.sara_refill()
+        out.append((ctx.read_rollouts(), ctx.read_logs(), ctx.sara_query()))
+        ctx.close()
+    (ra, la, qa), (rb, lb, qb) = out
+    assert qa["tokens"] == qb["tokens"] > 0 and qa["decode_steps"] == qb["decode_steps"]
+    for key in ra:
+        assert np.array_equal(ra[key], rb[key]), key
+    for key in la:
+        assert np.array_equal(la[key], lb[key]), key
