@@ -1669,7 +1669,9 @@ __device__ __forceinline__ uint32_t zkey(float z) {
   return (u & 0x80000000u) ? ~u : (u | 0x80000000u);
 }
 __device__ __forceinline__ uint64_t nucleus_weight(float z, float zmax) {
-  return (uint64_t)floor(ldexp(exp((double)z - (double)zmax), 44));
+  // 0 <= w <= 2^44 (NaN: 0), so w + 2^52 holds the whole number in its low bits
+  const double w = fmax(floor(ldexp(exp((double)z - (double)zmax), 44)), 0.0);
+  return (uint64_t)__double_as_longlong(w + 4503599627370496.0) & 0xFFFFFFFFFFFFFull;
 }
 
 // Gumbel-max over vocabulary chunk c of nch of row i: the chunk's exact best
@@ -1719,6 +1721,12 @@ __global__ __launch_bounds__(256) void k_sample_partial(const int32_t* __restric
           for (int q = 0; q < 4; ++q) z[e][q] = lg[min(4 * b + q, V - 1)];
         }
       }
+      if (temp != 1.0f) {                                // one branch around all divisions
+#pragma unroll
+        for (int e = 0; e < Q; ++e)
+#pragma unroll
+          for (int q = 0; q < 4; ++q) z[e][q] = __fdiv_rn(z[e][q], temp);
+      }
       f32x4 f[Q];                                        // score bounds, NaN for ids that take no part
       float lub = -INFINITY, lz = -INFINITY;             // the lane's best bound, its z
       uint32_t lw = 0u;                                  // and its noise word
@@ -1728,7 +1736,6 @@ __global__ __launch_bounds__(256) void k_sample_partial(const int32_t* __restric
         bool in[4], any = false;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
-          if (temp != 1.0f) z[e][q] = __fdiv_rn(z[e][q], temp);
           in[q] = b < b1 && 4 * b + q < V && zkey(z[e][q]) >= kth;
           any |= in[q];
           f[e][q] = __builtin_nanf("");
@@ -1811,43 +1818,66 @@ __device__ __forceinline__ float zval(const float* lg, int v, float temp) {
 
 // Vocabulary chunks per row in the top-p passes: enough (row, chunk) blocks to
 // fill the GPU, and no more, since every chunk writes and every pick reads a
-// 16 KiB histogram (128 rows x 151936 ids: a pick 6.7 us at 8 chunks, 9.9 at 16;
-// the histogram pass 35 us at both).
+// 16 KiB histogram (128 rows x 151936 ids: a pick 6.0 us at 8 chunks, 9 at 16,
+// the histogram passes alike).
 __device__ __forceinline__ int topp_chunks(int M) { return max(1, min(kTopPChunks, 1024 / max(M, 1))); }
 // Chunk c: [c*per, min(V, (c+1)*per)) with per a multiple of 4, so a chunk of a
 // row whose length V is a multiple of 4 starts 16-byte aligned.
 __device__ __forceinline__ int topp_chunk_len(int V, int nch) { return (((V + nch - 1) / nch) + 3) & ~3; }
 
-// Calls f(v, z) for every id v of [v0, v1) of the row lg, z = fp32(lg[v] / T).
-// A row that starts 16-byte aligned and whose length is divisible by 4 is
-// read as float4 with kTopPLoads loads of a thread in flight at once (a
-// chunk is ~40 floats per thread, so one or two rounds of loads); any other
-// row one float at a time.
-constexpr int kTopPLoads = 8;
+// Calls f(z, true) for every id of [v0, v1) of the row lg, z = fp32(lg[v] / T),
+// on all lanes of a wave together (f(z, false) where a lane has no id).  A row
+// that starts 16-byte aligned and whose length is divisible by 4 is read as
+// float4, kTopPLoads loads of a thread at a time and the next ones in flight
+// while these are used; any other row one float at a time.
+constexpr int kTopPLoads = 4;
 template <typename F>
 __device__ __forceinline__ void topp_visit(const float* __restrict__ lg, int V, int v0, int v1, float temp, F f) {
+  const int tid = threadIdx.x;
   if ((V & 3) == 0 && (reinterpret_cast<uintptr_t>(lg) & 15) == 0) {
     const float4* l4 = reinterpret_cast<const float4*>(lg);
-    const int q0 = v0 >> 2, q1 = v1 >> 2;
-    for (int base = q0 + (int)threadIdx.x; base < q1; base += 256 * kTopPLoads) {
-      float4 x[kTopPLoads];
+    const int q1 = v1 >> 2;
+    constexpr int kStep = 256 * kTopPLoads;
+    const auto load = [&](float4 (&x)[kTopPLoads], int base) {
 #pragma unroll
       for (int u = 0; u < kTopPLoads; ++u) {
-        const int qq = base + u * 256;
+        const int qq = base + u * 256 + tid;
         if (qq < q1) x[u] = l4[qq];
       }
+    };
+    const auto use = [&](float4 (&x)[kTopPLoads], int base) {
+      // one branch around all divisions: a choice for each value computes the
+      // division (11 instructions) and throws it away
+      if (temp != 1.0f) {
+#pragma unroll
+        for (int u = 0; u < kTopPLoads; ++u)
+          x[u] = make_float4(__fdiv_rn(x[u].x, temp), __fdiv_rn(x[u].y, temp), __fdiv_rn(x[u].z, temp),
+                             __fdiv_rn(x[u].w, temp));
+      }
 #pragma unroll
       for (int u = 0; u < kTopPLoads; ++u) {
-        const int qq = base + u * 256;
-        if (qq < q1) {
-          const float e4[4] = {x[u].x, x[u].y, x[u].z, x[u].w};
-#pragma unroll
-          for (int e = 0; e < 4; ++e) f(4 * qq + e, (temp == 1.0f) ? e4[e] : __fdiv_rn(e4[e], temp));
-        }
+        if (base + u * 256 >= q1) break;   // uniform
+        const bool ok = base + u * 256 + tid < q1;
+        f(x[u].x, ok);
+        f(x[u].y, ok);
+        f(x[u].z, ok);
+        f(x[u].w, ok);
       }
+    };
+    float4 x[kTopPLoads] = {}, y[kTopPLoads] = {};
+    int base = v0 >> 2;
+    load(x, base);
+    for (; base < q1; base += 2 * kStep) {
+      load(y, base + kStep);
+      use(x, base);
+      load(x, base + 2 * kStep);
+      use(y, base + kStep);
     }
   } else {
-    for (int v = v0 + (int)threadIdx.x; v < v1; v += 256) f(v, zval(lg, v, temp));
+    for (int v = v0; v < v1; v += 256) {
+      const bool ok = v + tid < v1;
+      f(ok ? zval(lg, v + tid, temp) : 0.0f, ok);
+    }
   }
 }
 
@@ -1863,7 +1893,7 @@ __global__ __launch_bounds__(256) void k_topp_max(const int32_t* __restrict__ M_
     const float* lg = logits + (size_t)(by_slot ? rows[i].slot : i) * V;
     const int v0 = min(V, c * per), v1 = min(V, v0 + per);
     float zm = -INFINITY;
-    topp_visit(lg, V, v0, v1, temp, [&](int, float z) { zm = fmaxf(zm, z); });
+    topp_visit(lg, V, v0, v1, temp, [&](float z, bool ok) { zm = ok ? fmaxf(zm, z) : zm; });
     zm = wave_max(zm);
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = zm;
     __syncthreads();
@@ -1879,40 +1909,70 @@ __device__ __forceinline__ float row_zmax(const float* __restrict__ pmax, int i,
 }
 
 // digit d of the descent: bits 31..21 (d = 0), 20..10 (d = 1), 9..0 (d = 2)
-__device__ __forceinline__ int digit_shift(int d) { return d == 0 ? 21 : (d == 1 ? 10 : 0); }
+__host__ __device__ constexpr int digit_shift(int d) { return d == 0 ? 21 : (d == 1 ? 10 : 0); }
 
+// Histogram pass of digit D.  The first is bound by the fp64 exponential of each
+// id (about 30 instructions of 4 cycles a wave); the others by reading the
+// logits and their histograms, since few ids match the bits decided so far: a
+// wave queues those in LDS and takes the exponential of 64 at once, where one
+// match in the wave would cost as much as 64.  128 rows x 151936 ids 38 / 26 /
+// 22 us (k_topp_max, which only reads, 14.7), 35 us on average for the three with
+// an exponential for each wave that holds a match and a discarded division.
+template <int D>
 __global__ __launch_bounds__(256) void k_topp_hist(const int32_t* __restrict__ M_ptr, int M,
     const RowDesc* __restrict__ rows, const float* __restrict__ logits, int V, int by_slot,
-    const CtlParams* __restrict__ cpd, float temp, const float* __restrict__ pmax, int d,
+    const CtlParams* __restrict__ cpd, float temp, const float* __restrict__ pmax,
     const uint32_t* __restrict__ prefix, unsigned long long* __restrict__ hist) {
   __shared__ unsigned long long h[kTopPBins];
+  __shared__ float queue[4][128];
+  float* const wq = queue[threadIdx.x >> 6];
   if (cpd) temp = cpd->temperature;
   if (M_ptr) M = *M_ptr;
   const int nch = topp_chunks(M), per = topp_chunk_len(V, nch);
-  const int sh = digit_shift(d);
-  const uint32_t dmask = (d == 2) ? 1023u : 2047u;
-  const int hi = (d == 1) ? 21 : 10;   // the bits decided before digit d (d > 0)
+  constexpr int sh = digit_shift(D);
+  constexpr int nbins = (D == 2) ? 1024 : kTopPBins;
+  constexpr uint32_t dmask = nbins - 1;
+  constexpr int hi = (D == 1) ? 21 : 10;   // the bits decided before digit D (D > 0)
+  const int lane = threadIdx.x & 63;
   for (int item = blockIdx.x; item < M * nch; item += gridDim.x) {
     const int i = item / nch, c = item - i * nch;
     const float* lg = logits + (size_t)(by_slot ? rows[i].slot : i) * V;
     const int v0 = min(V, c * per), v1 = min(V, v0 + per);
     const float zm = row_zmax(pmax, i, nch);
-    const uint32_t pre = (d > 0) ? prefix[i] : 0u;
-    for (int b = threadIdx.x; b < kTopPBins; b += 256) h[b] = 0ull;
+    const uint32_t pre = (D > 0) ? prefix[i] : 0u;
+    for (int b = threadIdx.x; b < nbins; b += 256) h[b] = 0ull;
     __syncthreads();
-    topp_visit(lg, V, v0, v1, temp, [&](int, float z) {
-      const uint32_t key = zkey(z);
-      if (d == 0 || (key >> hi) == (pre >> hi)) {
-        const uint64_t q = nucleus_weight(z, zm);
-        if (q) atomicAdd(&h[(key >> sh) & dmask], (unsigned long long)q);
-      }
-    });
+    const auto add = [&](float z) {
+      const uint64_t q = nucleus_weight(z, zm);
+      if (q) atomicAdd(&h[(zkey(z) >> sh) & dmask], (unsigned long long)q);
+    };
+    if (D == 0) {
+      topp_visit(lg, V, v0, v1, temp, [&](float z, bool ok) { if (ok) add(z); });
+    } else {
+      int put = 0, got = 0;
+      topp_visit(lg, V, v0, v1, temp, [&](float z, bool ok) {
+        const bool hit = ok && (zkey(z) >> hi) == (pre >> hi);
+        const unsigned long long hits = __ballot(hit);
+        if (hits == 0ull) return;
+        if (hit) wq[(put + __popcll(hits & ((1ull << lane) - 1ull))) & 127] = z;
+        put += __popcll(hits);
+        if (put - got >= 64) {
+          __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+          add(wq[(got + lane) & 127]);
+          got += 64;
+        }
+      });
+      __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+      if (lane < put - got) add(wq[(got + lane) & 127]);
+    }
     __syncthreads();
     unsigned long long* out = hist + (size_t)item * kTopPBins;
-    for (int b = threadIdx.x; b < kTopPBins; b += 256) out[b] = h[b];
+    for (int b = threadIdx.x; b < nbins; b += 256) out[b] = h[b];
     __syncthreads();   // h is cleared for the next item
   }
 }
+
+static auto topp_hist_kernel(int d) { return d == 0 ? k_topp_hist<0> : (d == 1 ? k_topp_hist<1> : k_topp_hist<2>); }
 
 // Per-row state of the descent: prefix (z*'s key bits decided so far; after
 // digit 2, z*'s key), above (weight of keys above the current range), target.
@@ -1930,12 +1990,17 @@ __global__ __launch_bounds__(kTopPThreads) void k_topp_pick(const int32_t* __res
   const int sh = digit_shift(d);
   for (int i = blockIdx.x; i < M; i += gridDim.x) {
     // the chunk histograms, summed in chunk order
-    const unsigned long long* hr = hist + (size_t)i * nch * kTopPBins;
+    const ulonglong2* hr = (const ulonglong2*)(hist + (size_t)i * nch * kTopPBins) + tid;
     unsigned long long h0 = 0ull, h1 = 0ull;
-#pragma unroll 4
-    for (int c = 0; c < nch; ++c) {
-      h0 += hr[(size_t)c * kTopPBins + 2 * tid];
-      h1 += hr[(size_t)c * kTopPBins + 2 * tid + 1];
+    if (d < 2 || tid < 512) {                 // the last digit has 1024 bins
+      for (int c = 0; c < nch; c += 8) {      // 8 loads in flight
+        ulonglong2 x[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) x[u] = hr[(size_t)min(c + u, nch - 1) * kTopPThreads];
+#pragma unroll
+        for (int u = 0; u < 8; ++u)
+          if (c + u < nch) { h0 += x[u].x; h1 += x[u].y; }
+      }
     }
     unsigned long long above = 0ull;
     uint32_t pre = 0u;
@@ -2447,8 +2512,8 @@ static void launch_topp_decode(sara_ctx* c, hipStream_t st, const float* lg, int
   PROF_E(c, kPToppMax, c->V, 0);
   for (int d = 0; d < 3; ++d) {
     PROF_B(c);
-    launch_k(c, st, k_topp_hist, dim3(g), dim3(256), 0, Mp, 0, rw, lg, c->V, by_slot, cp, 1.0f,
-             (const float*)c->topp_max, d, (const uint32_t*)c->topp_thr, c->topp_hist);
+    launch_k(c, st, topp_hist_kernel(d), dim3(g), dim3(256), 0, Mp, 0, rw, lg, c->V, by_slot, cp, 1.0f,
+             (const float*)c->topp_max, (const uint32_t*)c->topp_thr, c->topp_hist);
     PROF_E(c, kPToppHist, c->V, 0);
     PROF_B(c);
     launch_k(c, st, k_topp_pick, dim3(std::min(S, 1024)), dim3(kTopPThreads), 0, Mp, 0, cp, 1.0f, d,
@@ -2576,8 +2641,8 @@ static void enqueue_sample_rows(const SampleBufs& b, const float* logits, int n_
     const int g = std::min(n_rows * kTopPChunks, 2048);
     hipLaunchKernelGGL(k_topp_max, dim3(g), dim3(256), 0, st, none, n_rows, no_rows, logits, V, 0, no_cp, temp, b.pmax);
     for (int d = 0; d < 3; ++d) {
-      hipLaunchKernelGGL(k_topp_hist, dim3(g), dim3(256), 0, st, none, n_rows, no_rows, logits, V, 0, no_cp, temp,
-                         (const float*)b.pmax, d, (const uint32_t*)b.thr, b.hist);
+      hipLaunchKernelGGL(topp_hist_kernel(d), dim3(g), dim3(256), 0, st, none, n_rows, no_rows, logits, V, 0, no_cp,
+                         temp, (const float*)b.pmax, (const uint32_t*)b.thr, b.hist);
       hipLaunchKernelGGL(k_topp_pick, dim3(std::min(n_rows, 1024)), dim3(kTopPThreads), 0, st, none, n_rows, no_cp,
                          top_p, d, (const unsigned long long*)b.hist, b.thr, b.state, b.state + n_rows);
     }

@@ -27,6 +27,7 @@ def tokens(logits, rid, pos, seed, step, temp, top_p, shift=0, noalloc=False):
     (1, 5, 1.0, 1.0, 0), (1, 1024, 1.0, 1.0, 0), (1, 1025, 0.7, 1.0, 0), (1, 40001, 1.0, 1.0, 0), (1, 131072, 1.0, 1.0, 1),
     (3, 151936, 1.3, 1.0, 0), (65, 2052, 1.0, 1.0, 2), (70, 20484, 1.0, 1.0, 0), (5, 180000, 1.0, 1.0, 0),
     (1, 4096, 1.0, 0.9, 0), (63, 1000, 1.0, 0.8, 1), (65, 515, 0.7, 0.6, 0), (130, 2048, 1.0, 0.9, 0), (1030, 260, 1.0, 0.5, 0),
+    (3, 151936, 1.0, 0.9, 0), (2, 100002, 0.7, 0.95, 0), (1025, 8196, 1.0, 0.9, 0),
 ])
 def test_sampler_split(n, V, temp, top_p, shift):
     g = np.random.default_rng([n, V])
