@@ -196,7 +196,8 @@ int sara_refill(sara_ctx* ctx);
  * decisions follow every decode step and no round barrier reaches the
  * host).  Drives the step to completion: replays [decode, decide, refill]
  * from a HIP graph of graph_iters iterations, polling the done flag
- * asynchronously.
+ * asynchronously.  (bf16 models: from one of two graphs, by the live rows;
+ * same results.)
  * Synchronises before returning.  d_forced_tok as in sara_decode_step.
  * *iters_out receives the number of loop iterations enqueued. */
 int sara_run(sara_ctx* ctx, const int32_t* d_forced_tok, int32_t graph_iters,
@@ -317,7 +318,7 @@ int sara_sample_logits(const float* d_logits, int32_t n_rows, int32_t vocab,
 /* For callers that cannot allocate device memory (code under HIP graph
  * capture, tight serving loops, harnesses that forbid hipMalloc): the
  * sampler of sara_sample_logits with the same arguments and results, whose
- * buffers (row count, per-row chunk winners, top-p histograms and state)
+ * buffers (per-row chunk winners, top-p histograms and state)
  * live in one static device array per GPU of SARA_NOALLOC_SCRATCH_BYTES
  * bytes, held from the first call on a device until the process ends.  It
  * calls no allocating routine and does not synchronise: the work is

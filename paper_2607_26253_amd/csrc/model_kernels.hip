@@ -1234,8 +1234,8 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
 }
 
 // Fused q|k|v projection of the decode rows with the rotary / KV-append
-// epilogue (bf16 weights in rotation-pair order, see qkv_pair_col).  Block =
-// one 16-row weight tile; its 4 waves take a quarter of K each and stream
+// epilogue (bf16 weights in rotation-pair order, see qkv_pair_col).  Block = NT
+// 16-row weight tiles; its 4 waves take a quarter of K each and stream
 // their weight fragments and the activation fragments of up to 16*MT rows
 // through a D-stage register pipeline (the waves share no k range, so the
 // activations need no LDS staging).  The wave partial sums meet in LDS and
@@ -1243,14 +1243,14 @@ __global__ __launch_bounds__(256) void k_attention(const int32_t* __restrict__ M
 // activation tile t: rotate-half RoPE on q and k heads (the two members of
 // a rotation pair sit in lanes l and l ^ 32), q to qbuf as bf16, k and v to
 // the row's newest KV page (the attention kernel reads them from there).
-template <int HD, int MT, int D, int KS>
+template <int HD, int MT, int D, int KS, int NT>
 __device__ __forceinline__ void qkv_rope_mblock(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     int M, int m_base, int K, f32x4 (*red)[8][64], const RowDesc* __restrict__ rows,
     const float2* __restrict__ row_rope, int hq, int hkv, int layer, int64_t n_blocks,
     uint16_t* __restrict__ qbuf, uint16_t* __restrict__ kc, uint16_t* __restrict__ vc) {
   const int wave = threadIdx.x >> 6, lane = threadIdx.x & 63;
   const int row = lane & 15, grp = lane >> 4;
-  const int tile = blockIdx.x;
+  const int tile0 = blockIdx.x * NT;
   // KS = K / 128 32-wide k steps per wave; D divides KS, so the pipeline
   // issues D - 1 surplus (clamped, cache-hit) loads at most, none when D = KS
   static_assert(KS % D == 0, "pipeline depth must divide the k steps");
@@ -1258,7 +1258,7 @@ __device__ __forceinline__ void qkv_rope_mblock(const uint16_t* __restrict__ X, 
   // W in the wtiled_index layout: k step j of this wave sits in k block
   // (ks0 + j) / 2 (KS is even, so ks0 starts a block)
   const int wblock = ((hq + 2 * hkv) * HD / 16) * 1024;
-  const int woff = (ks0 / 2) * wblock + tile * 1024 + lane * 8;
+  const int woff = (ks0 / 2) * wblock + tile0 * 1024 + lane * 8;
   // activation fragments: X is fragment-major (tiled_index layout, as the
   // weights), so each fragment load of a wave is one contiguous 1 KiB read;
   // lanes of rows past M read rows of the last tile whose results are dropped
@@ -1270,13 +1270,12 @@ __device__ __forceinline__ void qkv_rope_mblock(const uint16_t* __restrict__ X, 
   // the row's newest-token KV slot and the rotation angles of its position.
   constexpr int TT = (MT + 3) / 4;
   constexpr int half = HD / 2;
-  const int c0 = tile * 16, h = c0 / HD, jt = (c0 % HD) >> 4;
   const bool second = grp >= 2;
-  const int dd = 8 * jt + 4 * (grp & 1);           // rotation index of the lane's first dim
-  const int nd = (second ? half : 0) + dd;          // its natural dim within the head
+  // rotation index of the lane's first dim in weight tile tile0 + n
+  const auto rot = [&](int n) { return 8 * (((tile0 + n) * 16 % HD) >> 4) + 4 * (grp & 1); };
   size_t pg_e[TT];
   int on_e[TT];
-  float2 cs_e[TT][4];
+  float2 cs_e[TT][NT][4];
 #pragma unroll
   for (int tt = 0; tt < TT; ++tt) {
     const int m = min(m_base + 16 * (wave + 4 * tt) + row, M - 1);
@@ -1285,17 +1284,23 @@ __device__ __forceinline__ void qkv_rope_mblock(const uint16_t* __restrict__ X, 
     pg_e[tt] = (size_t)layer * n_blocks + r.kv1 + (rel >> 4);
     on_e[tt] = rel & 15;
 #pragma unroll
-    for (int q = 0; q < 4; ++q) cs_e[tt][q] = row_rope[(size_t)m * half + dd + q];
-  }
-  struct Stage { u32x4 w; u32x4 x[MT]; };
-  Stage st[D];
-  f32x4 acc[MT];
+    for (int n = 0; n < NT; ++n)
 #pragma unroll
-  for (int t = 0; t < MT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+      for (int q = 0; q < 4; ++q) cs_e[tt][n][q] = row_rope[(size_t)m * half + rot(n) + q];
+  }
+  struct Stage { u32x4 w[NT]; u32x4 x[MT]; };
+  Stage st[D];
+  f32x4 acc[NT][MT];
+#pragma unroll
+  for (int n = 0; n < NT; ++n)
+#pragma unroll
+    for (int t = 0; t < MT; ++t) acc[n][t] = f32x4{0.f, 0.f, 0.f, 0.f};
   const int last = KS - 1;
   auto load = [&](Stage& sg, int step) {
     const int kk = max(min(step, last), 0);
-    sg.w = *(const u32x4*)(W + woff + (kk >> 1) * wblock + (kk & 1) * 512);
+#pragma unroll
+    for (int n = 0; n < NT; ++n)
+      sg.w[n] = *(const u32x4*)(W + woff + n * 1024 + (kk >> 1) * wblock + (kk & 1) * 512);
 #pragma unroll
     for (int t = 0; t < MT; ++t) sg.x[t] = *(const u32x4*)(X + xoff[t] + kk * 512);
   };
@@ -1303,8 +1308,10 @@ __device__ __forceinline__ void qkv_rope_mblock(const uint16_t* __restrict__ X, 
     if (step < KS) {
 #pragma unroll
       for (int t = 0; t < MT; ++t)
-        acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sg.w),
-                                                         __builtin_bit_cast(bf16x8, sg.x[t]), acc[t], 0, 0, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+          acc[n][t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, sg.w[n]),
+                                                              __builtin_bit_cast(bf16x8, sg.x[t]), acc[n][t], 0, 0, 0);
     }
   };
   if constexpr (D == KS) {
@@ -1325,60 +1332,68 @@ __device__ __forceinline__ void qkv_rope_mblock(const uint16_t* __restrict__ X, 
     }
   }
 #pragma unroll
-  for (int t = 0; t < MT; ++t) red[wave][t][lane] = acc[t];
-  __syncthreads();
+  for (int n = 0; n < NT; ++n) {
+    const int h = (tile0 + n) * 16 / HD;
+    const int nd = (second ? half : 0) + rot(n);      // natural dim of the lane's first value
 #pragma unroll
-  for (int tt = 0; tt < TT; ++tt) {
-    const int t = wave + 4 * tt;
-    if (t >= MT) break;
-    f32x4 v = red[0][t][lane];
-    v += red[1][t][lane];
-    v += red[2][t][lane];
-    v += red[3][t][lane];
-    f32x4 pv;
+    for (int t = 0; t < MT; ++t) red[wave][t][lane] = acc[n][t];
+    __syncthreads();
 #pragma unroll
-    for (int q = 0; q < 4; ++q) pv[q] = __shfl_xor(v[q], 32, 64);
-    const int m = m_base + 16 * t + row;
-    if (m >= M) continue;
-    float o[4];
-    if (h < hq + hkv) {
+    for (int tt = 0; tt < TT; ++tt) {
+      const int t = wave + 4 * tt;
+      if (t >= MT) break;
+      f32x4 v = red[0][t][lane];
+      v += red[1][t][lane];
+      v += red[2][t][lane];
+      v += red[3][t][lane];
+      f32x4 pv;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        const float2 c = cs_e[tt][q];
-        o[q] = second ? (v[q] * c.x + pv[q] * c.y) : (v[q] * c.x - pv[q] * c.y);
+      for (int q = 0; q < 4; ++q) pv[q] = __shfl_xor(v[q], 32, 64);
+      const int m = m_base + 16 * t + row;
+      if (m >= M) continue;
+      float o[4];
+      if (h < hq + hkv) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const float2 c = cs_e[tt][n][q];
+          o[q] = second ? (v[q] * c.x + pv[q] * c.y) : (v[q] * c.x - pv[q] * c.y);
+        }
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) o[q] = v[q];
       }
-    } else {
-#pragma unroll
-      for (int q = 0; q < 4; ++q) o[q] = v[q];
+      const uint32_t p01 = (uint32_t)f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16);
+      const uint32_t p23 = (uint32_t)f32_to_bf16(o[2]) | ((uint32_t)f32_to_bf16(o[3]) << 16);
+      const size_t pg = pg_e[tt];
+      const int on = on_e[tt];
+      if (h < hq) {
+        *(uint2*)(qbuf + ((size_t)m * hq + h) * HD + nd) = make_uint2(p01, p23);
+      } else if (h < hq + hkv) {
+        *(uint2*)(kc + ((pg * hkv + (h - hq)) * kBlockTok + on) * HD + nd) = make_uint2(p01, p23);
+      } else {
+        uint16_t* vp = vc + (pg * hkv + (h - hq - hkv)) * (size_t)HD * kBlockTok + on;
+        vp[(size_t)(nd + 0) * kBlockTok] = (uint16_t)(p01 & 0xFFFF);
+        vp[(size_t)(nd + 1) * kBlockTok] = (uint16_t)(p01 >> 16);
+        vp[(size_t)(nd + 2) * kBlockTok] = (uint16_t)(p23 & 0xFFFF);
+        vp[(size_t)(nd + 3) * kBlockTok] = (uint16_t)(p23 >> 16);
+      }
     }
-    const uint32_t p01 = (uint32_t)f32_to_bf16(o[0]) | ((uint32_t)f32_to_bf16(o[1]) << 16);
-    const uint32_t p23 = (uint32_t)f32_to_bf16(o[2]) | ((uint32_t)f32_to_bf16(o[3]) << 16);
-    const size_t pg = pg_e[tt];
-    const int on = on_e[tt];
-    if (h < hq) {
-      *(uint2*)(qbuf + ((size_t)m * hq + h) * HD + nd) = make_uint2(p01, p23);
-    } else if (h < hq + hkv) {
-      *(uint2*)(kc + ((pg * hkv + (h - hq)) * kBlockTok + on) * HD + nd) = make_uint2(p01, p23);
-    } else {
-      uint16_t* vp = vc + (pg * hkv + (h - hq - hkv)) * (size_t)HD * kBlockTok + on;
-      vp[(size_t)(nd + 0) * kBlockTok] = (uint16_t)(p01 & 0xFFFF);
-      vp[(size_t)(nd + 1) * kBlockTok] = (uint16_t)(p01 >> 16);
-      vp[(size_t)(nd + 2) * kBlockTok] = (uint16_t)(p23 & 0xFFFF);
-      vp[(size_t)(nd + 3) * kBlockTok] = (uint16_t)(p23 >> 16);
-    }
+    __syncthreads();   // red is reused by the next weight tile or m-block
   }
-  __syncthreads();   // red is reused by the next m-block
 }
 
-// Live row count read on the device.  Grid: x = one block per weight tile,
+// Live row count read on the device.  Grid: x = one block per NT weight tiles,
 // z = one block per 128 rows of the capacity.  The live 16-row activation
 // tiles are shared out in contiguous runs over the first min(gridDim.z,
 // zspread) z blocks (at most 8 tiles per block), so that a small batch keeps
 // several blocks per weight tile busy instead of one; zspread is chosen on
 // the host so that the whole grid's working blocks stay resident at once.
 // Every tile's arithmetic is the same whichever block computes it.
+// NT: 2 in the many-row loop, where the activation tiles read from L2 once per
+// weight tile are the bound (512 rows, d 2048, 2560 outputs: 27.5 us at one
+// weight tile a block, 22.6 at two), else 1 (few rows: twice the blocks).
 // KS = d_model / 128, one of 4, 8, 12, 16, 24, 32 (checked by sara_init).
-template <int HD, int KS>
+template <int HD, int KS, int NT>
 __global__ __launch_bounds__(256) void k_qkv_rope(const uint16_t* __restrict__ X, const uint16_t* __restrict__ W,
     const int32_t* __restrict__ M_ptr, int K, const RowDesc* __restrict__ rows,
     const float2* __restrict__ row_rope, int hq, int hkv, int layer, int64_t n_blocks,
@@ -1394,9 +1409,10 @@ __global__ __launch_bounds__(256) void k_qkv_rope(const uint16_t* __restrict__ X
     // of them from 16 on (the 16-step instance then fits two blocks per CU);
     // a half and a quarter of that for more rows
 #define SARA_QR(MT_, D_) \
-    if (mt == MT_) qkv_rope_mblock<HD, MT_, D_, KS>(X, W, M, m_base, K, red, rows, row_rope, hq, hkv, layer, \
-                                                    n_blocks, qbuf, kc, vc);
-    constexpr int D1 = KS < 16 ? KS : KS / 2, D3 = D1 / 2, D5 = D1 / 4;
+    if (mt == MT_) qkv_rope_mblock<HD, MT_, D_, KS, NT>(X, W, M, m_base, K, red, rows, row_rope, hq, hkv, layer, \
+                                                        n_blocks, qbuf, kc, vc);
+    // (two weight tiles: 4 and 2 steps, their registers hold no more)
+    constexpr int D1 = NT > 1 ? 4 : (KS < 16 ? KS : KS / 2), D3 = NT > 1 ? 4 : D1 / 2, D5 = NT > 1 ? 2 : D1 / 4;
     SARA_QR(1, D1) SARA_QR(2, D1) SARA_QR(3, D3) SARA_QR(4, D3)
     SARA_QR(5, D5) SARA_QR(6, D5) SARA_QR(7, D5) SARA_QR(8, D5)
 #undef SARA_QR
@@ -2368,10 +2384,14 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
     // q|k|v projection with the RoPE / KV-append epilogue, the paged
     // attention, then the merge of rows with several context splits
     PROF_B(c);
-#define SARA_QKV(KS_) \
-    launch_k(c, st, (k_qkv_rope<HD, KS_>), dim3(c->nqkv / 16, 1, (M_cap + 127) / 128), dim3(256), 0, \
+#define SARA_QKV_N(KS_, NT_) \
+    launch_k(c, st, (k_qkv_rope<HD, KS_, NT_>), dim3(c->nqkv / (16 * NT_), 1, (M_cap + 127) / 128), dim3(256), 0, \
              (const uint16_t*)x, (const uint16_t*)c->w_qkv[l], M_ptr, d, c->rows, c->row_rope, c->hq, c->hkv, l, \
-             c->n_blocks, (uint16_t*)c->qbuf, (uint16_t*)c->kc, (uint16_t*)c->vc, qkv_spread(c, k_qkv_rope<HD, KS_>))
+             c->n_blocks, (uint16_t*)c->qbuf, (uint16_t*)c->kc, (uint16_t*)c->vc, \
+             NT_ * qkv_spread(c, k_qkv_rope<HD, KS_, 1>))
+#define SARA_QKV(KS_) \
+    if (c->tile_rows) SARA_QKV_N(KS_, 2); \
+    else SARA_QKV_N(KS_, 1)
     switch (d / 128) {
       case 4: SARA_QKV(4); break;
       case 8: SARA_QKV(8); break;
@@ -2381,6 +2401,7 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
       default: SARA_QKV(32); break;
     }
 #undef SARA_QKV
+#undef SARA_QKV_N
     PROF_E(c, kPQkvRope, c->nqkv, d);
     PROF_B(c);
     const int cap = M_cap * c->dec_splits_max;
@@ -2390,7 +2411,9 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
              c->hq, c->hkv, c->dec_splits_max, 1.0f / sqrtf((float)HD), (const uint16_t*)c->qbuf, c->attn_part, x);
     PROF_E(c, kPAttn, 0, 0);
     PROF_B(c);
-    launch_k(c, st, (k_attn_combine<uint16_t, HD>), dim3(1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq,
+    // blocks of two waves: 1024 leave a CU 8 waves (512 rows of 16 heads: 14.0 us,
+    // 10.5 with 4096), but exit sooner where a few rows need no more
+    launch_k(c, st, (k_attn_combine<uint16_t, HD>), dim3(c->tile_rows ? 4096 : 1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq,
              c->hkv, c->dec_splits_max, kDecPages, 1, x);
     PROF_E(c, kPCombine, 0, 0);
     PROF_B(c);
