@@ -2429,8 +2429,10 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
     sp = gemm_decode(c, c->xa, c->w_d[l], M_ptr, M_cap, d, c->ffn, false);
     PROF_E(c, kPGemmN1, d, c->ffn);
     PROF_B(c);
-    // the next layer's norm (its q|k|v kernel reads fragment-major rows) or the final one
-    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d, l + 1 < c->L ? 1 : xt);
+    // the next layer's norm (its q|k|v kernel reads fragment-major rows) or the
+    // final one, in the order its reader takes: the tile LM head fragment-major,
+    // the few-row ones (the only form that writes logits for top-p) row-major
+    residual_norm_decode(c, M_ptr, M_cap, sp, c->norms + (size_t)(2 * l + 2) * d, l + 1 < c->L ? 1 : xt && !c->topp);
     PROF_E(c, kPResNorm, d, 0);
   }
 }

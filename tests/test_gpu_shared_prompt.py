@@ -54,14 +54,16 @@ def test_shared_prompt_splits_are_bit_identical(hq, hkv, hd, n0, prompts):
             assert bool(torch.isfinite(a).all()) and torch.equal(a, b), (key, t)
 
 
+@pytest.mark.parametrize("top_p,temperature", [(1.0, 1.0), (1.0, 0.7), (0.9, 1.0), (0.9, 0.7)])
 @pytest.mark.parametrize("width,n0,prompts", [((512, 8, 2, 64, 512), 8, 40), ((1024, 6, 1, 128, 1472), 7, 73)])
-def test_many_row_graph_is_bit_identical(width, n0, prompts):
+def test_many_row_graph_is_bit_identical(width, n0, prompts, top_p, temperature):
     """More than 256 live rows: sara_run replays the loop with the 256-row tile
     GEMMs, the eager calls run the few-row kernels; sampled tokens, logs and
     the state both leave behind are the same, also once rollouts have ended
-    and few rows are left."""
+    and few rows are left.  For both samplers, with and without a temperature."""
     lengths = [2 + (7 * u) % 60 for u in range(prompts)]
-    cfg = generic_cfg(*width, lengths, vocab=1008, k=8, n0=n0, budget_N=prompts * 8, max_new=40)
+    cfg = generic_cfg(*width, lengths, vocab=1008, k=8, n0=n0, budget_N=prompts * 8, max_new=40, top_p=top_p,
+                      temperature=temperature)
     cfg["alloc"].update(n_slots=prompts * n0, commit_min=8, forced_eos_u32=(1 << 32) // 24, pool_U=prompts)
     w, pool, seed = W.make_weights(cfg), W.pool_with_lengths(cfg, lengths), None
     out = []
