@@ -175,12 +175,7 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const uint16_t* __restrict
 #pragma unroll
       for (int n = 0; n < NT; n += 2) {
         if (tn + n >= ntl) continue;
-        float r[4];
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const float g = acc[n][m][q], u = acc[n + 1][m][q];
-          r[q] = silu_mul(g, u);
-        }
+        const f32x4 r = silu_mul(acc[n][m], acc[n + 1][m]);
         *(uint2*)(a.xa + tiled_index(m0 + 16 * m, (tn + n) * 8 + 4 * grp, F)) =
             make_uint2(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]));
       }

@@ -670,14 +670,9 @@ __device__ __forceinline__ void gemm_mblock(const uint16_t* __restrict__ X, cons
       for (int t = 0; t < MT; ++t) {
         int m = m_base + 16 * t + row;
         if (m < M) {
-          uint32_t pk[2];
-#pragma unroll
-          for (int q = 0; q < 4; q += 2) {
-            float g0 = acc[0][t][q], u0 = acc[NT - 1][t][q];
-            float g1 = acc[0][t][q + 1], u1 = acc[NT - 1][t][q + 1];
-            pk[q / 2] = pack_bf16(silu_mul(g0, u0), silu_mul(g1, u1));
-          }
-          *(uint2*)(o + (XT ? (size_t)tiled_index(m, f0, F) : (size_t)m * F + f0)) = make_uint2(pk[0], pk[1]);
+          const f32x4 r = silu_mul(acc[0][t], acc[NT - 1][t]);
+          *(uint2*)(o + (XT ? (size_t)tiled_index(m, f0, F) : (size_t)m * F + f0)) =
+              make_uint2(pack_bf16(r[0], r[1]), pack_bf16(r[2], r[3]));
         }
       }
     }

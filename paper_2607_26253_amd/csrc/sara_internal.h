@@ -386,9 +386,27 @@ __device__ __forceinline__ void sampler_key(uint64_t seed, int32_t step, uint32_
   k1 = (uint32_t)(seed >> 32) ^ (uint32_t)step;
 }
 
-// silu(g) * u on the hardware exponential and reciprocal (each within 1 ulp)
+// silu(g) u = g / (1 + exp(-g)) u.  The exponential e is the hardware's of the
+// rounded -g log2(e), and the reciprocal the hardware's; what the argument and
+// the sum lost by rounding (l, dl) goes into one correction of the quotient: at
+// most 1.4e-7 from silu(g), 3e-8 rms (expf and a division, half as many
+// instructions again: 1.8e-7 and 4e-8; without the correction 3.8e-6).  g of
+// -88 or less gives 0 (within 2e-36), an infinite one itself (s is then a NaN).
+// It costs a pool prefill (256 prompts, width 1536) 22.1 ms against 21.3, and with
+// expf and a division 22.6.
 __device__ __forceinline__ float silu_mul(float g, float u) {
-  return g * u * __builtin_amdgcn_rcpf(1.0f + __builtin_amdgcn_exp2f(-1.4426950408889634f * g));
+  constexpr float kL = 1.44269504f, kLlo = 1.92596299e-8f, kLn2 = 0.693147181f;   // log2(e) in two parts
+  const float a = __builtin_amdgcn_fmed3f(g, -87.0f, 128.0f);   // no overflow; e < 2^-126 is 0
+  const float h = -kL * a, l = fmaf(-kLlo, a, fmaf(-kL, a, -h));
+  const float e = __builtin_amdgcn_exp2f(h);
+  const float hi = fmaxf(1.0f, e), lo = fminf(1.0f, e), d = hi + lo;
+  const float dl = fmaf(e, l * kLn2, lo - (d - hi));
+  const float r = __builtin_amdgcn_rcpf(d), t = g * r;
+  const float s = fmaf(fmaf(-dl, t, fmaf(-d, t, g)), r, t);
+  return fminf(g < -88.0f ? -0.0f : s, fabsf(g)) * u;
+}
+__device__ __forceinline__ f32x4 silu_mul(f32x4 g, f32x4 u) {
+  return f32x4{silu_mul(g[0], u[0]), silu_mul(g[1], u[1]), silu_mul(g[2], u[2]), silu_mul(g[3], u[3])};
 }
 
 // SplitMix64 output finalizer (Steele, Lea, Flood, OOPSLA'14).
