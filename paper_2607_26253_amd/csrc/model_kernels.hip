@@ -1428,7 +1428,11 @@ __global__ __launch_bounds__(256) void k_qkv_rope(const uint16_t* __restrict__ X
 //   S^T = K q^T  (v_mfma_f32_16x16x32_bf16; G <= 8 query heads a row, 16
 //                 columns; lane (token l%16, k-group l/16) of K meets column l%16
 //                 of q over the same HD/4 dims, so the k order inside the MFMA is moot)
-//   softmax per column in base 2 over the 4 lanes holding its 32 scores
+//   softmax per column in base 2 over the 4 lanes holding its 32 scores.  The
+//                 maximum is kept as the base-2 value that was subtracted, so
+//                 that merging waves and splits adds no rounding of its own: at
+//                 scores near 100 weights scaled anew from the raw maxima were
+//                 8e-7 off on average, these are 2e-8
 //   O^T = V^T P^T (the score registers already have the B-operand layout, four
 //                 tokens of each page a lane, and transposed V pages give the A
 //                 operand; P enters as a bf16 hi + lo pair, so the product
@@ -1547,14 +1551,14 @@ __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict_
         mx = fmaxf(mx, fmaxf(fmaxf(sc[p][0], sc[p][1]), fmaxf(sc[p][2], sc[p][3])));
       mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
       mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
-      const float mc = mx * sl2;
+      mx *= sl2;
       u32x4 ph, plo;
 #pragma unroll
       for (int p = 0; p < 2; ++p)
 #pragma unroll
         for (int q = 0; q < 4; q += 2) {
-          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[p][q], sl2, -mc));
-          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[p][q + 1], sl2, -mc));
+          const float p0 = __builtin_amdgcn_exp2f(fmaf(sc[p][q], sl2, -mx));
+          const float p1 = __builtin_amdgcn_exp2f(fmaf(sc[p][q + 1], sl2, -mx));
           ls += p0 + p1;
           const uint32_t hi = pack_bf16(p0, p1);
           ph[2 * p + (q >> 1)] = hi;
@@ -1586,7 +1590,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict_
       float den = 0.f;
 #pragma unroll
       for (int w = 0; w < 4; ++w) {
-        const float wt = __builtin_amdgcn_exp2f((m_w[w][col] - m) * sl2);   // 0 for a wave without pages
+        const float wt = __builtin_amdgcn_exp2f(m_w[w][col] - m);   // 0 for a wave without pages
         num += wt * *(const f32x4*)&o_w[w][col][d4];
         den += wt * l_w[w][col];
       }
@@ -1597,7 +1601,7 @@ __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict_
         float* dst = part + ((((size_t)i * hkv + g) * n_splits + c) * kMaxGroup + head) * (HD + 2);
         *(float2*)(dst + d4) = make_float2(num[0], num[1]);
         *(float2*)(dst + d4 + 2) = make_float2(num[2], num[3]);
-        if (d4 == 0) *(float2*)(dst + HD) = make_float2(m * scale, den);
+        if (d4 == 0) *(float2*)(dst + HD) = make_float2(m, den);
       }
     }
     __syncthreads();   // LDS is reused by the next item
@@ -1610,13 +1614,15 @@ __global__ __launch_bounds__(256, 2) void k_attn_dec(const AttnItem* __restrict_
 // merge the context splits of every (row, query head) into o (model dtype)
 // skip_single: rows with one split were written by the attention kernel.
 // One pass over the splits, eight at a time with all their loads in flight,
-// rescaling the running (max, numerator, denominator) as it goes.
+// rescaling the running (max, numerator, denominator) as it goes.  Maxima are
+// natural in the fp32 attention's partials, base 2 in the bf16 one's.
 template <typename T, int HD>
 __global__ __launch_bounds__(HD) void k_attn_combine(const int32_t* __restrict__ M_ptr,
     const RowDesc* __restrict__ rows, const float* __restrict__ part, int hq, int hkv,
     int n_splits, int paged_splits, int skip_single, T* __restrict__ out) {
   // paged_splits: pages per context split of the paged (bf16) attention
   // kernels, 0 for the fp32 attention's token splits
+  const auto weight = [](float x) { return sizeof(T) == 2 ? __builtin_amdgcn_exp2f(x) : expf(x); };
   const int M = *M_ptr;
   for (int item = blockIdx.x; item < M * hq; item += gridDim.x) {
     const int i = item / hq, h = item - i * hq;
@@ -1652,12 +1658,12 @@ __global__ __launch_bounds__(HD) void k_attn_combine(const int32_t* __restrict__
       float m2 = mx;
 #pragma unroll
       for (int q = 0; q < 8; ++q) m2 = fmaxf(m2, pm[q]);
-      const float sc = (mx == -INFINITY) ? 0.f : expf(mx - m2);
+      const float sc = (mx == -INFINITY) ? 0.f : weight(mx - m2);
       num *= sc;
       den *= sc;
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        const float wgt = ((pm[q] == -INFINITY) ? 0.f : expf(pm[q] - m2)) * mk[q];
+        const float wgt = ((pm[q] == -INFINITY) ? 0.f : weight(pm[q] - m2)) * mk[q];
         num += wgt * po[q];
         den += wgt * pl_[q];
       }

@@ -27,8 +27,9 @@ namespace sara {
 //                 l / 16) receives the scores of keys 32 kg + 8 grp + j, j = 0..3
 //                 from a, 4..7 from b: exactly the B operand of the next product
 //   online softmax in base 2, one row per lane column (the 4 lanes of a row
-//                 exchange maxima; the sums meet at the end); O is rescaled
-//                 only when some row's maximum moved
+//                 exchange maxima; the sums meet at the end); the running maximum
+//                 is the base-2 value that was subtracted, so that alpha fits the
+//                 weights it rescales; O is rescaled only when some row's moved
 //   O^T += V^T P^T  P as a bf16 hi + lo pair (|p - hi - lo| <= 2^-16 p), so PV
 //                 has no bf16 rounding point; each lane keeps its own row's O,
 //                 so the rescale needs no exchange
@@ -138,14 +139,15 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_prefill(const int4* __restr
             for (int i = 0; i < 4; ++i)
               if (64 * kb + 32 * (e >> 1) + 8 * grp + 4 * (e & 1) + i > tq) s[n][e][i] = -INFINITY;
         }
-        float mx = m[n];
+        float mx = -INFINITY;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
           mx = fmaxf(mx, fmaxf(fmaxf(s[n][e][0], s[n][e][1]), fmaxf(s[n][e][2], s[n][e][3])));
         mx = fmaxf(mx, __shfl_xor(mx, 16, 64));
         mx = fmaxf(mx, __shfl_xor(mx, 32, 64));
+        mx = fmaxf(m[n], mx * scale_log2);
         if (__any(mx > m[n])) {
-          const float alpha = __builtin_amdgcn_exp2f((m[n] - mx) * scale_log2);
+          const float alpha = __builtin_amdgcn_exp2f(m[n] - mx);
           l[n] *= alpha;
 #pragma unroll
           for (int t = 0; t < NT; ++t)
@@ -153,14 +155,13 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_prefill(const int4* __restr
             for (int i = 0; i < 4; ++i) o[n][t][i] *= alpha;
           m[n] = mx;
         }
-        const float mc = mx * scale_log2;
         float ps = 0.f;
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
           for (int i = 0; i < 4; i += 2) {
-            const float p0 = __builtin_amdgcn_exp2f(fmaf(s[n][e][i], scale_log2, -mc));
-            const float p1 = __builtin_amdgcn_exp2f(fmaf(s[n][e][i + 1], scale_log2, -mc));
+            const float p0 = __builtin_amdgcn_exp2f(fmaf(s[n][e][i], scale_log2, -mx));
+            const float p1 = __builtin_amdgcn_exp2f(fmaf(s[n][e][i + 1], scale_log2, -mx));
             ps += p0 + p1;
             const uint32_t hi = pack_bf16(p0, p1);
             const uint32_t lo = pack_bf16(p0 - __uint_as_float(hi << 16), p1 - __uint_as_float(hi & 0xFFFF0000u));
@@ -204,13 +205,15 @@ __global__ __launch_bounds__(NW * 64, 2) void k_attn_prefill(const int4* __restr
     ls += __shfl_xor(ls, 16, 64);
     ls += __shfl_xor(ls, 32, 64);
     const float inv = 1.0f / ls;
+    // a / ls to fp32 accuracy: one correction of the product (three instructions, a division takes eleven)
+    const auto over = [&](float a) { const float q = a * inv; return fmaf(fmaf(-ls, q, a), inv, q); };
     const int tq = tb + 16 * n + row;
     if (tq >= nkeys) continue;
     const int r = row0 + tq - t0, c = (g * G + head) * HD + 4 * grp;
 #pragma unroll
     for (int t = 0; t < NT; ++t)
-      *(uint2*)(out + tiled_index(r, c + 16 * t, hq * HD)) = make_uint2(pack_bf16(o[n][t][0] * inv, o[n][t][1] * inv),
-                                          pack_bf16(o[n][t][2] * inv, o[n][t][3] * inv));
+      *(uint2*)(out + tiled_index(r, c + 16 * t, hq * HD)) = make_uint2(pack_bf16(over(o[n][t][0]), over(o[n][t][1])),
+                                          pack_bf16(over(o[n][t][2]), over(o[n][t][3])));
   }
 }
 
