@@ -222,14 +222,6 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   c->max_pos = ad->max_prompt + ad->max_new;
   c->Qcap = (int)std::min<int64_t>(ad->budget_N, (int64_t)c->U * c->k);
   c->elt = (md->dtype == SARA_BF16) ? 2 : 4;
-  // rows of a prefill chunk: a pool of up to kPrefillRowsBf16 prompt tokens
-  // runs as one chunk (long chunks fill the 256 x 256 tiles' grids)
-  c->prefill_rows = 4096;
-  if (md->dtype == SARA_BF16) {
-    const int64_t pool_rows = (int64_t)c->U * (ad->max_prompt - 1);
-    c->prefill_rows = (int)std::min<int64_t>(kPrefillRowsBf16, std::max<int64_t>(4096, (pool_rows + 255) / 256 * 256));
-  }
-  c->row_cap = (std::max(c->S, c->prefill_rows) + 15) / 16 * 16;   // whole 16-row fragments
   c->attn_splits_max = (c->max_pos + kAttnSplit - 1) / kAttnSplit;
   c->dec_splits_max = (c->MAXB + kDecPages - 1) / kDecPages;
   {
@@ -237,14 +229,14 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
     // falls back to one split when its partials would not fit)
     if (md->dtype == SARA_BF16) {
       // decode: the o and down projections (<= kMaxSplitsDec splits of
-      // [S][d]); prefill: q|k|v, o and down over a short chunk (a long one
-      // writes no partials).  The LM head, the gate|up projection and the
-      // q|k|v projection of decode write no partials.
+      // [S][d]); prefill: q|k|v, o and down over a chunk too short to fill the
+      // GPU without splits (no more of them than fit here).  The LM head, the
+      // gate|up projection and the q|k|v projection of decode write no partials.
       const int64_t npf = std::max<int64_t>(c->nqkv, c->d);
-      c->ws_floats = std::max<int64_t>((int64_t)kMaxSplitsDec * c->S * c->d, 2 * (int64_t)4096 * npf);
+      c->ws_floats = std::max<int64_t>((int64_t)kMaxSplitsDec * c->S * c->d, 2 * (int64_t)kPrefillRows * npf);
     } else {
       // fp32: the o and down outputs [rows][d], the logits [S][V]
-      c->ws_floats = std::max<int64_t>((int64_t)c->S * std::max(c->V, c->d), (int64_t)c->prefill_rows * c->d);
+      c->ws_floats = std::max<int64_t>((int64_t)c->S * std::max(c->V, c->d), (int64_t)kPrefillRows * c->d);
     }
   }
   const size_t E = (size_t)c->elt;
@@ -282,7 +274,6 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->off, sizeof(int32_t) * (c->U + 1));
   ALLOC(c->pre, sizeof(int32_t) * (c->U + 1));
   ALLOC(c->p, sizeof(double) * c->U);
-  if (md->dtype == SARA_BF16) ALLOC(c->pf_tiles, sizeof(int4) * (size_t)max_prefill_tiles(c));
   ALLOC(c->flen, sizeof(int32_t) * (size_t)c->U * c->k);
   // controller
   ALLOC(c->ctl, sizeof(Ctl));
@@ -316,19 +307,8 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->log_draw, sizeof(int64_t) * 2 * c->cap_draw);
   ALLOC(c->log_asg, sizeof(int64_t) * 4 * c->cap_asg);
   ALLOC(c->log_fin, sizeof(int64_t) * 6 * c->cap_fin);
-  // activations
-  ALLOC(c->rows, sizeof(RowDesc) * c->row_cap);
   ALLOC(c->rows_M, sizeof(int32_t));
-  ALLOC(c->h, sizeof(float) * (size_t)c->row_cap * d);
-  ALLOC(c->x, (size_t)c->row_cap * std::max(c->d, c->qdim) * E);
-  ALLOC(c->qbuf, (size_t)c->row_cap * c->qdim * E);
-  ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
   ALLOC(c->ws, sizeof(float) * (size_t)c->ws_floats);
-  // context-split partials: fp32 attention (every row), bf16 decode rows
-  ALLOC(c->attn_part, sizeof(float) *
-                          (size_t)(md->dtype == SARA_BF16 ? (int64_t)c->S * c->dec_splits_max
-                                                          : (int64_t)c->row_cap * c->attn_splits_max) *
-                          c->hkv * kMaxGroup * (c->hd + 2));
   // per (row, vocabulary chunk) winners: kSampleChunks chunks (fp32 models),
   // one per 128-id block of the fused LM-head sampler (bf16 models)
   const size_t nchunk = std::max<size_t>(kSampleChunks, (size_t)(c->V + 127) / 128);
@@ -348,6 +328,31 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->g_r, sizeof(float) * nroll);
   ALLOC(c->g_adv, sizeof(float) * nroll);
   ALLOC(c->g_n, sizeof(int32_t));
+  // Activations, for the rows of a prefill chunk.  A bf16 model's pool of up to
+  // kPrefillRowsBf16 prompt tokens runs as one chunk (long chunks fill the 256 x
+  // 256 tiles' grids: 82,000 tokens of width 1536 22.6 ms, 24.0 in chunks of 8,192),
+  // as long as the chunk takes no more than a quarter of the memory that is left.
+  const size_t row_bytes = sizeof(RowDesc) + sizeof(float) * d + (std::max(c->d, c->qdim) + c->qdim + (size_t)c->ffn) * E;
+  c->prefill_rows = kPrefillRows;
+  if (md->dtype == SARA_BF16) {
+    const int64_t pool_rows = ((int64_t)c->U * (ad->max_prompt - 1) + 255) / 256 * 256;
+    size_t left = 0, total = 0;
+    if (hipMemGetInfo(&left, &total) != hipSuccess) left = 0;
+    const int64_t fit = (int64_t)(left / 4 / row_bytes) / 256 * 256;
+    c->prefill_rows = (int)std::max<int64_t>(kPrefillRows, std::min({(int64_t)kPrefillRowsBf16, pool_rows, fit}));
+  }
+  c->row_cap = (std::max(c->S, c->prefill_rows) + 15) / 16 * 16;   // whole 16-row fragments
+  ALLOC(c->rows, sizeof(RowDesc) * c->row_cap);
+  ALLOC(c->h, sizeof(float) * (size_t)c->row_cap * d);
+  ALLOC(c->x, (size_t)c->row_cap * std::max(c->d, c->qdim) * E);
+  ALLOC(c->qbuf, (size_t)c->row_cap * c->qdim * E);
+  ALLOC(c->xa, (size_t)c->row_cap * c->ffn * E);
+  if (md->dtype == SARA_BF16) ALLOC(c->pf_tiles, sizeof(int4) * (size_t)max_prefill_tiles(c));
+  // context-split partials: fp32 attention (every row), bf16 decode rows
+  ALLOC(c->attn_part, sizeof(float) *
+                          (size_t)(md->dtype == SARA_BF16 ? (int64_t)c->S * c->dec_splits_max
+                                                          : (int64_t)c->row_cap * c->attn_splits_max) *
+                          c->hkv * kMaxGroup * (c->hd + 2));
 #undef ALLOC
   {
     hipError_t e = hipHostMalloc((void**)&c->h_done, 6 * sizeof(int32_t), hipHostMallocDefault);

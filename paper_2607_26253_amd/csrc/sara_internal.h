@@ -20,7 +20,8 @@ constexpr int kAttnSplit = 256;      // tokens per context split (fp32 VALU atte
 constexpr int kDecPpw = 2;           // KV pages per wave in the decode attention
 constexpr int kDecPages = 4 * kDecPpw;  // KV pages per context split in the decode attention
 constexpr int kMaxSplitsDec = 12;    // split-K partials of a decode GEMM (summed in one batch; a multiple of 4)
-constexpr int kPrefillRowsBf16 = 32768;  // most rows of a prefill chunk of a bf16 model
+constexpr int kPrefillRows = 4096;   // rows of a prefill chunk
+constexpr int kPrefillRowsBf16 = 32768;  // most rows of one of a bf16 model, where memory allows
 constexpr int kTileRows = 256;       // decode batches beyond this many rows take 256-row GEMM tiles
 constexpr int kAttnTile = 64;        // tokens per LDS tile inside a split
 constexpr int kSampleChunks = 16;    // vocabulary chunks per sampled row

@@ -89,3 +89,38 @@ def test_f32_layers(width, lengths, max_new):
     worst = max(float(np.max(np.abs(gpu["logits"][t][s] - ora["logits"][key]))) for (t, s), key in slot_rows(gpu).items())
     print(f"[f32] {width}: max |dlogit| {worst:.2e}", flush=True)
     assert worst <= 1e-4
+
+
+def test_prefill_chunk_fits_the_memory_left():
+    """Little device memory left: the context takes a smaller prefill chunk
+    than it would use otherwise, and its logits agree."""
+    import torch
+
+    import paper_2607_26253_amd as sara
+    lengths = [600] + [120 + u for u in range(63)]      # 9,900 tokens
+    cfg = generic_cfg(512, 8, 1, 64, 65536, lengths, vocab=512)
+    pool = W.pool_with_lengths(cfg, lengths)            # of 38,336 at most: a chunk of 32,768 rows would take 4.5 GB
+    g = torch.Generator(device="cuda").manual_seed(11)
+    w = [(torch.randn(shape, generator=g, device="cuda") * 0.02 if len(shape) == 2 else torch.ones(shape, device="cuda"))
+         .to(torch.bfloat16) for _, shape in W.weight_specs(cfg["model"])]
+    need = 2 * sum(t.numel() for t in w)      # the context's copy
+    out = []
+    for short in (False, True):
+        torch.cuda.empty_cache()
+        hold = None
+        if short:
+            free = torch.cuda.mem_get_info()[0]
+            # 3.5 GB left for the rest: a chunk of about 6,000 rows
+            hold = torch.empty(free - need - (7 << 29), dtype=torch.uint8, device="cuda")
+        ctx = sara.Sara(cfg["model"], cfg["alloc"], W.sampling_seed(cfg), [t.view(torch.int16) for t in w])
+        d_tok, d_p = torch.from_numpy(pool["tokens"]).cuda(), torch.from_numpy(pool["p"]).cuda()
+        ctx.sara_begin_step(d_tok, pool["offsets"], d_p, None, 0)
+        buf = torch.zeros((cfg["alloc"]["n_slots"], 512), dtype=torch.float32, device="cuda")
+        ctx.sara_decode_step(None, buf)
+        out.append(buf.cpu().numpy().astype(np.float64))
+        ctx.close()
+        del hold
+    a, b = out
+    assert np.isfinite(a).all() and np.abs(a).max() > 0
+    # other K splits of the prefill's o and down: other bf16 roundings, as against the oracle
+    assert np.linalg.norm(a - b) <= 1e-2 * np.linalg.norm(a)
