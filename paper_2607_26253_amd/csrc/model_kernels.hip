@@ -2083,12 +2083,14 @@ __device__ __forceinline__ bool forced_eos_fires(uint64_t seed, int32_t step, in
 __global__ __launch_bounds__(256) void k_sample_final(const Ctl* __restrict__ ctl,
     const RowDesc* __restrict__ rows, const float* __restrict__ best,
     const int32_t* __restrict__ bidx, int nchunks, int cstride, int rstride, const int32_t* __restrict__ forced,
-    const int32_t* __restrict__ flen, int model_free, const CtlParams* __restrict__ cpp,
+    const int32_t* const* __restrict__ forced_at, const int32_t* __restrict__ flen, int model_free,
+    const CtlParams* __restrict__ cpp,
     const double* __restrict__ p, int32_t* __restrict__ out_tok, int32_t* __restrict__ samp_tok,
     int32_t* __restrict__ slot_gen, int32_t* __restrict__ slot_tok, uint64_t* __restrict__ slot_hash,
     int32_t* __restrict__ fin, int32_t* __restrict__ r_len, int32_t* __restrict__ r_reward) {
   __shared__ float sb[256];
   __shared__ int si[256];
+  if (forced_at) forced = *forced_at;                      // captured loop: the table of the running sara_run
   const int M = ctl->done ? 0 : ctl->M;
   for (int i = blockIdx.x; i < M; i += gridDim.x) {
     float bs = -INFINITY;
@@ -2551,7 +2553,7 @@ static void launch_topp_decode(sara_ctx* c, hipStream_t st, const float* lg, int
   PROF_E(c, kPSampleP, c->V, 0);
 }
 
-int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_free) {
+int launch_decode(sara_ctx* c, const int32_t* forced, const int32_t* const* forced_at, float* logits, int model_free) {
   hipStream_t st = c->stream;
   const int S = c->S;
   PROF_B(c);
@@ -2626,7 +2628,7 @@ int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_f
   // the top-p passes), [chunk][S] from the fused LM head
   const bool fused = !model_free && c->md.dtype == SARA_BF16 && !c->topp;
   launch_k(c, st, k_sample_final, dim3(std::min(S, 1024)), dim3(256), 0, c->ctl, c->rows,
-                     c->samp_best, c->samp_idx, nchunks, fused ? S : 1, fused ? 1 : nchunks, forced, c->flen,
+                     c->samp_best, c->samp_idx, nchunks, fused ? S : 1, fused ? 1 : nchunks, forced, forced_at, c->flen,
                      model_free,
                      (const CtlParams*)c->cp_dev, c->p, c->out_tok, c->samp_tok, c->slot_gen, c->slot_tok, c->slot_hash, c->fin,
                      c->r_len, c->r_reward);

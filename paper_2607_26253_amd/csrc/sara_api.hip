@@ -328,6 +328,7 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->g_r, sizeof(float) * nroll);
   ALLOC(c->g_adv, sizeof(float) * nroll);
   ALLOC(c->g_n, sizeof(int32_t));
+  ALLOC(c->forced_dev, sizeof(*c->forced_dev));
   // Activations, for the rows of a prefill chunk.  A bf16 model's pool of up to
   // kPrefillRowsBf16 prompt tokens runs as one chunk (long chunks fill the 256 x
   // 256 tiles' grids: 82,000 tokens of width 1536 22.6 ms, 24.0 in chunks of 8,192),
@@ -358,6 +359,8 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
     hipError_t e = hipHostMalloc((void**)&c->h_done, 6 * sizeof(int32_t), hipHostMallocDefault);
     if (e != hipSuccess) { sara_destroy(c); return hip_fail(e, "hipHostMalloc"); }
     memset(c->h_done, 0, 6 * sizeof(int32_t));
+    e = hipHostMalloc((void**)&c->h_forced, sizeof(*c->h_forced), hipHostMallocDefault);
+    if (e != hipSuccess) { sara_destroy(c); return hip_fail(e, "hipHostMalloc"); }
   }
 
   hipStream_t st = c->stream;
@@ -524,7 +527,7 @@ extern "C" int sara_decode_step(sara_ctx* c, const int32_t* d_forced_tok, float*
   if (!c->in_step) { set_error("sara_decode_step before sara_begin_step"); return SARA_ESTATE; }
   if (model_free && !d_forced_tok) return einval("model_free needs a forced-token table");
   c->prof_active = c->prof_enabled && !c->capturing;
-  launch_decode(c, d_forced_tok, d_logits, model_free);
+  launch_decode(c, d_forced_tok, nullptr, d_logits, model_free);
   HIP_TRY(hipGetLastError(), "decode launch");
   if (c->prof_active) {
     c->prof_active = false;
@@ -590,14 +593,14 @@ static void drop_graph(sara_ctx::LoopGraph& g) {
   g = sara_ctx::LoopGraph{};
 }
 
-static int build_graph(sara_ctx* c, sara_ctx::LoopGraph& g, bool tile_rows, const int32_t* forced, int iters) {
+static int build_graph(sara_ctx* c, sara_ctx::LoopGraph& g, bool tile_rows, int iters) {
   drop_graph(g);
   HIP_TRY(hipStreamBeginCapture(c->stream, hipStreamCaptureModeThreadLocal), "begin capture");
   c->capturing = true;
   c->prof_active = false;
   c->tile_rows = tile_rows;
   for (int i = 0; i < iters; ++i) {
-    launch_decode(c, forced, nullptr, 0);
+    launch_decode(c, nullptr, c->forced_dev, nullptr, 0);
     launch_decide_refill(c);
   }
   c->tile_rows = false;
@@ -605,7 +608,6 @@ static int build_graph(sara_ctx* c, sara_ctx::LoopGraph& g, bool tile_rows, cons
   HIP_TRY(hipStreamEndCapture(c->stream, &g.graph), "end capture");
   HIP_TRY(hipGraphInstantiate(&g.exec, g.graph, nullptr, nullptr, 0), "graph instantiate");
   g.iters = iters;
-  g.forced = forced;
   return SARA_OK;
 }
 
@@ -618,6 +620,9 @@ extern "C" int sara_run(sara_ctx* c, const int32_t* d_forced_tok, int32_t graph_
   HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming), "event");
   HIP_TRY(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming), "event");
   memset(c->h_done, 0, 6 * sizeof(int32_t));
+  *c->h_forced = d_forced_tok;   // the last run's copy is done: every run ends with a wait
+  HIP_TRY(hipMemcpyAsync(c->forced_dev, c->h_forced, sizeof(*c->h_forced), hipMemcpyHostToDevice, c->stream),
+          "forced table");
   int64_t iters = 0;
   int n = 0;
   int rc = SARA_OK;
@@ -628,8 +633,8 @@ extern "C" int sara_run(sara_ctx* c, const int32_t* d_forced_tok, int32_t graph_
     // row count, with bit-identical results; only the speed differs.
     const bool many = c->md.dtype == SARA_BF16 && c->run_M > kTileRows;
     sara_ctx::LoopGraph& g = c->loop_graph[many ? 1 : 0];
-    if (!g.exec || g.iters != graph_iters || g.forced != d_forced_tok) {
-      rc = build_graph(c, g, many, d_forced_tok, graph_iters);
+    if (!g.exec || g.iters != graph_iters) {
+      rc = build_graph(c, g, many, graph_iters);
       if (rc) break;
     }
     hipError_t e = hipGraphLaunch(g.exec, c->stream);
@@ -840,6 +845,7 @@ extern "C" void sara_destroy(sara_ctx* c) {
   (void)hipStreamSynchronize(c->stream);
   for (auto& g : c->loop_graph) drop_graph(g);
   if (c->h_done) (void)hipHostFree(c->h_done);
+  if (c->h_forced) (void)hipHostFree(c->h_forced);
   for (hipEvent_t e : c->prof_events) (void)hipEventDestroy(e);
   for (void* p : c->owned) (void)hipFree(p);
   delete c;

@@ -218,10 +218,13 @@ struct sara_ctx {
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
     int iters = 0;
-    const int32_t* forced = nullptr;
   } loop_graph[2];
   int run_M = 0;                  // live rows as last known to the host
   bool tile_rows = false;         // launch_decode uses the tile GEMMs (capture of loop_graph[1])
+  // forced-token table of the current sara_run, read through memory: the graphs
+  // serve every table
+  const int32_t** forced_dev = nullptr;
+  const int32_t** h_forced = nullptr;   // pinned
   int32_t* h_done = nullptr;      // pinned: 2 x (done flag, error word, live rows)
 
   std::vector<void*> owned;       // device allocations freed by sara_destroy
@@ -285,7 +288,7 @@ void residual_norm_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap, int sp, co
 void launch_qkv_epilogue_bf16(sara_ctx* c, const int32_t* M_ptr, int M, int sp, int layer);
 // launchers (model)
 int launch_prefill(sara_ctx* c);
-int launch_decode(sara_ctx* c, const int32_t* forced, float* logits, int model_free);
+int launch_decode(sara_ctx* c, const int32_t* forced, const int32_t* const* forced_at, float* logits, int model_free);
 // launchers (controller)
 int launch_reset(sara_ctx* c);
 int launch_decide(sara_ctx* c);

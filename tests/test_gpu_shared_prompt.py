@@ -86,3 +86,34 @@ def test_many_row_graph_is_bit_identical(width, n0, prompts, top_p, temperature)
         assert np.array_equal(ra[key], rb[key]), key
     for key in la:
         assert np.array_equal(la[key], lb[key]), key
+
+
+@pytest.mark.parametrize("graph_iters", [1, 5])
+def test_run_follows_the_table_of_each_call(graph_iters):
+    """One context, captured loops kept: every sara_run takes the forced table
+    (or none) of its own call."""
+    lengths = [3 + u for u in range(12)]
+    cfg = generic_cfg(512, 4, 2, 64, 512, lengths, k=2, n0=2, budget_N=24, max_new=9)
+    cfg["model"]["eos_id"] = -1
+    cfg["alloc"].update(n_slots=24)
+    w, pool = W.make_weights(cfg), W.pool_with_lengths(cfg, lengths)
+    ctx, _ = device_setup(cfg, w)
+    d_tok, d_p, _ = upload_pool(pool)
+    g = np.random.default_rng(4)
+    a, b = (torch.from_numpy(g.integers(0, 500, (24, 9)).astype(np.int32)).cuda() for _ in range(2))
+
+    def tokens(table, graph=True):
+        ctx.sara_begin_step(d_tok, pool["offsets"], d_p, None, 0)
+        if graph:
+            ctx.sara_run(table, graph_iters=graph_iters)
+        else:
+            while not ctx.sara_query()["done"]:
+                ctx.sara_decode_step(table)
+                ctx.sara_posterior_decide()
+                ctx.sara_refill()
+        return ctx.read_rollouts()["tokens"]
+
+    free = tokens(None, graph=False)
+    for table in (a, b, None, a, None, b):
+        assert np.array_equal(tokens(table), free if table is None else table.cpu().numpy())
+    ctx.close()
