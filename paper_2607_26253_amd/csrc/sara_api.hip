@@ -124,6 +124,23 @@ int prof_collect(sara_ctx* c) {
 }  // namespace sara
 
 
+// Live rows beyond which the captured loop of a bf16 model takes the 256 x 256
+// tile GEMMs.  A tile launch costs about the same for every row of its last row
+// tile and has a fixed part that few blocks cannot hide, so the bound falls with
+// the weights a launch multiplies (mean of gate|up, down and, at top_p = 1, the
+// LM head): whole loop against the few-row one, 1536 wide, 2 layers, 32768 ids
+// 1.03 at 426 rows (0.94 at 320, 1.01 at 384), 1 layer, 151936 ids 1.00 at 338
+// (0.96 at 306); 2048 wide, 32768 ids 1.09 at 368 (0.98 at 320); 4096 wide 1.04 at
+// 303.  Up to 1024 wide, where K is 32 steps at most, the tiles lose wherever the
+// last row tile is nearly empty (0.85-0.97 at 513, 769 and 1025 rows, 0.93-1.13 at
+// 2050) and gain from nine row tiles on (0.99-1.11 at 2306, 1.03-1.15 at 3074).
+static int many_rows(const sara_ctx* c) {
+  const double layer = 3.0 * c->ffn * c->d;
+  const double mean = c->topp ? layer / 2.0 : (c->L * layer + (double)c->V * c->d) / (2 * c->L + 1);
+  const double rows = 288.0 + 4.5e9 / mean;
+  return (int)std::min(std::max(rows, c->d < 1536 ? 2304.0 : 0.0), 1e9);
+}
+
 static int dmalloc(void** p, size_t bytes, std::vector<void*>& owned) {
   if (bytes == 0) bytes = 16;
   hipError_t e = hipMalloc(p, bytes);
@@ -315,6 +332,7 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   ALLOC(c->samp_best, sizeof(float) * (size_t)c->S * nchunk);
   ALLOC(c->samp_idx, sizeof(int32_t) * (size_t)c->S * nchunk);
   c->topp = c->ad.top_p < 1.0f;
+  c->many_rows = many_rows(c);
   // nucleus sampling reads fp32 logits; the bf16 LM head writes them here
   if (c->topp && c->md.dtype == SARA_BF16) ALLOC(c->topp_logits, sizeof(float) * (size_t)c->S * c->V);
   if (c->topp) {
@@ -628,10 +646,10 @@ extern "C" int sara_run(sara_ctx* c, const int32_t* d_forced_tok, int32_t graph_
   int rc = SARA_OK;
   volatile int32_t* h = c->h_done;   // per slot: done flag, error word, live rows
   while (iters < max_iters) {
-    // The loop with the tile GEMMs for more than kTileRows live rows, as known
+    // The loop with the tile GEMMs for more than many_rows live rows, as known
     // when the launch before the last one ended.  Either graph is right for any
     // row count, with bit-identical results; only the speed differs.
-    const bool many = c->md.dtype == SARA_BF16 && c->run_M > kTileRows;
+    const bool many = c->md.dtype == SARA_BF16 && c->run_M > c->many_rows;
     sara_ctx::LoopGraph& g = c->loop_graph[many ? 1 : 0];
     if (!g.exec || g.iters != graph_iters) {
       rc = build_graph(c, g, many, graph_iters);

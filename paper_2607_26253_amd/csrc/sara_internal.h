@@ -22,7 +22,6 @@ constexpr int kDecPages = 4 * kDecPpw;  // KV pages per context split in the dec
 constexpr int kMaxSplitsDec = 12;    // split-K partials of a decode GEMM (summed in one batch; a multiple of 4)
 constexpr int kPrefillRows = 4096;   // rows of a prefill chunk
 constexpr int kPrefillRowsBf16 = 32768;  // most rows of one of a bf16 model, where memory allows
-constexpr int kTileRows = 256;       // decode batches beyond this many rows take 256-row GEMM tiles
 constexpr int kAttnTile = 64;        // tokens per LDS tile inside a split
 constexpr int kSampleChunks = 16;    // vocabulary chunks per sampled row
 constexpr int kTopPChunks = 16;      // vocabulary chunks per row in the top-p passes
@@ -213,13 +212,14 @@ struct sara_ctx {
   int32_t* g_n = nullptr;         // committed count used for the CSR
 
   // graph replay: the loop captured with the few-row kernels [0] and, for
-  // batches of more than kTileRows live rows, the 256 x 256 tile GEMMs [1]
+  // batches of more than many_rows live rows, the 256 x 256 tile GEMMs [1]
   struct LoopGraph {
     hipGraphExec_t exec = nullptr;
     hipGraph_t graph = nullptr;
     int iters = 0;
   } loop_graph[2];
   int run_M = 0;                  // live rows as last known to the host
+  int many_rows = 0;
   bool tile_rows = false;         // launch_decode uses the tile GEMMs (capture of loop_graph[1])
   // forced-token table of the current sara_run, read through memory: the graphs
   // serve every table

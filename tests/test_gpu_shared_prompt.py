@@ -55,12 +55,13 @@ def test_shared_prompt_splits_are_bit_identical(hq, hkv, hd, n0, prompts):
 
 
 @pytest.mark.parametrize("top_p,temperature", [(1.0, 1.0), (1.0, 0.7), (0.9, 1.0), (0.9, 0.7)])
-@pytest.mark.parametrize("width,n0,prompts", [((512, 8, 2, 64, 512), 8, 40), ((1024, 6, 1, 128, 1472), 7, 73)])
+@pytest.mark.parametrize("width,n0,prompts", [((1536, 6, 2, 64, 8960), 7, 120), ((1024, 6, 1, 128, 4096), 8, 400)])
 def test_many_row_graph_is_bit_identical(width, n0, prompts, top_p, temperature):
-    """More than 256 live rows: sara_run replays the loop with the 256-row tile
-    GEMMs, the eager calls run the few-row kernels; sampled tokens, logs and
-    the state both leave behind are the same, also once rollouts have ended
-    and few rows are left.  For both samplers, with and without a temperature."""
+    """Many live rows (840 of a wide model, 3,200 of a narrow one): sara_run
+    replays the loop with the 256-row tile GEMMs, the eager calls run the
+    few-row kernels; sampled tokens, logs and the state both leave behind are
+    the same, also once rollouts have ended and few rows are left.  For both
+    samplers, with and without a temperature."""
     lengths = [2 + (7 * u) % 60 for u in range(prompts)]
     cfg = generic_cfg(*width, lengths, vocab=1008, k=8, n0=n0, budget_N=prompts * 8, max_new=40, top_p=top_p,
                       temperature=temperature)
