@@ -356,9 +356,10 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
   if (md->dtype == SARA_BF16) {
     const int64_t pool_rows = ((int64_t)c->U * (ad->max_prompt - 1) + 255) / 256 * 256;
     size_t left = 0, total = 0;
-    if (hipMemGetInfo(&left, &total) != hipSuccess) left = 0;
-    const int64_t fit = (int64_t)(left / 4 / row_bytes) / 256 * 256;
-    c->prefill_rows = (int)std::max<int64_t>(kPrefillRows, std::min({(int64_t)kPrefillRowsBf16, pool_rows, fit}));
+    if (pool_rows > kPrefillRows && hipMemGetInfo(&left, &total) == hipSuccess) {
+      const int64_t fit = (int64_t)(left / 4 / row_bytes) / 256 * 256;
+      c->prefill_rows = (int)std::max<int64_t>(kPrefillRows, std::min({(int64_t)kPrefillRowsBf16, pool_rows, fit}));
+    }
   }
   c->row_cap = (std::max(c->S, c->prefill_rows) + 15) / 16 * 16;   // whole 16-row fragments
   ALLOC(c->rows, sizeof(RowDesc) * c->row_cap);
@@ -374,11 +375,9 @@ extern "C" int sara_init(const sara_model_desc* md, const sara_alloc_desc* ad,
                           c->hkv * kMaxGroup * (c->hd + 2));
 #undef ALLOC
   {
-    hipError_t e = hipHostMalloc((void**)&c->h_done, 6 * sizeof(int32_t), hipHostMallocDefault);
+    hipError_t e = hipHostMalloc((void**)&c->h_poll, sizeof(*c->h_poll), hipHostMallocDefault);
     if (e != hipSuccess) { sara_destroy(c); return hip_fail(e, "hipHostMalloc"); }
-    memset(c->h_done, 0, 6 * sizeof(int32_t));
-    e = hipHostMalloc((void**)&c->h_forced, sizeof(*c->h_forced), hipHostMallocDefault);
-    if (e != hipSuccess) { sara_destroy(c); return hip_fail(e, "hipHostMalloc"); }
+    memset(c->h_poll, 0, sizeof(*c->h_poll));
   }
 
   hipStream_t st = c->stream;
@@ -637,14 +636,14 @@ extern "C" int sara_run(sara_ctx* c, const int32_t* d_forced_tok, int32_t graph_
   hipEvent_t ev[2];
   HIP_TRY(hipEventCreateWithFlags(&ev[0], hipEventDisableTiming), "event");
   HIP_TRY(hipEventCreateWithFlags(&ev[1], hipEventDisableTiming), "event");
-  memset(c->h_done, 0, 6 * sizeof(int32_t));
-  *c->h_forced = d_forced_tok;   // the last run's copy is done: every run ends with a wait
-  HIP_TRY(hipMemcpyAsync(c->forced_dev, c->h_forced, sizeof(*c->h_forced), hipMemcpyHostToDevice, c->stream),
+  memset(c->h_poll->done, 0, sizeof(c->h_poll->done));
+  c->h_poll->forced = d_forced_tok;   // the last run's copy is done: every run ends with a wait
+  HIP_TRY(hipMemcpyAsync(c->forced_dev, &c->h_poll->forced, sizeof(c->h_poll->forced), hipMemcpyHostToDevice, c->stream),
           "forced table");
   int64_t iters = 0;
   int n = 0;
   int rc = SARA_OK;
-  volatile int32_t* h = c->h_done;   // per slot: done flag, error word, live rows
+  volatile int32_t* h = c->h_poll->done;   // per slot: done flag, error word, live rows
   while (iters < max_iters) {
     // The loop with the tile GEMMs for more than many_rows live rows, as known
     // when the launch before the last one ended.  Either graph is right for any
@@ -659,7 +658,7 @@ extern "C" int sara_run(sara_ctx* c, const int32_t* d_forced_tok, int32_t graph_
     if (e != hipSuccess) { rc = hip_fail(e, "graph launch"); break; }
     iters += graph_iters;
     int slot = n & 1;
-    e = hipMemcpyAsync(&c->h_done[3 * slot], &c->ctl->done, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
+    e = hipMemcpyAsync(&c->h_poll->done[3 * slot], &c->ctl->done, 3 * sizeof(int32_t), hipMemcpyDeviceToHost, c->stream);
     if (e == hipSuccess) e = hipEventRecord(ev[slot], c->stream);
     if (e != hipSuccess) { rc = hip_fail(e, "poll"); break; }
     if (n > 0) {
@@ -862,8 +861,7 @@ extern "C" void sara_destroy(sara_ctx* c) {
   if (!c) return;
   (void)hipStreamSynchronize(c->stream);
   for (auto& g : c->loop_graph) drop_graph(g);
-  if (c->h_done) (void)hipHostFree(c->h_done);
-  if (c->h_forced) (void)hipHostFree(c->h_forced);
+  if (c->h_poll) (void)hipHostFree(c->h_poll);
   for (hipEvent_t e : c->prof_events) (void)hipEventDestroy(e);
   for (void* p : c->owned) (void)hipFree(p);
   delete c;

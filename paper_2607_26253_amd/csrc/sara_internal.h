@@ -224,8 +224,11 @@ struct sara_ctx {
   // forced-token table of the current sara_run, read through memory: the graphs
   // serve every table
   const int32_t** forced_dev = nullptr;
-  const int32_t** h_forced = nullptr;   // pinned
-  int32_t* h_done = nullptr;      // pinned: 2 x (done flag, error word, live rows)
+  struct Poll {
+    int32_t done[6];              // 2 x (done flag, error word, live rows)
+    const int32_t* forced;        // the table of the current sara_run
+  };
+  Poll* h_poll = nullptr;         // pinned
 
   std::vector<void*> owned;       // device allocations freed by sara_destroy
   // per-launch profiling of eager decode steps
