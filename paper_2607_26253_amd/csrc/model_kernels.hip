@@ -2,17 +2,20 @@
 //
 // Per layer, over the rows of a batch (occupied slots in decode, prompt
 // tokens in prefill):
-//   gemm(x, W_qkv) -> qkv epilogue (split-K sum, RoPE, bf16 q, paged KV append)
+//   q|k|v GEMM with RoPE and the paged KV append in its epilogue (a short bf16
+//   prefill chunk: split-K partials and k_qkv_epilogue)
 //   paged GQA attention over ragged contexts (split-context + combine)
 //   gemm(o, W_o)   -> residual add + RMSNorm -> x
-//   gemm(x, W_gu)  -> SwiGLU -> a
+//   gemm(x, W_gu) with SwiGLU in its epilogue -> a
 //   gemm(a, W_d)   -> residual add + RMSNorm of the next layer (or final) -> x
-// then the LM head gemm and the Gumbel-max sampler.
+// then the LM head gemm and the Gumbel-max sampler.  The layers of a bf16
+// prefill are in prefill_kernels.hip, its tile GEMM in gemm_tile.h.
 //
-// GEMMs take both operands with K contiguous ([rows][K]) and run on the
-// bf16 MFMA (v_mfma_f32_16x16x32_bf16) with fp32 accumulation; split-K
-// partials go to a workspace and are summed in split order by the epilogue,
-// so results do not depend on scheduling.  The fp32 model uses a VALU GEMM.
+// GEMMs take both operands with K contiguous and run on the bf16 MFMA
+// (v_mfma_f32_16x16x32_bf16), fp32 models' on the fp32 one
+// (v_mfma_f32_16x16x4_f32), with fp32 accumulation; split-K partials go to a
+// workspace and are summed in split order by the consumer, so results do not
+// depend on scheduling.
 #include <mutex>
 
 #include "gemm_tile.h"
@@ -353,7 +356,7 @@ __global__ __launch_bounds__(256) void k_embed_norm(const int32_t* __restrict__ 
 //  2. exact scores (fp64 noise, gumbel_exact) for the candidates whose bound
 //     reaches gumbel_candidate_floor(max): the block's exact winner is always
 //     among them, so the result equals an exact evaluation of every id;
-//  3. exact (score, id) maximum per row to sa.best / sa.idx [m][gridDim.x].
+//  3. exact (score, id) maximum per row to sa.best / sa.idx [vocabulary block][ld].
 // LDS: the X staging buffer, free after the k loop.  151936 ids, 32 rows: 88 us with
 // the GEMM against 95 with a logarithm an id and exact scores place by place;
 // 32768 ids, 512 rows: 119 against 174.

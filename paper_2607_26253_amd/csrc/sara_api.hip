@@ -37,9 +37,29 @@ static int einval(const std::string& msg) {
 const char* const kProfNames[kPNumClasses] = {
     "k_gemm_bf16_lds<1,8,64,0,0>", "k_gemm_bf16_lds<2,8,64,1,0>", "k_gemm_bf16_lds<2,8,64,2,0>",
     "k_attn_dec<128>", "k_attn_combine", "k_residual_norm_f4",
-    "k_embed_norm", "k_sample_partial", "k_sample_final", "k_decode_rows", "k_copy_logits", "k_qkv_rope",
+    "k_decode_embed", "k_sample_partial", "k_sample_final", "k_copy_logits", "k_qkv_rope",
     "k_topp_max", "k_topp_hist", "k_topp_pick", "k_gemm_bf16_lds<1,8,64,0,2>",
     ".gemm[q|k|v]", ".gemm[o]", ".gemm[gate|up]", ".gemm[down]", ".gemm[lm_head]"};
+
+// name of a class in this context: the instances above are those of a bf16 model
+// with heads of 128 and top_p = 1
+static std::string prof_name(const sara_ctx* c, int cls) {
+  const std::string hd = std::to_string(c->hd);
+  if (c->md.dtype == SARA_F32) {
+    switch (cls) {
+      case kPGemmN1: return "k_gemm_f32<2,0>";
+      case kPGemmGU: return "k_gemm_f32<2,1>";
+      case kPQkvRope: return "k_gemm_f32<2,2>";
+      case kPGemmLM: return "k_gemm_f32<2,0> lm_head";
+      case kPAttn: return "k_attention<" + hd + ">";
+      case kPResNorm: return "k_residual_norm_v";
+    }
+  } else {
+    if (cls == kPAttn) return "k_attn_dec<" + hd + ">";
+    if (cls == kPGemmLM && c->topp) return "k_gemm_bf16_lds<2,8,64,3,0>";
+  }
+  return kProfNames[cls];
+}
 
 // prof_begin reserves an event pair for the next kernel launch; launch_k
 // hands it to hipExtLaunchKernelGGL, which stamps the kernel's own start and
@@ -560,7 +580,7 @@ extern "C" int sara_reset_profile(sara_ctx* c) {
   c->prof_next_event = 0;
   c->prof_tot.assign(kPNumClasses, sara_kernel_profile{});
   for (int i = 0; i < kPNumClasses; ++i)
-    strncpy(c->prof_tot[i].name, kProfNames[i], sizeof(c->prof_tot[i].name) - 1);
+    strncpy(c->prof_tot[i].name, prof_name(c, i).c_str(), sizeof(c->prof_tot[i].name) - 1);
   return SARA_OK;
 }
 

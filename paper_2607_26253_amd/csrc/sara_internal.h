@@ -190,9 +190,9 @@ struct sara_ctx {
   int32_t* rows_M = nullptr;      // device row count of the prefill chunk
   int row_cap = 0;
   float* h = nullptr;             // [row_cap][d] residual stream
-  void* x = nullptr;              // [row_cap][max(d, ffn, qdim)] GEMM input (model dtype)
+  void* x = nullptr;              // [row_cap][max(d, qdim)] GEMM input (model dtype)
   void* qbuf = nullptr;           // [row_cap][hq][hd]
-  void* xa = nullptr;             // [row_cap][ffn] SwiGLU output (bf16 models)
+  void* xa = nullptr;             // [row_cap][ffn] SwiGLU output (model dtype)
   float* ws = nullptr;            // GEMM partial outputs
   float* attn_part = nullptr;
   float* samp_best = nullptr;
@@ -254,7 +254,7 @@ namespace sara {
 // one class per kernel (per template instance for the GEMMs, as a kernel
 // trace names them), then a breakdown of the GEMMs by weight matrix
 enum ProfClass { kPGemmN1, kPGemmGU, kPGemmLM, kPAttn, kPCombine, kPResNorm,
-                 kPEmbed, kPSampleP, kPSampleF, kPRows, kPCopy, kPQkvRope, kPToppMax, kPToppHist, kPToppSel,
+                 kPEmbed, kPSampleP, kPSampleF, kPCopy, kPQkvRope, kPToppMax, kPToppHist, kPToppSel,
                  kPGemmO1, kPGemmQkv, kPGemmO, kPGemmGu, kPGemmD, kPGemmLm, kPNumClasses };
 extern const char* const kProfNames[kPNumClasses];
 void prof_begin(sara_ctx* c);
