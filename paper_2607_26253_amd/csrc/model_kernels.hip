@@ -160,7 +160,7 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
     const float* __restrict__ w, int d, float eps, float* __restrict__ h, T* __restrict__ x,
     int U, int PB, int SB, const float2* __restrict__ rope, int half, float2* __restrict__ row_rope,
     AttnItem* __restrict__ items, int32_t* __restrict__ n_items, int spg, const PromptPlace* __restrict__ places,
-    int hkv, int rows_per_item, int resident) {
+    int hkv, int rows_per_item, int resident, int V) {
   __shared__ float red[4];
   __shared__ int scan[4];
   const int M = ctl->done ? 0 : ctl->M;
@@ -259,7 +259,8 @@ __global__ __launch_bounds__(256) void k_decode_embed(const Ctl* __restrict__ ct
     // rotation angles of this row's position, read by every layer's q|k|v kernel
     for (int e = threadIdx.x; e < half; e += 256) row_rope[(size_t)i * half + e] = rope[(size_t)r.pos * half + e];
     if (!do_embed) continue;
-    const T* er = embed + (size_t)tok * d;
+    // a row whose logits were all NaN has no best id and carries INT_MAX
+    const T* er = embed + (size_t)min((uint32_t)tok, (uint32_t)V - 1u) * d;
     float* hr = h + (size_t)i * d;
     float v[VPT][8];
     float ss = 0.f;
@@ -2565,7 +2566,7 @@ int launch_decode(sara_ctx* c, const int32_t* forced, const int32_t* const* forc
   launch_k(c, st, k_decode_embed<T_>, dim3(eg), dim3(256), 0, c->ctl, (const ActiveRow*)c->active, c->slot_gen,      \
            c->slot_tok, c->k, c->rows, c->rows_M, model_free ? 0 : 1, (const T_*)c->embed, c->norms, c->d,           \
            c->md.rms_eps, c->h, (T_*)c->x, c->U, c->PB, c->SB, c->rope, c->hd / 2, c->row_rope, items_, c->attn_nitems, \
-           kDecPages, (const PromptPlace*)c->places, c->hkv, 16 / c->G, attn_resident(c))
+           kDecPages, (const PromptPlace*)c->places, c->hkv, 16 / c->G, attn_resident(c), c->V)
   if (c->md.dtype == SARA_BF16) SARA_EMBED(uint16_t, model_free ? (AttnItem*)nullptr : c->attn_items);
   else SARA_EMBED(float, (AttnItem*)nullptr);
 #undef SARA_EMBED

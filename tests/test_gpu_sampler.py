@@ -50,3 +50,27 @@ def test_sampler_split(n, V, temp, top_p, shift):
             assert OS.near_tie(sc) or (top_p < 1.0 and OS.nucleus_margin(logits[i], temp, top_p) < 1e-8), (i, got[i], tok)
             skipped += 1
     assert skipped <= 1
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "f32"])
+@pytest.mark.parametrize("top_p", [1.0, 0.9])
+def test_decode_survives_nan_logits(dtype, top_p):
+    """A model whose logits are all NaN has no best id; the step still runs to
+    its end, with every rollout at the cap."""
+    import workloads as W
+    from tests.gpu_harness import device_setup, upload_pool
+    from tests.test_gpu_prefill import generic_cfg
+    lengths = [3, 9, 20]
+    cfg = generic_cfg(512, 4, 2, 64, 512, lengths, max_new=5, top_p=top_p)
+    cfg["model"].update(dtype=dtype, eos_id=-1)
+    w = W.make_weights(cfg)
+    w["lm_head"][:] = 0x7FC0 if dtype == "bf16" else np.nan
+    ctx, _ = device_setup(cfg, w)
+    pool = W.pool_with_lengths(cfg, lengths)
+    d_tok, d_p, _ = upload_pool(pool)
+    ctx.sara_begin_step(d_tok, pool["offsets"], d_p, None, 0)
+    ctx.sara_run(None, graph_iters=4)
+    q, r = ctx.sara_query(), ctx.read_rollouts()
+    ctx.close()
+    assert q["done"] and q["rollouts"] >= 3
+    assert set(r["length"].tolist()) <= {0, 5} and (r["length"] == 5).sum() == q["rollouts"]
