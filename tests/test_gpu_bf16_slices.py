@@ -248,11 +248,10 @@ def test_bf16_two_layer_long_context_strict():
 
 # prompt lengths of the full-length case: the longest context reaches the
 # long-rollout workload's range (prompt 4590 + 20 new tokens, 37 pages of
-# 128-token splits), every decode row has more than 8 splits (the merge runs
-# several batches of 8), and the pool's 7,387 prompt rows cross the 4,096-row
-# prefill chunk inside prompt 1
+# 128-token splits) and every decode row has more than 8 splits (the merge runs
+# several batches of 8).  (A prompt across two prefill chunks:
+# test_gpu_prefill.py, 33,000 rows.)
 FULL_LENGTH_PROMPTS = [1100, 4590, 1700]
-PREFILL_CHUNK_ROWS = 4096
 SPLIT_TOKENS = 8 * 16
 
 
@@ -260,23 +259,19 @@ SPLIT_TOKENS = 8 * 16
 def test_bf16_two_layer_full_length_contexts(name):
     """2 layers at the model's full width and vocabulary, teacher forced from
     the oracle, with contexts of 1,100-4,610 tokens: decode attention over up
-    to 37 context splits (the split merge's later batches of 8), a prompt
-    prefilled across two 4,096-row chunks, every row's logits within
-    3e-2 * rms element-wise, logs bit-exact, fused sampler = exact sampler."""
+    to 37 context splits (the split merge's later batches of 8), every row's
+    logits within 3e-2 * rms element-wise, logs bit-exact, fused sampler =
+    exact sampler."""
     lens = FULL_LENGTH_PROMPTS
     full = W.get_config(name)
     cfg = W.parity_slice(full, B=len(lens), N=8 * len(lens), prompt_len=(min(lens), max(lens)), max_new=20,
                          pool_U=len(lens))
     cfg["model"]["n_layers"] = 2
     pool = W.pool_with_lengths(cfg, lens, 0)
-    rows = np.concatenate([[0], np.cumsum(np.array(lens) - 1)])
-    straddle = [u for u in range(len(lens))
-                if rows[u] // PREFILL_CHUNK_ROWS != (rows[u + 1] - 1) // PREFILL_CHUNK_ROWS]
-    assert straddle, "no prompt crosses a prefill chunk"
     assert min(lens) - 1 > 8 * SPLIT_TOKENS       # every row: more than one batch of 8 splits
     w = cached_weights(cfg)
     seed = W.sampling_seed(cfg)
-    print(f"[full-length] {name}: prompts {lens}, prompts crossing a prefill chunk {straddle}", flush=True)
+    print(f"[full-length] {name}: prompts {lens}", flush=True)
     ora = ORUN.run_step(cfg, w, pool, seed, keep_logits=lambda u, j, i: True)
     ctx, _ = device_setup(cfg, w)
     gpu = run_gpu_step(ctx, cfg, pool, forced=forced_table(cfg, ora["rollouts_detail"]), capture_logits=True)
