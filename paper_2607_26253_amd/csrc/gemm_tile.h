@@ -1,5 +1,5 @@
 // The 256 x 256 tile GEMM of the bf16 models: every prefill projection of a long
-// chunk, and decode batches of more than one row tile.
+// chunk, and the many-row loop of decode.
 #pragma once
 
 #include "sara_internal.h"
@@ -31,8 +31,9 @@ namespace sara {
 // the decode GEMMs' (gemm_mblock), so with the same K splits the results are
 // bit-identical to theirs and a row's do not depend on which kernel ran.
 //
-// Bound by the matrix cores (and their clock under load): 1.3-1.4 PFLOP/s on
-// the prefill shapes (16384^3 library product: 1.6), where 128 x 128 tiles with
+// Bound by the matrix cores (and their clock under load): 1.2-1.3 PFLOP/s on
+// the prefill shapes (16384^3 library product: 1.6; gate|up of 80,000 rows, 1536
+// wide: 1.25, a tenth of it the SwiGLU epilogue), where 128 x 128 tiles with
 // register-staged activations reached 0.57-0.82 and all eight waves in phase on
 // the same ring 0.80-0.91.
 //
@@ -75,8 +76,8 @@ __global__ __launch_bounds__(512, 2) void k_gemm_tile(const uint16_t* __restrict
   // Block -> tile: ids are dealt to the 8 XCDs in turn; each XCD takes a
   // contiguous stretch of an order that walks 4 row tiles by every column
   // tile, so that the 32 blocks running at once on an XCD share few X and W
-  // tiles in its L2 (4 x 8: gate|up 1.36 PFLOP/s; 8 x 4 1.34, row tiles alone
-  // 1.20).
+  // tiles in its L2 (gate|up with a shorter SwiGLU: 4 x 8 1.36 PFLOP/s; 8 x 4 1.34,
+  // row tiles alone 1.20).
   int bn, bm;
   {
     const int nb = (ntl - a.tile0 + 15) >> 4, mb = (mtl + 15) >> 4, total = nb * mb;
