@@ -309,7 +309,10 @@ int grpo_group_advantages(const float* d_r, const int32_t* d_group_off, int32_t 
  * d_logits[r][vocab] fp32, rollout ids d_rid[r], generated indices d_pos[r]
  * -> d_tok[r] (Gumbel-max at temperature over the top-p nucleus, the whole
  * vocabulary when top_p = 1; forced EOS if eos_id >= 0 and forced_eos_u32 >
- * 0).  top_p in (0, 1], else SARA_EINVAL.  Synchronises the stream. */
+ * 0).  top_p in (0, 1], else SARA_EINVAL.  -inf logits are masked ids.  At
+ * top_p = 1 a +inf logit wins over all finite ones (the lowest id of several)
+ * and a NaN never wins; a row of NaN only gives INT32_MAX.  With top_p < 1 a
+ * row's largest logit must be finite.  Synchronises the stream. */
 int sara_sample_logits(const float* d_logits, int32_t n_rows, int32_t vocab,
                        const int32_t* d_rid, const int32_t* d_pos, uint64_t seed,
                        int32_t step_index, float temperature, float top_p, int32_t eos_id,
@@ -339,11 +342,12 @@ int sara_sample_logits_noalloc(const float* d_logits, int32_t n_rows, int32_t vo
                                uint32_t forced_eos_u32, int32_t* d_tok, void* stream);
 
 /* Self-check of the fused LM-head sampler (bf16 models).  That sampler
- * scores every vocabulary id with an fp32 estimate of the Gumbel noise and
+ * bounds the score of every vocabulary id from the bits of its noise word,
+ * scores the best bounds with an fp32 estimate of the Gumbel noise, and
  * re-scores exactly (fp64 noise rounded to fp32, the definition of the noise
- * above) only the ids whose estimate lies within a fixed margin of the best;
- * its output equals the exact Gumbel-max provided the estimate is within
- * 2e-5 of the exact noise for every input.  This call evaluates both for all
+ * above) only the ids whose bound reaches the best such score less a fixed
+ * margin; its output equals the exact Gumbel-max provided the estimate is
+ * within 2e-5 of the exact noise for every input.  This call evaluates both for all
  * 2^24 noise inputs on the device and writes the largest absolute distance
  * to *h_out (host).  Synchronous on stream; returns SARA_EHIP on HIP
  * failure. */
