@@ -2419,7 +2419,7 @@ static void decode_layers_bf16(sara_ctx* c, const int32_t* M_ptr, int M_cap) {
     PROF_E(c, kPAttn, 0, 0);
     PROF_B(c);
     // blocks of two waves: 1024 leave a CU 8 waves (512 rows of 16 heads: 14.0 us,
-    // 10.5 with 4096), but exit sooner where a few rows need no more
+    // 10.5 with 4096, 8.9 with base-2 weights), but exit sooner where a few rows need no more
     launch_k(c, st, (k_attn_combine<uint16_t, HD>), dim3(c->tile_rows ? 4096 : 1024), dim3(HD), 0, M_ptr, c->rows, c->attn_part, c->hq,
              c->hkv, c->dec_splits_max, kDecPages, 1, x);
     PROF_E(c, kPCombine, 0, 0);

@@ -41,7 +41,7 @@ namespace sara {
 // Bound by the vector unit and the MFMA about equally (per 16 tokens x 64 keys
 // at hd 128: 48 MFMAs = 768 cycles, and 16 exponentials and about 170 other
 // vector instructions).  4096 rows of 128-512-token prompts, 12 query heads:
-// 36 us, where one block per (query row, KV head, 256-token split) and a merge
+// 36-38 us, where one block per (query row, KV head, 256-token split) and a merge
 // pass took 215; three prompts of 1,100-4,590 tokens, 16 heads: 192 us a
 // chunk against 873.
 template <int HD, int NW>
